@@ -134,7 +134,8 @@ typedef struct jf_plan jf_plan;
                                   and replay it (see there) */
 #define JF_FLAG_NO_CHAIN 16u   /* run every step as its own launch: no chains of in-place complex64
                                   steps applied to one LDS tile per HBM pass (same results bit for
-                                  bit; chains are the default) */
+                                  bit; chains are the default), no runs of small steps in one
+                                  launch (FP64 arithmetic: results of the form's accuracy) */
 /* Search effort of the planner: JF_FLAG_EFFORT(e), e = 1..15, runs 2^(e+5) randomised greedy
  * restarts per component.  The default (e = 0 in the flags) sizes the search to the network:
  * min(2^17, max(2^12, 8e7 / tensors)) restarts, i.e. 2^17 up to ~600 tensors and 2^16 at ~1200,
@@ -269,7 +270,9 @@ jf_status jf_fidelity_noalloc(jf_plan* plan, void* stream, jf_result* out, doubl
  * with a pair of HIP events attached to the dispatch of every contraction-step kernel
  * (hipExtLaunchKernelGGL: the events time the kernel itself, not the queue gaps around it), and
  * reports the summed kernel time together with the algorithmic bytes and flops of those
- * launches (each step reads its input tensor and writes its output once).  F_J is not returned.
+ * launches (each step reads its input tensor and writes its output once).  The steps that a
+ * fidelity call runs several to a launch (small tensors) are launched one by one here.  F_J is not
+ * returned.
  */
 typedef struct {
   long long launches;   /* contraction-step kernel launches */
@@ -346,7 +349,7 @@ typedef enum {
  * can run the step (a warm-up launch, then reps launches between HIP events, on the step's own
  * input and output buffers) and keeps the fastest for all later runs of this plan; a chain of
  * steps is timed as one launch against its steps run one launch each (with their tuned kernels)
- * and the faster is kept.  The
+ * and the faster is kept, and so is a run of small steps in one launch against theirs.  The
  * workspace contents are undefined afterwards (no result is produced).  Choices are cached for
  * the process by step shape (arithmetic, kS, kN, rows per tile, tile count, in place or not) and
  * by chain shape, so plans sharing shapes are tuned once.  A chain computes exactly what its steps
@@ -360,11 +363,19 @@ jf_status jf_autotune(jf_plan* plan, void* dev_ws, size_t ws_bytes, void* stream
 /*
  * jf_set_kernel_variant -- force one kernel (jf_kernel_variant) on every step it can run; the
  * other steps keep the AUTO rule.  Chains stay chains under JF_KV_GAUSS_256 / 512 (they compute
- * the Gauss form) and are split into their steps under the other kernels.  JF_KV_AUTO restores the
- * rule and the chains everywhere (and so undoes jf_autotune).  For testing each kernel against
+ * the Gauss form) and are split into their steps under the other kernels; small steps then get a
+ * launch each.  JF_KV_AUTO restores the
+ * rule, the chains and the runs of small steps everywhere (and so undoes jf_autotune).  For testing each kernel against
  * the oracle.  Host only.  Errors: JF_E_ARG (JF_KV_CHAIN is not a per-step kernel).
  */
 jf_status jf_set_kernel_variant(jf_plan* plan, int variant);
+
+/*
+ * jf_set_grid_wait -- test aid: the longest wait, in ticks of the device's 100 MHz wall clock, of the
+ * barrier between the steps that one launch runs (default 2 s; 0 gives up at once).  A pass whose
+ * barrier gives up is run again with one launch per step before the call returns.  Host only.
+ */
+jf_status jf_set_grid_wait(jf_plan* plan, long long ticks);
 
 /* Definition 1: C1 and C2 are epsilon-equivalent iff F_J > 1 - eps (strict). Returns 1/0,
  * or -1 for a NULL result. */

@@ -104,6 +104,29 @@ bool validate_program(const Program& P, std::string& why) {
         return false;
       }
     }
+    int run_end = 0;
+    for (const GridRun& r : cp.runs) {
+      bool ok = r.first >= run_end && r.last - r.first >= 2 && r.last - r.first <= GRID_MAX_STEPS &&
+                r.last <= (int)cp.steps.size();
+      int lvl = -1;
+      for (int s = r.first; ok && s < r.last; ++s) {
+        const Step& st = cp.steps[s];
+        GridTables tb;
+        grid_tables(st, tb);
+        ok = grid_step_ok(st) && tb.F == st.rA - st.kS && tb.F + st.kN == st.rC && tb.lr >= 0 && tb.lr <= tb.F &&
+             st.kS + tb.lr <= GRID_TILE && (!st.final_step || s + 1 == r.last);
+        for (size_t l = 0; l < cp.levels.size(); ++l)
+          if (s >= cp.levels[l].first && s < cp.levels[l].last) {
+            if (lvl < 0) lvl = int(l);
+            ok = ok && lvl == int(l);
+          }
+      }
+      if (!ok) {
+        why = "grid run of component " + std::to_string(c) + " is malformed";
+        return false;
+      }
+      run_end = r.last;
+    }
     {  // the offsets of the Kraus-site levels and a leaf's output stay inside the output array
       long long top = 0;
       for (auto& lv : cp.levels) top += (lv.nvar - 1) * lv.out_stride;
@@ -185,6 +208,25 @@ void emulate_step(const Step& st, const std::vector<cd>& B, const cd* A, cd* C) 
   }
 }
 
+// The same step with the row addressing of a grid run.
+void emulate_grid_step(const Step& st, const std::vector<cd>& B, const cd* A, cd* C) {
+  GridTables tb;
+  grid_tables(st, tb);
+  const int K = 1 << st.kS, Nn = 1 << st.kN;
+  for (long long f = 0; f < (1LL << tb.F); ++f) {
+    unsigned a = 0, c = 0;
+    for (int d = 0; d < GRID_DIGITS; ++d) {
+      a += tb.digA[d][(f >> (4 * d)) & 15];
+      c += tb.digC[d][(f >> (4 * d)) & 15];
+    }
+    for (int n = 0; n < Nn; ++n) {
+      cd acc = 0;
+      for (int s = 0; s < K; ++s) acc += A[a + st.offS_A[s]] * B[size_t(s) * Nn + n];
+      C[c + st.offN_C[n]] = acc;
+    }
+  }
+}
+
 // A chain on the host with the tile-local tables of the chain kernel: per tile, gather 2^T
 // elements, apply every step of the chain in place on the tile, scatter the tile back.
 void emulate_chain(const ComponentProgram& cp, const Chain& ch, const std::vector<const std::vector<cd>*>& Bs,
@@ -229,6 +271,9 @@ void emulate_level(const ComponentProgram& cp, int lv, const std::vector<cd>& pa
     for (int si = L.first; si < L.last; ++si) {
       const Step& st = cp.steps[si];
       const std::vector<cd>& B = st.B[variant_index(cp, st, vv)];
+      bool in_run = false;
+      for (const GridRun& r : cp.runs) in_run = in_run || (si >= r.first && si < r.last);
+      const auto emulate = in_run ? emulate_grid_step : emulate_step;
       if (st.chain >= 0 && cp.chains[st.chain].first == si) {
         const Chain& ch = cp.chains[st.chain];
         std::vector<const std::vector<cd>*> Bs;
@@ -241,14 +286,14 @@ void emulate_level(const ComponentProgram& cp, int lv, const std::vector<cd>& pa
         cd* dst = out.data() + out_base + v * L.out_stride;
         if (cp.accumulate) {  // a partial result of the sliced wires: added in
           std::vector<cd> leaf(size_t(cp.leaf_len), 0.0);
-          emulate_step(st, B, cur.data(), leaf.data());
+          emulate(st, B, cur.data(), leaf.data());
           for (long long i = 0; i < cp.leaf_len; ++i) dst[i] += leaf[size_t(i)];
         } else {
-          emulate_step(st, B, cur.data(), dst);
+          emulate(st, B, cur.data(), dst);
         }
       } else {
         nxt.assign(size_t(1) << st.rC, 0.0);
-        emulate_step(st, B, cur.data(), nxt.data());
+        emulate(st, B, cur.data(), nxt.data());
         cur.swap(nxt);
       }
     }

@@ -28,6 +28,8 @@
 namespace jf {
 
 static_assert(LDS_RESIDENT_MAX == LDS_RESIDENT_LOG2, "the planner's LDS-resident components fit the persistent kernel");
+static_assert(GRID_MAX_STEPS == GRID_STEPS && GRID_DIGITS == 5 && GRID_LOCAL == 10 && GRID_TILE == 11,
+              "the planner's grid runs fit k_grid");
 
 namespace {
 
@@ -40,11 +42,15 @@ struct DevLayout {
   size_t res_off = 0;    // F_J, 1 - F_J, |Im|, written by the device
   size_t lds_items_off = 0, lds_steps_off = 0;
   size_t ctr_off = 0;    // counter of the persistent launch's fused assembly (zero in the image)
+  size_t fail_off = 0;   // failure word of the grid runs (zero in the image)
+  size_t flags_off = 0;  // barrier flags of the grid runs (zero in the image)
+  size_t grid_bytes = 0; // bytes of the workspace that only the grid runs use
   std::vector<size_t> leaf_off;                           // per component with sliced wires: its leaf buffer
   std::vector<int> lds_comps;                             // components run by the persistent kernel
   int lds_steps = 0;
   std::vector<std::vector<size_t>> step_desc;             // per component, per step: descriptor offset
   std::vector<std::vector<size_t>> chain_desc;            // per component, per chain: descriptor offset
+  std::vector<std::vector<size_t>> run_desc;              // per component, per grid run: its steps' GridSteps
   std::vector<std::vector<std::vector<size_t>>> step_b;   // per component, step, variant: B offset
   std::vector<std::vector<size_t>> level_buf;             // per component: 2 buffers per level, offsets in
                                                           // the buffer region [buf_off, total)
@@ -74,6 +80,10 @@ struct DevState {
   // per component, per chain: 1 = run its steps one launch each (the autotuner found the chain
   // slower, or a kernel variant was forced on every step)
   std::vector<std::vector<char>> chain_off;
+  // per component, per grid run: 1 = run its steps launch by launch (the autotuner found the run
+  // slower, or a kernel variant was forced)
+  std::vector<std::vector<char>> run_off;
+  long long grid_wait = 200000000;          // longest wait of a grid barrier: 2 s of the 100 MHz wall clock
   bool validated = false;                   // the program passed validate_program (plans are immutable)
   hipEvent_t ev_order = nullptr, ev0 = nullptr, ev1 = nullptr;
   // pinned host landing area of the component sums (4 doubles each): a pageable destination
@@ -255,6 +265,46 @@ void balanced_round(const std::vector<cd>& M, std::vector<float>& out) {
     }
 }
 
+// The most bytes of a workspace that grid runs may add (the no-allocation scratch holds them beside
+// JF_NOALLOC_BYTES).
+constexpr size_t kGridTableBytes = 1 << 20;
+
+// The device descriptors of a grid run: where each step's tensors are (a step whose tensors hold at
+// most 2^GRID_LOCAL elements runs in every workgroup's LDS; the last step of a run that is not the
+// component's last leaves its output in memory) and its addressing.
+std::vector<GridStep> grid_descriptors(const ComponentProgram& cp, const GridRun& run) {
+  std::vector<GridStep> out(size_t(run.last - run.first));
+  bool in_lds = false;  // the previous step's output
+  for (int s = run.first; s < run.last; ++s) {
+    const Step& st = cp.steps[s];
+    GridTables tb;
+    grid_tables(st, tb);
+    GridStep& d = out[size_t(s - run.first)];
+    std::memset(&d, 0, sizeof(d));
+    const bool local = st.rA <= GRID_LOCAL && st.rC <= GRID_LOCAL;
+    GridShape g = {};
+    g.kS = st.kS;
+    g.kN = st.kN;
+    g.F = tb.F;
+    g.lr = tb.lr;
+    g.in32 = st.in_prec == P_C64;
+    g.out32 = st.out_prec == P_C64;
+    g.mode = mode_of(st);
+    g.final_step = st.final_step;
+    g.src_lds = in_lds || local;
+    g.dst_lds = local && (st.final_step || s + 1 < run.last);
+    in_lds = g.dst_lds;
+    d.shape = g.pack();
+    for (size_t i = 0; i < st.offS_A.size(); ++i) d.offS[i] = unsigned(st.offS_A[i]);
+    for (size_t i = 0; i < st.offN_C.size(); ++i) d.offN[i] = unsigned(st.offN_C[i]);
+    for (int q = 0; q < 16 * GRID_DIGITS; ++q) {
+      d.digA[q] = tb.digA[q / 16][q % 16];
+      d.digC[q] = tb.digC[q / 16][q % 16];
+    }
+  }
+  return out;
+}
+
 void build_layout(const Program& P, DevState& S) {
   DevLayout& L = S.lay;
   size_t off = 0;
@@ -301,7 +351,32 @@ void build_layout(const Program& P, DevState& S) {
   L.lds_steps_off = off;
   off += align256(size_t(L.lds_steps) * sizeof(LdsStep));
   L.ctr_off = off;
+  L.fail_off = off + 128;
   off += 256;
+  // grid runs: descriptors and barrier flags, at most kGridTableBytes (else the plan runs without)
+  L.run_desc.resize(P.comps.size());
+  S.run_off.resize(P.comps.size());
+  size_t table = GRID_WGS * GRID_FLAG_STRIDE * sizeof(unsigned);
+  bool any_run = false;
+  for (auto& cp : P.comps)
+    if (!cp.lds_resident)
+      for (const GridRun& r : cp.runs) {
+        table += align256(size_t(r.last - r.first) * sizeof(GridStep));
+        any_run = true;
+      }
+  if (any_run && table <= kGridTableBytes) {
+    L.grid_bytes = table;
+    L.flags_off = off;
+    off += GRID_WGS * GRID_FLAG_STRIDE * sizeof(unsigned);
+    for (size_t c = 0; c < P.comps.size(); ++c) {
+      if (P.comps[c].lds_resident) continue;
+      S.run_off[c].assign(P.comps[c].runs.size(), 0);
+      for (const GridRun& r : P.comps[c].runs) {
+        L.run_desc[c].push_back(off);
+        off += align256(size_t(r.last - r.first) * sizeof(GridStep));
+      }
+    }
+  }
   L.image_end = off;
   L.out_off = off;
   long long outn = 0;
@@ -438,6 +513,11 @@ void build_layout(const Program& P, DevState& S) {
       }
       d.ops = boff;
       std::memcpy(&S.host_image[L.chain_desc[c][q]], &d, sizeof(d));
+    }
+  for (size_t c = 0; c < P.comps.size(); ++c)
+    for (size_t q = 0; q < L.run_desc[c].size(); ++q) {
+      const std::vector<GridStep> d = grid_descriptors(P.comps[c], P.comps[c].runs[q]);
+      std::memcpy(&S.host_image[L.run_desc[c][q]], d.data(), d.size() * sizeof(GridStep));
     }
   double one = 1.0, zero = 0.0;
   float onef = 1.0f, zerof = 0.0f;
@@ -611,26 +691,136 @@ jf_status tune_chain(DevState& S, size_t c, int q, const ChainDesc* dd, const Ch
   return JF_OK;
 }
 
-// Enqueue the steps of level lv of component c for Kraus variant v of the level's sliced site,
-// starting from `parent` (nullptr: the constant 1 of the first step's precision), the component's
-// output at element offset `base`; *end receives the level's last output (no synchronisation).
-jf_status enqueue_level(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipStream_t stream, size_t c, int lv,
-                        const std::vector<int>& vv, const void* parent, long long base, const void** end, Prof* prof,
-                        Tune* tune) {
+// How a pass uses grid runs, and what their last launch took over.
+struct GridUse {
+  bool assemble = false;   // nothing is left to do before the assembly once this component is summed
+  bool summed = false;     // the component's sum of |t|^2 is done
+  bool assembled = false;  // and the assembly
+};
+
+int run_starting_at(const ComponentProgram& cp, int si) {
+  for (size_t q = 0; q < cp.runs.size(); ++q)
+    if (cp.runs[q].first == si) return int(q);
+  return -1;
+}
+
+// The buffer that holds a grid run's output: the steps that write memory alternate between the
+// level's buffers as k_grid does.
+const void* grid_output(const GridArgs& a) {
+  const void* cur = a.in;
+  for (int i = 0; i < a.n; ++i)
+    if (!GridShape::unpack(a.shape[i]).dst_lds) cur = cur == a.buf[0] ? a.buf[1] : a.buf[0];
+  return cur;
+}
+
+AssembleArgs assemble_args(jf_plan* p, unsigned char* ws);
+jf_status enqueue_steps(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipStream_t stream, size_t c, int lv,
+                        int from, int to, const std::vector<int>& vv, const void* cur, long long base, const void** end,
+                        Prof* prof, Tune* tune, GridUse* gu);
+
+// Process-wide cache of grid-run decisions (1 = launch by launch), keyed by the steps' shapes.
+std::map<std::vector<long long>, int> g_run_cache;
+
+// Time a grid run against its steps' own launches (tuned, chains included) and keep the faster.
+jf_status tune_run(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipStream_t stream, size_t c, int lv, int q,
+                   const std::vector<int>& vv, const void* in, long long base, int reps) {
+  DevState& S = state_of(p);
+  const ComponentProgram& cp = p->prog.comps[c];
+  const GridRun& run = cp.runs[q];
+  std::vector<long long> key;
+  for (int s = run.first; s < run.last; ++s) {
+    const Step& st = cp.steps[s];
+    for (long long v : {(long long)st.kS, (long long)st.kN, (long long)st.rA, (long long)st.rC, (long long)mode_of(st),
+                        (long long)st.chain >= 0 ? 1LL : 0LL, (long long)st.final_step})
+      key.push_back(v);
+  }
+  {
+    std::lock_guard<std::mutex> g(g_tune_mu);
+    auto it = g_run_cache.find(key);
+    if (it != g_run_cache.end()) {
+      S.run_off[c][q] = char(it->second);
+      return JF_OK;
+    }
+  }
+  EventPair ev;
+  JF_HIP(hipEventCreate(&ev.a));
+  JF_HIP(hipEventCreate(&ev.b));
+  float ms[2] = {0, 0};
+  for (int mode = 0; mode < 2; ++mode) {
+    S.run_off[c][q] = char(mode);
+    const void* end = nullptr;
+    GridUse gu;
+    for (int r = 0; r <= reps; ++r) {  // the first is the warm-up
+      if (r == 1) JF_HIP(hipEventRecord(ev.a, stream));
+      const jf_status st = enqueue_steps(p, ws, bufs, stream, c, lv, run.first, run.last, vv, in, base, &end, nullptr,
+                                         nullptr, &gu);
+      if (st != JF_OK) return st;
+    }
+    JF_HIP(hipEventRecord(ev.b, stream));
+    JF_HIP(hipEventSynchronize(ev.b));
+    JF_HIP(hipEventElapsedTime(&ms[mode], ev.a, ev.b));
+  }
+  S.run_off[c][q] = ms[0] <= ms[1] ? 0 : 1;
+  std::lock_guard<std::mutex> g(g_tune_mu);
+  g_run_cache[key] = S.run_off[c][q];
+  return JF_OK;
+}
+
+// Enqueue steps [from, to) of level lv of component c (the levels at the values vv) on the tensor
+// `cur`, the component's output at element offset `base`; *end receives the last output (no
+// synchronisation).  gu not null: grid runs go out as one launch each.
+jf_status enqueue_steps(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipStream_t stream, size_t c, int lv,
+                        int from, int to, const std::vector<int>& vv, const void* cur, long long base, const void** end,
+                        Prof* prof, Tune* tune, GridUse* gu) {
   const ComponentProgram& cp = p->prog.comps[c];
   DevState& S = state_of(p);
   const DevLayout& L = S.lay;
-  const Level& lev = cp.levels[lv];
   unsigned char* out = ws + L.out_off + size_t(cp.out_off) * 16;
-  const void* cur = parent;
-  if (!cur) {
-    const Step& s0 = cp.steps[lev.first < lev.last ? lev.first : 0];
-    cur = ws + L.const_off + (s0.in_prec == P_C64 ? 16 : 0);
-  }
   unsigned char* b0 = bufs + L.level_buf[c][2 * lv];
   unsigned char* b1 = bufs + L.level_buf[c][2 * lv + 1];
-  for (int si = lev.first; si < lev.last; ++si) {
+  for (int si = from; si < to; ++si) {
     const Step& st = cp.steps[si];
+    if (gu) {
+      const int q = run_starting_at(cp, si);
+      if (q >= 0 && q < (int)L.run_desc[c].size() && !S.run_off[c][q]) {
+        const GridRun& run = cp.runs[q];
+        GridArgs a = {};
+        a.steps = reinterpret_cast<const GridStep*>(ws + L.run_desc[c][q]);
+        a.n = run.last - run.first;
+        a.in = cur;
+        a.buf[0] = b0;
+        a.buf[1] = b1;
+        a.flags = reinterpret_cast<unsigned*>(ws + L.flags_off);
+        a.fail = reinterpret_cast<unsigned*>(ws + L.fail_off);
+        a.limit = S.grid_wait;
+        const GridStep* hs = reinterpret_cast<const GridStep*>(&S.host_image[L.run_desc[c][q]]);
+        for (int k = 0; k < a.n; ++k) a.shape[k] = hs[k].shape;
+        for (int k = run.first; k < run.last; ++k)
+          a.B[k - run.first] = ws + L.step_b[c][k][variant_index(cp, cp.steps[k], vv)];
+        const Step& fs = cp.steps[run.last - 1];
+        if (fs.final_step) {
+          a.out = cp.accumulate ? static_cast<void*>(ws + L.leaf_off[c]) : static_cast<void*>(out + size_t(base) * 16);
+          // one workgroup sums the output, so a large one keeps its own launches (as launch_sumsq)
+          if (fs.rC <= 14 && cp.leaves == 1 && !cp.accumulate && cp.out_len == (1LL << fs.rC)) {
+            a.sums = reinterpret_cast<double*>(ws + L.sums_off) + 4 * c;
+            gu->summed = true;
+            if (gu->assemble) {
+              a.as = assemble_args(p, ws);
+              gu->assembled = true;
+            }
+          }
+        }
+        JF_HIP(launch_grid(a, stream));
+        if (fs.final_step) {
+          if (cp.accumulate) JF_HIP(launch_accumulate(out + size_t(base) * 16, a.out, cp.leaf_len, stream));
+          cur = a.out;
+        } else {
+          cur = grid_output(a);
+        }
+        si = run.last - 1;
+        continue;
+      }
+    }
     if (st.chain >= 0 && cp.chains[st.chain].first == si && (tune || !S.chain_off[c][st.chain])) {
       // a chain: steps [first, last) in one launch, in place when the input is this level's
       const Chain& ch = cp.chains[st.chain];
@@ -742,10 +932,41 @@ jf_status enqueue_level(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipS
   return JF_OK;
 }
 
+// Enqueue the steps of level lv from `parent` (nullptr: the constant 1 of the first step's precision).
+// On the first visit of a tuning pass the level's grid runs are timed too, after their steps.
+jf_status enqueue_level(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipStream_t stream, size_t c, int lv,
+                        const std::vector<int>& vv, const void* parent, long long base, const void** end, Prof* prof,
+                        Tune* tune, GridUse* gu) {
+  const ComponentProgram& cp = p->prog.comps[c];
+  DevState& S = state_of(p);
+  const DevLayout& L = S.lay;
+  const Level& lev = cp.levels[lv];
+  const void* cur = parent;
+  if (!cur) {
+    const Step& s0 = cp.steps[lev.first < lev.last ? lev.first : 0];
+    cur = ws + L.const_off + (s0.in_prec == P_C64 ? 16 : 0);
+  }
+  const void* start = cur;
+  jf_status st = enqueue_steps(p, ws, bufs, stream, c, lv, lev.first, lev.last, vv, cur, base, end, prof, tune,
+                               prof || tune ? nullptr : gu);
+  if (st != JF_OK || !tune || !gu) return st;
+  for (size_t q = 0; q < L.run_desc[c].size(); ++q) {
+    const GridRun& run = cp.runs[q];
+    if (run.first < lev.first || run.last > lev.last || tune->done[c][run.first] == 2) continue;
+    // the run's input: the level's, or what an earlier step of the level left in a level buffer (the
+    // data is garbage by now, which the timing does not see)
+    const void* in = run.first == lev.first ? start : bufs + L.level_buf[c][2 * lv + 1];
+    st = tune_run(p, ws, bufs, stream, c, lv, int(q), vv, in, base, tune->reps);
+    if (st != JF_OK) return st;
+    tune->done[c][run.first] = 2;
+  }
+  return JF_OK;
+}
+
 // Clear component c's output and walk its levels depth first: every prefix is computed once and
 // kept in its level buffer while the Kraus operators of the next sliced site are iterated.
 jf_status enqueue_component(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipStream_t stream, size_t c, Prof* prof,
-                            Tune* tune) {
+                            Tune* tune, GridUse* gu) {
   const ComponentProgram& cp = p->prog.comps[c];
   const DevLayout& L = state_of(p).lay;
   // Every output entry is written by the final steps of the leaves, except where leaves add
@@ -774,7 +995,7 @@ jf_status enqueue_component(jf_plan* p, unsigned char* ws, unsigned char* bufs, 
     vv[f.lv] = f.v;
     const long long base = f.base + f.v * lev.out_stride;
     const void* cur = nullptr;
-    jf_status st = enqueue_level(p, ws, bufs, stream, c, f.lv, vv, f.parent, base, &cur, prof, tune);
+    jf_status st = enqueue_level(p, ws, bufs, stream, c, f.lv, vv, f.parent, base, &cur, prof, tune, gu);
     if (st != JF_OK) return st;
     if (f.lv + 1 < (int)cp.levels.size()) stack.push_back({f.lv + 1, 0, cur, base});
   }
@@ -827,20 +1048,20 @@ AssembleArgs assemble_args(jf_plan* p, unsigned char* ws) {
   a.v0im = v0.imag();
   a.res = reinterpret_cast<double*>(ws + S.lay.res_off);
   a.host = S.pinned_res_dev;
+  a.fail = reinterpret_cast<const unsigned*>(ws + S.lay.fail_off);
   a.counter = reinterpret_cast<unsigned*>(ws + S.lay.ctr_off);
   return a;
 }
 
 // The product over components and 1 - F_J of a plan, on the device (after all its components).
 jf_status enqueue_assemble(jf_plan* p, unsigned char* ws, hipStream_t stream) {
-  const AssembleArgs a = assemble_args(p, ws);
-  JF_HIP(launch_assemble(a.sums, a.ncomp, a.alg, a.a, a.v0re, a.v0im, a.res, a.host, stream));
+  JF_HIP(launch_assemble(assemble_args(p, ws), stream));
   return JF_OK;
 }
 
 jf_status enqueue_program(jf_plan* p, unsigned char* ws, hipStream_t stream, Prof* prof = nullptr,
                           bool skip_lds = false, Tune* tune = nullptr, unsigned char* bufs = nullptr,
-                          hipStream_t side = nullptr, bool assemble = true) {
+                          hipStream_t side = nullptr, bool assemble = true, bool grid = true) {
   const Program& P = p->prog;
   DevState& S = state_of(p);
   const DevLayout& L = S.lay;
@@ -862,17 +1083,26 @@ jf_status enqueue_program(jf_plan* p, unsigned char* ws, hipStream_t stream, Pro
                                                   side, S.ev_fork, S.ev_join);
     if (st != JF_OK) return st;
   }
+  grid = grid && L.grid_bytes > 0 && grid_fits_device();
+  size_t last = 0;  // the last component on this stream
+  for (size_t c = 0; c < P.comps.size(); ++c)
+    if (!P.comps[c].lds_resident) last = c;
+  bool assembled = false;
   for (size_t c = 0; c < P.comps.size(); ++c) {
     const ComponentProgram& cp = P.comps[c];
     if (cp.lds_resident) continue;
-    jf_status st = enqueue_component(p, ws, bufs, stream, c, prof, tune);
+    GridUse gu;
+    gu.assemble = assemble && !side && c == last;
+    jf_status st = enqueue_component(p, ws, bufs, stream, c, prof, tune, grid ? &gu : nullptr);
     if (st != JF_OK) return st;
-    JF_HIP(launch_sumsq(ws + L.out_off + size_t(cp.out_off) * 16, cp.out_len,
-                        reinterpret_cast<double*>(ws + L.sums_off) + 4 * c,
-                        reinterpret_cast<double*>(ws + L.sumsq_off), stream));
+    if (!gu.summed)
+      JF_HIP(launch_sumsq(ws + L.out_off + size_t(cp.out_off) * 16, cp.out_len,
+                          reinterpret_cast<double*>(ws + L.sums_off) + 4 * c,
+                          reinterpret_cast<double*>(ws + L.sumsq_off), stream));
+    assembled = gu.assembled;
   }
   if (side) JF_HIP(hipStreamWaitEvent(stream, S.ev_join, 0));
-  return assemble ? enqueue_assemble(p, ws, stream) : JF_OK;
+  return assemble && !assembled ? enqueue_assemble(p, ws, stream) : JF_OK;
 }
 
 // Copy the plan's tables into ws (unless they are there already).  region: the bytes from ws on
@@ -952,8 +1182,8 @@ jf_status pinned_res_of(jf_plan* p) {
 // assembly kernel has written the result into the plan's pinned landing area (pinned_res_of before
 // the enqueue), so only the terms need a copy; without (the no-allocation entry point: no host
 // allocation by the library), the result is copied into pageable host memory.
-jf_status read_results(jf_plan* p, unsigned char* ws, hipStream_t stream, jf_result* out, double* terms,
-                       bool pinned = true) {
+jf_status read_results(jf_plan* p, unsigned char* ws, hipStream_t stream, jf_result* out, double* terms, bool pinned,
+                       bool* gave_up) {
   const Program& P = p->prog;
   DevState& S = state_of(p);
   double res[4];
@@ -970,6 +1200,8 @@ jf_status read_results(jf_plan* p, unsigned char* ws, hipStream_t stream, jf_res
   }
   JF_HIP(hipStreamSynchronize(stream));
   if (on_host) std::memcpy(res, S.pinned_res, sizeof(res));
+  *gave_up = res[3] != 0.0;
+  if (*gave_up) return JF_OK;
   jf_result r;
   static_result(P, &r);
   r.fj = res[0];
@@ -978,6 +1210,25 @@ jf_status read_results(jf_plan* p, unsigned char* ws, hipStream_t stream, jf_res
   *out = r;
   if (terms) gather_terms(P, co, terms);
   return JF_OK;
+}
+
+// Wait for a pass and read it back; a pass whose grid runs gave up waiting (their workgroups were not
+// resident together: the device was held by others) is run again with a launch per step.  bufs and
+// skip_lds as in enqueue_program (a batch member).
+jf_status finish_pass(jf_plan* p, unsigned char* ws, hipStream_t stream, jf_result* out, double* terms,
+                      bool pinned = true, unsigned char* bufs = nullptr, bool skip_lds = false) {
+  bool gave_up = false;
+  jf_status st = read_results(p, ws, stream, out, terms, pinned, &gave_up);
+  if (st != JF_OK || !gave_up) return st;
+  const DevState& S = state_of(p);
+  const DevLayout& L = S.lay;
+  // the failure word and the barrier flags as they were uploaded: zero
+  JF_HIP(hipMemcpyAsync(ws + L.fail_off, &S.host_image[L.fail_off], sizeof(unsigned), hipMemcpyHostToDevice, stream));
+  JF_HIP(hipMemcpyAsync(ws + L.flags_off, &S.host_image[L.flags_off], GRID_WGS * GRID_FLAG_STRIDE * sizeof(unsigned),
+                        hipMemcpyHostToDevice, stream));
+  st = enqueue_program(p, ws, stream, nullptr, skip_lds, nullptr, bufs, nullptr, true, false);
+  if (st != JF_OK) return st;
+  return read_results(p, ws, stream, out, terms, pinned, &gave_up);
 }
 
 // One run of a plan.  With JF_FLAG_GRAPH the step program is captured into a hipGraph on the first
@@ -1048,7 +1299,7 @@ jf_status run_one(jf_plan* p, void* ws, size_t ws_bytes, hipStream_t stream, jf_
   }
   JF_HIP(hipEventRecord(S.ev1, s));
   jf_result r;
-  st = read_results(p, w, s, &r, terms);
+  st = finish_pass(p, w, s, &r, terms);
   if (st != JF_OK) return st;
   float ms = 0;
   JF_HIP(hipEventElapsedTime(&ms, S.ev0, S.ev1));
@@ -1078,7 +1329,7 @@ extern "C" jf_status jf_fidelity_alg1(jf_plan* p, void* ws, size_t ws_bytes, voi
 // Device scratch of jf_fidelity_noalloc: one copy per GPU, held until the process ends.  In host
 // code the name `scratch` is a host-side stand-in, never a device address: the device address
 // comes from hipGetSymbolAddress, taken once per device with that device current.
-static __device__ __align__(256) unsigned char scratch[JF_NOALLOC_BYTES];
+static __device__ __align__(256) unsigned char scratch[JF_NOALLOC_BYTES + kGridTableBytes];
 
 namespace {
 constexpr int kMaxDevices = 64;
@@ -1118,7 +1369,7 @@ extern "C" jf_status jf_fidelity_noalloc(jf_plan* p, void* stream_v, jf_result* 
     set_error("jf_fidelity_noalloc: per-term traces exist for Algorithm I plans only");
     return JF_E_ARG;
   }
-  const size_t need = state_of(p).lay.total;
+  const size_t need = state_of(p).lay.total - state_of(p).lay.grid_bytes;  // the grid runs' tables have room beside
   if (need > JF_NOALLOC_BYTES) {
     set_error("jf_fidelity_noalloc: the plan needs a workspace of " + std::to_string(need) +
               " bytes; the no-allocation scratch holds " + std::to_string((size_t)JF_NOALLOC_BYTES));
@@ -1128,7 +1379,7 @@ extern "C" jf_status jf_fidelity_noalloc(jf_plan* p, void* stream_v, jf_result* 
   jf_status st = scratch_of_current_device(&ws);
   if (st != JF_OK) return st;
   hipStream_t stream = static_cast<hipStream_t>(stream_v);
-  st = check_ws(p, ws, JF_NOALLOC_BYTES);
+  st = check_ws(p, ws, JF_NOALLOC_BYTES + kGridTableBytes);
   if (st != JF_OK) return st;
   const auto t0 = std::chrono::steady_clock::now();
   st = upload(p, ws, stream);  // a copy of the plan's tables (every plan shares the scratch)
@@ -1136,7 +1387,7 @@ extern "C" jf_status jf_fidelity_noalloc(jf_plan* p, void* stream_v, jf_result* 
   st = enqueue_program(p, static_cast<unsigned char*>(ws), stream);  // eager: no graph, no events
   if (st != JF_OK) return st;
   jf_result r;
-  st = read_results(p, static_cast<unsigned char*>(ws), stream, &r, terms, false);
+  st = finish_pass(p, static_cast<unsigned char*>(ws), stream, &r, terms, false);
   if (st != JF_OK) return st;
   r.seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
   *out = r;
@@ -1250,6 +1501,17 @@ extern "C" jf_status jf_autotune(jf_plan* p, void* ws, size_t ws_bytes, void* st
   return JF_OK;
 }
 
+extern "C" jf_status jf_set_grid_wait(jf_plan* p, long long ticks) {
+  if (!p || ticks < 0) {
+    set_error("jf_set_grid_wait: bad argument");
+    return JF_E_ARG;
+  }
+  DevState& S = state_of(p);
+  S.grid_wait = ticks;
+  S.variant_gen = g_variant_gen.fetch_add(1);  // captured launches hold the old limit
+  return JF_OK;
+}
+
 extern "C" jf_status jf_set_kernel_variant(jf_plan* p, int variant) {
   if (!p || variant < KV_AUTO || variant >= KV_COUNT) {
     set_error("jf_set_kernel_variant: bad argument");
@@ -1265,6 +1527,7 @@ extern "C" jf_status jf_set_kernel_variant(jf_plan* p, int variant) {
   // chains repeat; AUTO brings the chains back
   const bool keep = variant == KV_AUTO || variant == KV_GAUSS_256 || variant == KV_GAUSS_512;
   for (auto& v : S.chain_off) std::fill(v.begin(), v.end(), char(!keep));
+  for (auto& v : S.run_off) std::fill(v.begin(), v.end(), char(variant != KV_AUTO));
   S.variant_gen = g_variant_gen.fetch_add(1);
   return JF_OK;
 }
@@ -1321,7 +1584,7 @@ extern "C" jf_status jf_decide_equivalence(jf_plan* p, double eps, void* ws, siz
     st = enqueue_program(p, w, stream);
     if (st != JF_OK) return st;
     jf_result r;
-    st = read_results(p, w, stream, &r, nullptr);
+    st = finish_pass(p, w, stream, &r, nullptr);
     if (st != JF_OK) return st;
     d.fj_lower = d.fj_upper = r.fj;
     d.leaves_run = d.leaves_total;
@@ -1334,7 +1597,7 @@ extern "C" jf_status jf_decide_equivalence(jf_plan* p, double eps, void* ws, siz
     for (size_t c = 0; c < P.comps.size(); ++c) {
       const ComponentProgram& cp = P.comps[c];
       if (cp.lds_resident || int(c) == last) continue;
-      st = enqueue_component(p, w, w + L.buf_off, stream, c, nullptr, nullptr);
+      st = enqueue_component(p, w, w + L.buf_off, stream, c, nullptr, nullptr, nullptr);
       if (st != JF_OK) return st;
       JF_HIP(launch_sumsq(w + L.out_off + size_t(cp.out_off) * 16, cp.out_len,
                           reinterpret_cast<double*>(w + L.sums_off) + 4 * c,
@@ -1385,7 +1648,7 @@ extern "C" jf_status jf_decide_equivalence(jf_plan* p, double eps, void* ws, siz
       for (int lv = from; lv < nl; ++lv) {
         base[lv] = (lv ? base[lv - 1] : 0) + v[lv] * cp.levels[lv].out_stride;
         st = enqueue_level(p, w, w + L.buf_off, stream, size_t(last), lv, v, lv ? end[lv - 1] : nullptr, base[lv], &end[lv],
-                           nullptr, nullptr);
+                           nullptr, nullptr, nullptr);
         if (st != JF_OK) return st;
       }
       JF_HIP(launch_sumsq(out_last, cp.out_len, sums_last, reinterpret_cast<double*>(w + L.sumsq_off), stream));
@@ -1622,7 +1885,7 @@ extern "C" jf_status jf_fidelity_batch(jf_plan* const* plans, int n, void* ws, s
   }
   JF_HIP(hipEventRecord(e1, stream));
   for (int i = 0; i < n; ++i) {
-    st = read_results(plans[i], base[i], stream, &out[i], nullptr);
+    st = finish_pass(plans[i], base[i], stream, &out[i], nullptr, true, bufs, true);
     if (st != JF_OK) return st;
   }
   float ms = 0;

@@ -154,6 +154,25 @@ struct ChainTables {
   std::vector<std::vector<unsigned short>> fDig;   // per step: 3 x 16 entries
 };
 
+// A grid run: consecutive small steps of one level [first, last) that one launch executes (k_grid,
+// kernels.hip): the tensors pass from step to step through the level buffers, or through LDS where
+// both tensors of a step hold at most 2^GRID_LOCAL elements.
+constexpr int GRID_MAX_STEPS = 48;   // steps per launch (their operators are kernel arguments)
+constexpr int GRID_LOCAL = 10;       // log2 elements a workgroup keeps in LDS (FP64)
+constexpr int GRID_MAX_KN = 10;      // kS + kN: operators of at most 2^10 entries
+constexpr int GRID_TILE = 11;        // log2 elements (K x rows) of a workgroup's staged tile
+constexpr int GRID_DIGITS = 5;       // 4-bit digits of a row index
+struct GridRun {
+  int first = 0, last = 0;
+};
+// Addressing of a step in a grid run: row f (the untouched legs, ascending) of A lies at
+// sum_c digA[c][(f >> 4c) & 15], of C at the same sum over digC; s and n as in the step's tables.
+struct GridTables {
+  int F = 0;   // log2 rows
+  int lr = 0;  // log2 rows of a workgroup's tile
+  unsigned digA[GRID_DIGITS][16] = {}, digC[GRID_DIGITS][16] = {};
+};
+
 struct Level {
   int first = 0, last = 0;       // steps [first, last)
   int site = -1;                 // sliced Kraus site iterated at this level (-1: none)
@@ -187,8 +206,12 @@ struct ComponentProgram {
   // one level and every intermediate <= 2^LDS_RESIDENT_MAX elements: runs whole in one workgroup (LDS)
   bool lds_resident = false;
   std::vector<Chain> chains;
+  std::vector<GridRun> runs;     // by first step, ascending
 };
 
+void grid_tables(const Step& st, GridTables& out);
+// whether a step may join a grid run (sizes and operator)
+bool grid_step_ok(const Step& st);
 void chain_tables(const ComponentProgram& cp, const Chain& ch, ChainTables& out);
 // index into st.B of the variant selected by the values vv[lv] of the enclosing levels
 inline size_t variant_index(const ComponentProgram& cp, const Step& st, const std::vector<int>& vv) {

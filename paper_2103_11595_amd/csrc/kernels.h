@@ -148,6 +148,7 @@ struct AssembleArgs {
   double a, v0re, v0im;
   double* res;
   double* host;        // pinned host landing area or null
+  const unsigned* fail;  // the grid runs' failure word of the plan's workspace, or null
   unsigned* counter;   // zero before the launch, zero again after it (the last workgroup resets it)
 };
 hipError_t launch_persistent(const LdsItem* items, int n_items, const LdsStep* steps, hipStream_t stream);
@@ -160,6 +161,66 @@ int chain_threads(const ChainDesc& h);
 hipError_t launch_persistent_assemble(const LdsItem* items, int n_items, const LdsStep* steps,
                                       const AssembleArgs& as, hipStream_t stream);
 
+// Grid runs: consecutive small steps in one launch of a few workgroups (k_grid).  Step i reads the
+// tensor that step i - 1 wrote.  Tensors pass through LDS (GS_LDS: every workgroup holds the whole
+// tensor, at most 2^10 elements, in FP64) or through the two level buffers, with a grid barrier
+// between the step that writes a buffer and the one that reads it.
+constexpr int GRID_STEPS = 48;       // steps per launch
+constexpr int GRID_WGS = 64;         // workgroups of a launch
+constexpr int GRID_NT = 512;         // threads of a workgroup
+constexpr int GRID_FLAG_STRIDE = 32; // unsigned words between the workgroups' barrier flags (128 bytes)
+constexpr int GRID_OP = 1536;        // double2 entries of an operator in LDS: K rows of Nn + 8
+// What a step is, packed into one word of the launch's arguments (scalar loads): log2 sizes, storage
+// and place of its tensors (LDS tensors are FP64), the type its operator block is stored in.
+struct GridShape {
+  int kS, kN;
+  int F, lr;              // log2 rows, log2 rows of a workgroup's tile
+  int in32, out32;        // complex64 storage (level buffers only)
+  int src_lds, dst_lds;   // where the input is, where the output goes
+  int mode;               // KernelMode of the operator block
+  int final_step;         // the output goes to the component's output (double2)
+  __host__ __device__ unsigned pack() const {
+    return unsigned(kS | kN << 3 | F << 6 | lr << 11 | in32 << 15 | out32 << 16 | src_lds << 17 | dst_lds << 18 | mode << 19 |
+                    final_step << 22);
+  }
+  static __host__ __device__ GridShape unpack(unsigned w) {
+    GridShape s;
+    s.kS = w & 7;
+    s.kN = w >> 3 & 7;
+    s.F = w >> 6 & 31;
+    s.lr = w >> 11 & 15;
+    s.in32 = w >> 15 & 1;
+    s.out32 = w >> 16 & 1;
+    s.src_lds = w >> 17 & 1;
+    s.dst_lds = w >> 18 & 1;
+    s.mode = w >> 19 & 7;
+    s.final_step = w >> 22 & 1;
+    return s;
+  }
+};
+struct GridStep {
+  unsigned shape;               // GridShape, read on the host only
+  unsigned offS[DMAXK], offN[DMAXK];
+  unsigned digA[80], digC[80];  // row f: sum over 4-bit digits c of dig[16 c + digit]
+};
+struct GridArgs {
+  const GridStep* steps;
+  int n;                  // steps of this launch
+  const void* in;         // input of the first step
+  void* buf[2];           // the level's buffers; the first written is buf[0] unless it is the input
+  void* out;              // output of a final step
+  unsigned* flags;        // GRID_WGS barrier flags, GRID_FLAG_STRIDE words apart, equal before a launch
+  unsigned* fail;         // set when a wait passed its limit: the results of this pass are void
+  long long limit;        // longest wait at a barrier, in ticks of the 100 MHz wall clock
+  double* sums;           // not null (a final step): double-double sum of |out|^2 and the first entry
+  AssembleArgs as;        // res not null: then also the assembly of F_J
+  unsigned shape[GRID_STEPS];
+  const void* B[GRID_STEPS];
+};
+hipError_t launch_grid(const GridArgs& a, hipStream_t stream);
+// Whether the current device holds the workgroups of several such launches at once.
+bool grid_fits_device();
+
 // Attach a start / stop event pair to the step-kernel launches of this thread (nullptr, nullptr
 // to stop): the events then bracket the kernel execution itself.
 void set_launch_events(hipEvent_t start, hipEvent_t stop);
@@ -170,11 +231,10 @@ hipError_t launch_zero(void* out, long long n_double2, hipStream_t stream);
 // between the two events: the HBM ceiling of the step kernels' access pattern.
 hipError_t launch_stream_copy(const void* src, void* dst, size_t bytes, int bpl, hipStream_t stream, hipEvent_t ev0,
                               hipEvent_t ev1);
-// res[0..3] = F_J, 1 - F_J, |Im| (Algorithm II), 0 from the components' sums (4 doubles each:
+// res[0..3] = F_J, 1 - F_J, |Im| (Algorithm II) and, where fail is not null, *fail (grid runs), from the components' sums (4 doubles each:
 // double-double sum of |t|^2, first entry): the product over components on the device; host, if not
 // null, is pinned host memory that receives the same four values
-hipError_t launch_assemble(const double* sums, int ncomp, int alg, double a, double v0re, double v0im, double* res,
-                           double* host, hipStream_t stream);
+hipError_t launch_assemble(const AssembleArgs& as, hipStream_t stream);
 // out[i] += part[i] for i < n (double2 entries): a leaf's partial result of sliced wires
 hipError_t launch_accumulate(void* out, const void* part, long long n_double2, hipStream_t stream);
 

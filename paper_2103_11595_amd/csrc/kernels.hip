@@ -17,6 +17,7 @@
 //                        / split-form steps applied to one LDS tile per HBM pass
 //   k_persistent         whole small components in one workgroup's LDS (and, for a plan made
 //                        of them only, the assembly of F_J by the last workgroup)
+//   k_grid               runs of small steps in one launch, a grid barrier between them
 //   k_sumsq_part/_final  the FP64 double-double sum of |t|^2 (two fixed-tree passes); k_sumsq_one
 //                        the same for a small output in one launch
 //   k_assemble           F_J and 1 - F_J from the components' sums (device and pinned host)
@@ -1242,8 +1243,7 @@ __device__ __forceinline__ double2 load_op(const void* B, int mode, int idx, int
 
 constexpr int PERSIST_NT = 1024;  // 16 waves: the FP64 products of one component hide each other's latency
 
-__device__ void assemble_result(const double* sums, int ncomp, int alg, double a, double v0re, double v0im,
-                                double* res, double* host);
+__device__ void assemble_result(const AssembleArgs& as);
 
 __global__ __launch_bounds__(PERSIST_NT) void k_persistent(const LdsItem* __restrict__ items, int n_items,
                                                            const LdsStep* __restrict__ steps, AssembleArgs as) {
@@ -1348,9 +1348,427 @@ __global__ __launch_bounds__(PERSIST_NT) void k_persistent(const LdsItem* __rest
     // release this workgroup's sums, count it; the last one acquires every sum and assembles
     const unsigned done = __hip_atomic_fetch_add(as.counter, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
     if (done == gridDim.x - 1) {
-      assemble_result(as.sums, as.ncomp, as.alg, as.a, as.v0re, as.v0im, as.res, as.host);
+      assemble_result(as);
       __hip_atomic_store(as.counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // ready for the next run
     }
+  }
+}
+
+// ----------------------------------------------------------------------------- grid runs ---
+// A run of small steps in one launch.  What bounds such steps is not their data (at most 1 MB a
+// side) but the chain launch -> descriptor -> tables -> operator -> data -> products -> store drain
+// that a launch of its own costs each of them.  Here GRID_WGS workgroups stay resident: the next
+// step's descriptor and operator are fetched during the current step, a step costs one exchange of the tensor through the level buffers, and steps of at most 2^10 elements run in
+// every workgroup's LDS at once, without any exchange.
+//
+// The exchange.  Agent-scope fences (write-back and invalidate of the L2s, by every workgroup) cost
+// 3-6 us a step here, so none are used: the tensors are read and written past the L2s with
+// agent-scope buffer accesses (sc1), a workgroup's stores are complete (vmcnt) before its flag is
+// stored, and every workgroup polls all flags, 128 bytes apart.  Measured on MI355X, 64 workgroups:
+// 1.5 us for the barrier, 2.6 us with 16 KB written and 16 KB read by each; 64 workgroups take all
+// of a 1 MB tensor in tiles of 16 KB and several such launches fit the device at once.  A step costs
+// 3.6 us where its own launch cost 7.8 (the 51 steps of a 19-qubit doubled chain of 2^16 complex128
+// elements: 398 -> 212 us a pass; 11 steps up to 2^16: 112 -> 64 us).  Up to 2 MB a side the steps'
+// own launches, FP32 chains above all, are as fast (a sliced 10-qubit plan 1.37 ms with runs up to
+// 1 MB, 1.58 up to 2 MB, 1.56 without runs).
+//
+// The wait is bounded: past a.limit a workgroup sets *fail and leaves, launches that find *fail set
+// do nothing, and the assembly reports it, so that the host runs the pass again launch by launch.
+//
+// Arithmetic: FP64 matrix cores on the real embedding (as k_absorb_mfma_rd) whatever the form; the
+// operator is the FP64 value of its stored block, complex64 tensors are widened on load and rounded
+// on store.
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+constexpr int GRID_NT_LOG2 = 9, GRID_WGS_LOG2 = 6;
+static_assert(GRID_NT == 1 << GRID_NT_LOG2 && GRID_WGS == 1 << GRID_WGS_LOG2);
+constexpr int AUX_AGENT = 16;  // sc1: coherent across the agent
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t grid_rsrc(const void* p, int log2n, int c64) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (c64 ? 8 : 16) << log2n, 0x00027000);
+}
+__device__ __forceinline__ void grid_store(__amdgpu_buffer_rsrc_t r, unsigned i, int c64, double2 v) {
+  if (c64) {
+    u32x2 w;
+    w.x = __float_as_uint(float(v.x));
+    w.y = __float_as_uint(float(v.y));
+    __builtin_amdgcn_raw_buffer_store_b64(w, r, int(i * 8), 0, AUX_AGENT);
+  } else {
+    f64v2 u;
+    u.x = v.x;
+    u.y = v.y;
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, u), r, int(i * 16), 0, AUX_AGENT);
+  }
+}
+
+struct GridShared {
+  double2 x[2][1 << 10];  // the two LDS tensors; the staged tile (2^11 elements) takes both
+  double2 op[GRID_OP];    // operator, row s at s (Nn + 8): the lane groups' rows fall on different banks
+  double red[GRID_NT / 64][4][64];
+  GridStep sd[2];
+  // the launch's arguments per step: read from the argument segment one after another, as the steps
+  // need them, each new line of it would cost a step its latency
+  const void* B[GRID_STEPS];
+  unsigned shape[GRID_STEPS];
+  unsigned base;
+  int ok;
+};
+
+// Operator entries as they are stored, and their FP64 values (load_op in two halves, so that the loads
+// stay in flight under the current step).  Entry i has 1 to 4 parts of 8 bytes, part q at byte
+// entry i + part q: FP64 (Re, Im), FP32 and split pieces (Re, Im) pairs to be added up.
+struct GridOp {
+  const unsigned char* B = nullptr;
+  int parts = 0, entry = 0, part = 0, f64 = 0, bytes = 0;
+};
+__device__ __forceinline__ GridOp grid_op(const void* B, int mode, int KN) {
+  GridOp o;
+  o.B = static_cast<const unsigned char*>(B);
+  o.f64 = mode == KM_F64 || mode == KM_F32_TO_F64;
+  const bool split = mode == KM_SPLIT || mode == KM_SPLIT4;
+  o.parts = mode == KM_F32 ? 1 : mode == KM_SPLIT ? 3 : mode == KM_SPLIT4 ? 4 : 2;
+  o.entry = o.f64 || split ? 16 : 8;
+  o.part = o.f64 ? 8 : o.entry * KN;
+  o.bytes = o.f64 ? 16 * KN : o.parts * o.entry * KN;
+  return o;
+}
+__device__ __forceinline__ double2 grid_op_value(const GridOp& o, const unsigned long long (&w)[4]) {
+  if (o.f64) return make_double2(__builtin_bit_cast(double, w[0]), __builtin_bit_cast(double, w[1]));
+  double2 v = make_double2(0.0, 0.0);
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    if (q < o.parts) {
+      v.x += double(__uint_as_float(unsigned(w[q])));
+      v.y += double(__uint_as_float(unsigned(w[q] >> 32)));
+    }
+  return v;
+}
+
+// dst[e] = element at(q), e = thread + q GRID_NT < n <= 4 GRID_NT, of the tensor at src: every load is
+// issued before the first use.
+template <class AT>
+__device__ __forceinline__ void grid_fill(double2* dst, const void* src, int log2n, int c64, int n, AT at) {
+  const __amdgpu_buffer_rsrc_t r = grid_rsrc(src, log2n, c64);
+  const int tid = threadIdx.x;
+  if (c64) {
+    u32x2 v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (q * GRID_NT < n) v[q] = __builtin_amdgcn_raw_buffer_load_b64(r, int(at(q) * 8), 0, AUX_AGENT);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (tid + q * GRID_NT < n)
+        dst[tid + q * GRID_NT] = make_double2(double(__uint_as_float(v[q].x)), double(__uint_as_float(v[q].y)));
+  } else {
+    u32x4 v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (q * GRID_NT < n) v[q] = __builtin_amdgcn_raw_buffer_load_b128(r, int(at(q) * 16), 0, AUX_AGENT);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (tid + q * GRID_NT < n) {
+        const f64v2 u = __builtin_bit_cast(f64v2, v[q]);
+        dst[tid + q * GRID_NT] = make_double2(u.x, u.y);
+      }
+  }
+}
+
+// Offset of row f < 2^F.
+__device__ __forceinline__ unsigned grid_digits(const unsigned* dig, int f, int F) {
+  unsigned o = dig[f & 15];
+  if (F > 4) o += dig[16 + ((f >> 4) & 15)];
+  if (F > 8) o += dig[32 + ((f >> 8) & 15)];
+  if (F > 12) o += dig[48 + ((f >> 12) & 15)];
+  if (F > 16) o += dig[64 + ((f >> 16) & 15)];
+  return o;
+}
+
+__device__ __forceinline__ int grid_uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ const void* grid_uniform_ptr(const void* p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane(int(v)), hi = __builtin_amdgcn_readfirstlane(int(v >> 32));
+  return reinterpret_cast<const void*>(uint64_t(hi) << 32 | lo);
+}
+
+// PER k-steps of a unit: acc += the real embedding's products over s = 4 t + g, t = t0 .. t0 + PER - 1.
+// STAGED: A(s, row) at tile[(s << lr) + row]; else at x[row offset + offS[s]].  bcol: this lane's
+// operator column, rows ldb apart.
+template <int PER, bool STAGED>
+__device__ __forceinline__ void grid_ksteps(const GridShared& sh, const GridStep& sd, const double2* A, int arow, int lr,
+                                            const double2* bcol, int ldb, int K, int t0, int g, int cb, doublex4& acc) {
+  using M = Mfma<double>;
+  double2 av[PER], bv[PER];
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const int s = 4 * (t0 + j) + g, sc = s < K ? s : K - 1;  // s >= K: only where K < 4
+    av[j] = A[STAGED ? (sc << lr) + arow : arow + int(sd.offS[sc])];
+    bv[j] = bcol[sc * ldb];
+    if (PER == 1 && s >= K) av[j] = bv[j] = make_double2(0.0, 0.0);
+  }
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    acc = M::op(cb ? bv[j].y : bv[j].x, av[j].x, acc);
+    acc = M::op(cb ? bv[j].x : -bv[j].y, av[j].y, acc);
+  }
+}
+
+// Products of the step over rows [0, rows) of a tile, row r being the tensor's row f0 + r, and over
+// the outputs from 8 mb0 on, 2^lmb groups of 8; put(offset in C, value) takes the outputs.  A unit is
+// 16 rows x 8 outputs (Nn < 8: the operator rows past Nn feed outputs that are not stored); with
+// fewer units than waves the sum over s is shared out over 2 or 4 waves (adding their partial sums
+// through LDS costs about as much as 8 of a lane's products).
+template <bool STAGED, class PF>
+__device__ __forceinline__ void grid_products(GridShared& sh, const GridStep& sd, const GridShape& gs, const double2* A,
+                                              int rows, int f0, int mb0, int lmb, PF put) {
+  using M = Mfma<double>;
+  constexpr int NW = GRID_NT / 64;
+  const int lane = threadIdx.x & 63, wave = grid_uniform(threadIdx.x >> 6), g = lane >> 4, l16 = lane & 15;
+  const int K = 1 << gs.kS, Nn = 1 << gs.kN, ldb = Nn + 8;
+  const int lrb = rows <= 16 ? 0 : 31 - __builtin_clz(rows) - 4, units = 1 << (lmb + lrb);
+  int lks = 0;
+  while ((units << (lks + 1)) <= NW && K >= (32 << lks)) ++lks;
+  const int per = K <= 4 ? 1 : K >> (2 + lks);
+  const int cb = M::c_of(l16), nl = M::n_of(l16);
+  for (int u = wave; u < units << lks; u += NW) {
+    // the unit a wave multiplies, and (of a shared sum: the wave's own) the one it stores
+    const int v = u >> lks, t0 = (u & ((1 << lks) - 1)) * per, w = lks ? u : v;
+    const int r = ((v >> lmb) << 4) + l16, rc = r < rows ? r : rows - 1;
+    const int arow = STAGED ? rc : int(grid_digits(sd.digA, f0 + rc, gs.F));
+    const double2* bcol = sh.op + ((mb0 + (v & ((1 << lmb) - 1))) << 3) + nl;
+    const int n = ((mb0 + (w & ((1 << lmb) - 1))) << 3) + g, ro = ((w >> lmb) << 4) + l16;
+    const bool mine = w < units && ro < rows;
+    unsigned c0 = 0, c1 = 0;
+    if (mine) {
+      const unsigned c = grid_digits(sd.digC, f0 + ro, gs.F);
+      c0 = c + sd.offN[n & (DMAXK - 1)];
+      c1 = c + sd.offN[(n + 4) & (DMAXK - 1)];
+    }
+    doublex4 acc = {0, 0, 0, 0};
+    if (per >= 4) {
+      for (int t = 0; t < per; t += 4)
+        grid_ksteps<4, STAGED>(sh, sd, A, arow, gs.lr, bcol, ldb, K, t0 + t, g, cb, acc);
+    } else if (per == 2) {
+      grid_ksteps<2, STAGED>(sh, sd, A, arow, gs.lr, bcol, ldb, K, t0, g, cb, acc);
+    } else {
+      grid_ksteps<1, STAGED>(sh, sd, A, arow, gs.lr, bcol, ldb, K, t0, g, cb, acc);
+    }
+    if (lks) {  // units << lks <= NW: one trip, and every wave below that bound takes part
+#pragma unroll
+      for (int q = 0; q < 4; ++q) sh.red[u][q][lane] = acc[q];
+    }
+    if (lks) __syncthreads();
+    if (lks && w < units) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        acc[q] = sh.red[w << lks][q][lane] + sh.red[(w << lks) + 1][q][lane];
+        if (lks > 1) acc[q] += sh.red[(w << lks) + 2][q][lane] + sh.red[(w << lks) + 3][q][lane];
+      }
+    }
+    if (mine) {
+      if (n < Nn) put(c0, make_double2(acc[0], acc[1]));
+      if (n + 4 < Nn) put(c1, make_double2(acc[2], acc[3]));
+    }
+  }
+  if (lks) {
+    if (wave >= units << lks) __syncthreads();  // the waves without a unit
+    __syncthreads();
+  }
+}
+
+// Wait, in wave 0, until every workgroup's flag has reached `want`; past the limit *fail is set.
+__device__ __forceinline__ void grid_wait(GridShared& sh, const GridArgs& a, unsigned want) {
+  const long long t0 = wall_clock64();
+  bool done = false;
+  for (int polls = 1;; ++polls) {
+    if (!done)
+      done = int(__hip_atomic_load(a.flags + threadIdx.x * GRID_FLAG_STRIDE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) -
+                 want) >= 0;
+    if (__all(done)) return;
+    if ((polls & 31) == 0 && wall_clock64() - t0 >= a.limit) {
+      if (threadIdx.x == 0) {
+        sh.ok = 0;
+        __hip_atomic_store(a.fail, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      return;
+    }
+  }
+}
+
+__global__ __launch_bounds__(GRID_NT) void k_grid(GridArgs a) {
+  __shared__ GridShared sh;
+  const int tid = threadIdx.x;
+  constexpr int DW = sizeof(GridStep) / 4, OPT = (1 << 10) / GRID_NT;
+  static_assert(DW <= GRID_NT, "one descriptor word per thread");
+  if (tid == 0) {
+    sh.base = __hip_atomic_load(a.flags + blockIdx.x * GRID_FLAG_STRIDE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    sh.ok = __hip_atomic_load(a.fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
+  }
+  if (tid < a.n) {
+    sh.B[tid] = a.B[tid];
+    sh.shape[tid] = a.shape[tid];
+  }
+  // the first two descriptors, then step 0's operator
+  if (tid < DW) {
+    reinterpret_cast<int*>(&sh.sd[0])[tid] = reinterpret_cast<const int*>(a.steps)[tid];
+    if (a.n > 1) reinterpret_cast<int*>(&sh.sd[1])[tid] = reinterpret_cast<const int*>(a.steps + 1)[tid];
+  }
+  __syncthreads();
+  if (!sh.ok) return;
+  const unsigned base = sh.base;
+  {
+    const GridShape g0 = GridShape::unpack(grid_uniform(sh.shape[0]));
+    const int KN = 1 << (g0.kS + g0.kN);
+    for (int i = tid; i < KN; i += GRID_NT) sh.op[i + 8 * (i >> g0.kN)] = load_op(sh.B[0], g0.mode, i, KN);
+  }
+  const void* cur = a.in;  // the tensor in memory, where the current one is
+  int x = 0;               // the LDS tensor, where the current one is
+  unsigned epoch = 0;
+  bool in_mem = true;      // the current tensor is in memory
+  for (int i = 0; i < a.n; ++i) {
+    const GridStep& sd = sh.sd[i & 1];
+    const bool last = i + 1 == a.n;
+    // the next step's operator and the descriptor after that: in flight during this step
+    unsigned long long raw[OPT][4];
+    GridOp nop;
+    int word = 0, nkN = 0, nKN = 0;
+    if (!last) {
+      const GridShape ng = GridShape::unpack(grid_uniform(sh.shape[i + 1]));
+      nkN = ng.kN;
+      nKN = 1 << (ng.kS + nkN);
+      nop = grid_op(grid_uniform_ptr(sh.B[i + 1]), ng.mode, nKN);
+      const __amdgpu_buffer_rsrc_t rb =
+          __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(nop.B), 0, nop.bytes, 0x00027000);
+#pragma unroll
+      for (int w = 0; w < 4; ++w)
+        if (w < nop.parts)  // entries past the block read as zero or as another part, and are not used
+#pragma unroll
+          for (int q = 0; q < OPT; ++q)
+            raw[q][w] = __builtin_bit_cast(unsigned long long, __builtin_amdgcn_raw_buffer_load_b64(
+                                                                   rb, (tid + q * GRID_NT) * nop.entry, w * nop.part, 0));
+      if (i + 2 < a.n && tid < DW) word = reinterpret_cast<const int*>(a.steps + i + 2)[tid];
+    }
+    const GridShape gs = GridShape::unpack(grid_uniform(sh.shape[i]));
+    const int lmb = gs.kN <= 3 ? 0 : gs.kN - 3;
+    const int rA = gs.F + gs.kS;
+    if (gs.src_lds && in_mem) {  // a small tensor: every workgroup takes all of it into LDS
+      grid_fill(sh.x[0], cur, rA, gs.in32, 1 << rA, [&](int q) { return unsigned(tid + q * GRID_NT); });
+      x = 0;
+    }
+    if (gs.dst_lds) {
+      __syncthreads();  // input, operator and descriptor visible
+      double2* C = sh.x[x ^ 1];
+      grid_products<false>(sh, sd, gs, sh.x[x], 1 << gs.F, 0, 0, lmb, [&](unsigned c, double2 v) { C[c] = v; });
+      x ^= 1;
+      in_mem = false;
+    } else {
+      void* dst = gs.final_step ? a.out : (cur == a.buf[0] ? a.buf[1] : a.buf[0]);
+      const __amdgpu_buffer_rsrc_t rc = grid_rsrc(dst, gs.F + gs.kN, gs.out32);
+      // a workgroup's work: a row tile and, while there are fewer tiles than workgroups, a share of
+      // the outputs
+      const int rows = 1 << gs.lr, ltiles = gs.F - gs.lr;
+      int lcs = 0;
+      while (lcs < lmb && ltiles + lcs < GRID_WGS_LOG2) ++lcs;
+      const auto put = [&](unsigned c, double2 v) { grid_store(rc, c, gs.out32, v); };
+      double2* tile = &sh.x[0][0];  // [s][row]
+      if (gs.src_lds) __syncthreads();
+      for (int w = blockIdx.x; w < 1 << (ltiles + lcs); w += GRID_WGS) {
+        const int f0 = (w >> lcs) << gs.lr, mb0 = (w & ((1 << lcs) - 1)) << (lmb - lcs);
+        if (gs.src_lds) {
+          grid_products<false>(sh, sd, gs, sh.x[x], rows, f0, mb0, lmb - lcs, put);
+        } else {
+          // a thread's elements lie in one row (rows divides GRID_NT)
+          const unsigned ra = grid_digits(sd.digA, f0 + (tid & (rows - 1)), gs.F);
+          grid_fill(tile, cur, rA, gs.in32, rows << gs.kS, [&](int q) {
+            return ra + sd.offS[((tid >> gs.lr) + (q << (GRID_NT_LOG2 - gs.lr))) & (DMAXK - 1)];
+          });
+          __syncthreads();
+          grid_products<true>(sh, sd, gs, tile, rows, f0, mb0, lmb - lcs, put);
+          __syncthreads();
+        }
+      }
+      cur = dst;
+      in_mem = true;
+    }
+    const bool exchange = in_mem;
+    if (last && !(exchange && a.sums)) break;
+    if (exchange) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's stores are complete
+    __syncthreads();                                                // and every wave's; operator and descriptor free
+    ++epoch;
+    if (exchange && tid == 0)
+      __hip_atomic_store(a.flags + blockIdx.x * GRID_FLAG_STRIDE, base + epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (last) {  // workgroup 0 sums the output that all of them wrote
+      if (blockIdx.x != 0) return;
+    } else {
+#pragma unroll
+      for (int q = 0; q < OPT; ++q) {
+        const int e = tid + q * GRID_NT;
+        if (e < nKN) sh.op[e + 8 * (e >> nkN)] = grid_op_value(nop, raw[q]);
+      }
+      if (tid < DW) reinterpret_cast<int*>(&sh.sd[i & 1])[tid] = word;
+    }
+    if (exchange && tid < GRID_WGS) grid_wait(sh, a, base + epoch);  // wave 0: one flag per lane
+    __syncthreads();  // operator, descriptor and (exchange) every workgroup's output visible
+    if (!sh.ok) return;
+  }
+  // the end of the run
+  if (blockIdx.x != 0) return;
+  const GridShape gl = GridShape::unpack(grid_uniform(sh.shape[a.n - 1]));
+  if (!gl.final_step || (in_mem && !a.sums)) return;
+  // a small component output: to memory if it is in LDS, and the double-double sum of |out|^2 over a
+  // fixed tree
+  __syncthreads();
+  const double2* X = sh.x[x];
+  const int lout = gl.F + gl.kN;
+  const __amdgpu_buffer_rsrc_t ro = grid_rsrc(a.out, lout, 0);
+  double hi = 0.0, lo = 0.0;
+  double2 first = make_double2(0.0, 0.0);
+  for (int e0 = 0; e0 < (1 << lout); e0 += 4 * GRID_NT) {
+    double2 v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int e = e0 + tid + q * GRID_NT;
+      v[q] = make_double2(0.0, 0.0);
+      if (e >= (1 << lout)) continue;
+      if (in_mem) {
+        const f64v2 u = __builtin_bit_cast(f64v2, __builtin_amdgcn_raw_buffer_load_b128(ro, e * 16, 0, AUX_AGENT));
+        v[q] = make_double2(u.x, u.y);
+      } else {
+        v[q] = X[e];
+        static_cast<double2*>(a.out)[e] = v[q];
+      }
+    }
+    if (e0 == 0) first = v[0];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      double s, err;
+      two_sum(hi, fma(v[q].x, v[q].x, v[q].y * v[q].y), s, err);
+      hi = s;
+      lo += err;
+    }
+  }
+  if (!a.sums) return;
+  double* rh = &sh.red[0][0][0];
+  double* rl = rh + GRID_NT;
+  rh[tid] = hi;
+  rl[tid] = lo;
+  __syncthreads();
+  for (int w = GRID_NT / 2; w > 0; w >>= 1) {
+    if (tid < w) {
+      double s, err;
+      two_sum(rh[tid], rh[tid + w], s, err);
+      err += rl[tid] + rl[tid + w];
+      const double h = s + err;
+      rl[tid] = err - (h - s);
+      rh[tid] = h;
+    }
+    __syncthreads();
+  }
+  if (tid == 0) {
+    a.sums[0] = rh[0];
+    a.sums[1] = rl[0];
+    a.sums[2] = first.x;  // thread 0's first entry
+    a.sums[3] = first.y;
+    if (a.as.res) assemble_result(a.as);
   }
 }
 
@@ -1746,6 +2164,29 @@ hipError_t launch_chain(const ChainDesc* d_desc, const ChainDesc& h, const void*
   return hipGetLastError();
 }
 
+hipError_t launch_grid(const GridArgs& a, hipStream_t stream) {
+  if (a.n < 1 || a.n > GRID_STEPS || !a.steps || !a.in || !a.flags || !a.fail) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_grid, dim3(GRID_WGS), dim3(GRID_NT), 0, stream, a);
+  return hipGetLastError();
+}
+
+// The barrier of a grid run needs its workgroups resident together: the device has to hold those of
+// four launches (one per hardware queue of a process) at once.
+bool grid_fits_device() {
+  static std::mutex mu;
+  static std::map<int, bool> cache;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return false;
+  std::lock_guard<std::mutex> lk(mu);
+  auto it = cache.find(dev);
+  if (it != cache.end()) return it->second;
+  int per_cu = 0, cus = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(k_grid), GRID_NT, 0) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    return false;
+  return cache[dev] = (long long)per_cu * cus >= 4LL * GRID_WGS;
+}
+
 hipError_t launch_persistent(const LdsItem* items, int n_items, const LdsStep* steps, hipStream_t stream) {
   if (n_items <= 0) return hipSuccess;
   const int grid = n_items < 2048 ? n_items : 2048;
@@ -1806,12 +2247,12 @@ hipError_t launch_stream_copy(const void* src, void* dst, size_t bytes, int bpl,
 // squared modulus of the traced-out scalar), F_J = hi + lo and 1 - F_J = (1 - hi) - lo, where 1 - hi
 // is exact for hi in [0.5, 2] (Sterbenz).  Algorithm II: T / d^2 = v0 prod_c value_c (complex),
 // F_J = Re, 1 - F_J = 1 - Re (exact for Re in [0.5, 2]), |Im| the residual.  res[0..2].
-__device__ void assemble_result(const double* sums, int ncomp, int alg, double a, double v0re, double v0im,
-                                double* res, double* host) {
-  if (alg == 1) {
-    double hi = a, lo = 0.0;
-    for (int c = 0; c < ncomp; ++c) {
-      const double sh = sums[4 * c], sl = sums[4 * c + 1];
+__device__ void assemble_result(const AssembleArgs& as) {
+  double res[4];
+  if (as.alg == 1) {
+    double hi = as.a, lo = 0.0;
+    for (int c = 0; c < as.ncomp; ++c) {
+      const double sh = as.sums[4 * c], sl = as.sums[4 * c + 1];
       const double h = hi * sh;
       const double l = fma(hi, sh, -h) + hi * sl + lo * sh;
       hi = h + l;
@@ -1821,9 +2262,9 @@ __device__ void assemble_result(const double* sums, int ncomp, int alg, double a
     res[1] = (1.0 - hi) - lo;
     res[2] = 0.0;
   } else {
-    double vr = v0re, vi = v0im;
-    for (int c = 0; c < ncomp; ++c) {
-      const double cr = sums[4 * c + 2], ci = sums[4 * c + 3];
+    double vr = as.v0re, vi = as.v0im;
+    for (int c = 0; c < as.ncomp; ++c) {
+      const double cr = as.sums[4 * c + 2], ci = as.sums[4 * c + 3];
       const double nr = vr * cr - vi * ci;
       vi = vr * ci + vi * cr;
       vr = nr;
@@ -1832,20 +2273,22 @@ __device__ void assemble_result(const double* sums, int ncomp, int alg, double a
     res[1] = 1.0 - vr;
     res[2] = fabs(vi);
   }
-  res[3] = 0.0;
-  if (host)  // the caller's pinned host landing area: the result needs no copy back
-    for (int i = 0; i < 4; ++i) host[i] = res[i];
+  // a grid run that gave up waiting voids the pass: the host sees it here and runs the pass again
+  // without grid runs
+  res[3] = as.fail && __hip_atomic_load(as.fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? 1.0 : 0.0;
+  for (int i = 0; i < 4; ++i) {
+    as.res[i] = res[i];
+    if (as.host) as.host[i] = res[i];  // the caller's pinned host landing area: the result needs no copy back
+  }
 }
 
-__global__ void k_assemble(const double* sums, int ncomp, int alg, double a, double v0re, double v0im, double* res,
-                           double* host) {
+__global__ void k_assemble(AssembleArgs as) {
   if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  assemble_result(sums, ncomp, alg, a, v0re, v0im, res, host);
+  assemble_result(as);
 }
 
-hipError_t launch_assemble(const double* sums, int ncomp, int alg, double a, double v0re, double v0im, double* res,
-                           double* host, hipStream_t stream) {
-  hipLaunchKernelGGL(k_assemble, dim3(1), dim3(64), 0, stream, sums, ncomp, alg, a, v0re, v0im, res, host);
+hipError_t launch_assemble(const AssembleArgs& as, hipStream_t stream) {
+  hipLaunchKernelGGL(k_assemble, dim3(1), dim3(64), 0, stream, as);
   return hipGetLastError();
 }
 

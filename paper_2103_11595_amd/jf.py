@@ -111,7 +111,7 @@ EXPORTS = ["jf_load_circuit", "jf_plan_contraction", "jf_plan_info", "jf_plan_st
            "jf_fidelity_alg1", "jf_fidelity_alg2", "jf_batch_workspace", "jf_fidelity_batch",
            "jf_is_equivalent", "jf_free_circuit", "jf_free_plan", "jf_last_error", "jf_emulate_plan",
            "jf_profile_run", "jf_plan_describe", "jf_profile_steps", "jf_autotune", "jf_set_kernel_variant",
-           "jf_decide_equivalence", "jf_workspace_release", "jf_fidelity_noalloc", "jf_stream_copy"]
+           "jf_decide_equivalence", "jf_workspace_release", "jf_fidelity_noalloc", "jf_stream_copy", "jf_set_grid_wait"]
 
 _lib = None
 
@@ -151,6 +151,7 @@ def lib():
     L.jf_profile_steps.argtypes = [vp, vp, sz, vp, C.POINTER(jf_step_profile), C.c_int, C.POINTER(C.c_int)]
     L.jf_autotune.argtypes = [vp, vp, sz, vp, C.c_int]
     L.jf_set_kernel_variant.argtypes = [vp, C.c_int]
+    L.jf_set_grid_wait.argtypes = [vp, C.c_longlong]
     L.jf_decide_equivalence.argtypes = [vp, C.c_double, vp, sz, vp, C.POINTER(jf_decision)]
     L.jf_workspace_release.argtypes = [vp, sz]
     L.jf_fidelity_noalloc.argtypes = [vp, vp, C.POINTER(jf_result), C.POINTER(C.c_double)]
