@@ -510,6 +510,7 @@ def main():
     mm = PEAK["c64" if args.dtype != "c128" else "c128"]["mfma"]
     kv_names = {v: k for k, v in jf.KERNEL_VARIANTS.items()}
     kv_names[jf.KV_CHAIN] = "chain"
+    kv_names[jf.KV_BLOCK] = "block"
 
     def label(x):
         # the kernel a launch ran: its variant, and for chains the kind and workgroup size
@@ -541,6 +542,8 @@ def main():
     if dom_name.startswith("chain"):
         kind, nt = dom_name.rstrip("0123456789"), dom_name[len(dom_name.rstrip("0123456789")):] or "256"
         symbol = f"k_{kind}<{nt}>"
+    elif dom_name == "block":
+        symbol = "k_block<double>" if args.dtype == "c128" else "k_block<float>"
     else:
         symbol = dom_name
     # large contractions (complex GEMMs of K >= 16 summed and new extents, intensity >= 8 flop/B)

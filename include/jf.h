@@ -136,6 +136,8 @@ typedef struct jf_plan jf_plan;
                                   steps applied to one LDS tile per HBM pass (same results bit for
                                   bit; chains are the default), no runs of small steps in one
                                   launch (FP64 arithmetic: results of the form's accuracy) */
+#define JF_FLAG_SMALL_BLOCKS 32u /* test aid: blocks of steps on one LDS tile at any size (the default
+                                    keeps them to large tensors), and no runs of small steps */
 /* Search effort of the planner: JF_FLAG_EFFORT(e), e = 1..15, runs 2^(e+5) randomised greedy
  * restarts per component.  The default (e = 0 in the flags) sizes the search to the network:
  * min(2^17, max(2^12, 8e7 / tensors)) restarts, i.e. 2^17 up to ~600 tensors and 2^16 at ~1200,
@@ -338,9 +340,11 @@ typedef enum {
   JF_KV_FMA = 5,
   JF_KV_GAUSS_256 = 6,
   JF_KV_GAUSS_512 = 7,
-  JF_KV_CHAIN = 8   /* reported by jf_profile_steps only: a chain of in-place complex64 steps
+  JF_KV_CHAIN = 8,  /* reported by jf_profile_steps only: a chain of in-place complex64 steps
                        applied to one LDS tile per HBM pass (not a choice for
                        jf_set_kernel_variant) */
+  JF_KV_BLOCK = 9 /* reported by jf_profile_steps only: steps, size-changing ones among them, applied
+                       to one LDS tile per HBM pass */
 } jf_kernel_variant;
 
 /*

@@ -104,6 +104,37 @@ bool validate_program(const Program& P, std::string& why) {
         return false;
       }
     }
+    int block_end = 0;
+    for (const Block& b : cp.blocks) {
+      Block again;
+      bool ok = b.first >= block_end && b.last <= (int)cp.steps.size() && b.last - b.first >= 2 &&
+                b.last - b.first <= BLOCK_MAX_STEPS && block_tile(cp, b.first, b.last, again) && again.T == b.T &&
+                again.Pin == b.Pin && again.Pout == b.Pout && again.hiA == b.hiA && again.hiC == b.hiC;
+      for (int s = b.first; ok && s < b.last; ++s)
+        for (const GridRun& r : cp.runs) ok = ok && (s < r.first || s >= r.last);
+      bool one_level = false;
+      for (auto& lv : cp.levels) one_level = one_level || (b.first >= lv.first && b.last <= lv.last);
+      if (ok && one_level) {
+        BlockTables tb;
+        block_tables(cp, b, tb);
+        auto span = [](const std::vector<int>& bits) {
+          int m = 0;
+          for (int x : bits) m |= x;
+          return m;
+        };
+        ok = (span(tb.lin) | span(tb.lout)) < (1 << b.T) && tb.lin.size() == b.Pin.size() && tb.lout.size() == b.Pout.size() &&
+             b.Pin.size() + b.hiA.size() == size_t(cp.steps[b.first].rA) &&
+             b.Pout.size() + b.hiC.size() == size_t(cp.steps[b.last - 1].rC);
+        for (int p : b.hiC) ok = ok && p >= 0;
+        for (int q = 0; q < b.last - b.first; ++q)
+          ok = ok && (span(tb.f[q]) | span(tb.s[q]) | span(tb.n[q])) < (1 << b.T) && tb.f[q].size() >= 4;
+      }
+      if (!ok || !one_level) {
+        why = "block of component " + std::to_string(c) + " is malformed";
+        return false;
+      }
+      block_end = b.last;
+    }
     int run_end = 0;
     for (const GridRun& r : cp.runs) {
       bool ok = r.first >= run_end && r.last - r.first >= 2 && r.last - r.first <= GRID_MAX_STEPS &&
@@ -208,6 +239,45 @@ void emulate_step(const Step& st, const std::vector<cd>& B, const cd* A, cd* C) 
   }
 }
 
+// A block on the host with the tables of the block kernel: per tile, gather the input's elements,
+// apply every step in place on the local index, scatter the output's.
+void emulate_block(const ComponentProgram& cp, const Block& b, const std::vector<const std::vector<cd>*>& Bs,
+                   const std::vector<cd>& X, std::vector<cd>& Y) {
+  BlockTables tb;
+  block_tables(cp, b, tb);
+  auto local = [](const std::vector<int>& bits, int i) {
+    int o = 0;
+    for (size_t k = 0; k < bits.size(); ++k)
+      if ((i >> k) & 1) o ^= bits[k];
+    return o;
+  };
+  auto place = [](const std::vector<int>& pos, long long i) {
+    long long o = 0;
+    for (size_t k = 0; k < pos.size(); ++k) o |= ((i >> k) & 1LL) << pos[k];
+    return o;
+  };
+  std::vector<cd> tile(size_t(1) << b.T);
+  for (long long t = 0; t < b.nTiles; ++t) {
+    const long long bA = place(b.hiA, t), bC = place(b.hiC, t);
+    for (int l = 0; l < (1 << b.Pin.size()); ++l) tile[local(tb.lin, l)] = X[bA + place(b.Pin, l)];
+    for (int j = 0; j < b.last - b.first; ++j) {
+      const Step& st = cp.steps[b.first + j];
+      const int K = 1 << st.kS, Nn = 1 << st.kN;
+      std::vector<cd> a(K);
+      for (int f = 0; f < (1 << tb.f[j].size()); ++f) {
+        const int fl = local(tb.f[j], f);
+        for (int s = 0; s < K; ++s) a[s] = tile[fl ^ local(tb.s[j], s)];
+        for (int n = 0; n < Nn; ++n) {
+          cd acc = 0;
+          for (int s = 0; s < K; ++s) acc += a[s] * (*Bs[j])[size_t(s) * Nn + n];
+          tile[fl ^ local(tb.n[j], n)] = acc;
+        }
+      }
+    }
+    for (int l = 0; l < (1 << b.Pout.size()); ++l) Y[bC + place(b.Pout, l)] = tile[local(tb.lout, l)];
+  }
+}
+
 // The same step with the row addressing of a grid run.
 void emulate_grid_step(const Step& st, const std::vector<cd>& B, const cd* A, cd* C) {
   GridTables tb;
@@ -274,7 +344,19 @@ void emulate_level(const ComponentProgram& cp, int lv, const std::vector<cd>& pa
       bool in_run = false;
       for (const GridRun& r : cp.runs) in_run = in_run || (si >= r.first && si < r.last);
       const auto emulate = in_run ? emulate_grid_step : emulate_step;
-      if (st.chain >= 0 && cp.chains[st.chain].first == si) {
+      const Block* blk = nullptr;
+      for (const Block& b : cp.blocks)
+        if (b.first == si) blk = &b;
+      if (blk) {
+        std::vector<const std::vector<cd>*> Bs;
+        for (int q = blk->first; q < blk->last; ++q) Bs.push_back(&cp.steps[q].B[variant_index(cp, cp.steps[q], vv)]);
+        nxt.assign(size_t(1) << cp.steps[blk->last - 1].rC, 0.0);
+        emulate_block(cp, *blk, Bs, cur, nxt);
+        cur.swap(nxt);
+        si = blk->last - 1;
+        continue;
+      }
+      if (st.chain >= 0 && cp.chains[st.chain].first == si && !chain_in_block(cp, cp.chains[st.chain])) {
         const Chain& ch = cp.chains[st.chain];
         std::vector<const std::vector<cd>*> Bs;
         for (int q = ch.first; q < ch.last; ++q) Bs.push_back(&cp.steps[q].B[variant_index(cp, cp.steps[q], vv)]);

@@ -30,6 +30,7 @@ namespace jf {
 static_assert(LDS_RESIDENT_MAX == LDS_RESIDENT_LOG2, "the planner's LDS-resident components fit the persistent kernel");
 static_assert(GRID_MAX_STEPS == GRID_STEPS && GRID_DIGITS == 5 && GRID_LOCAL == 10 && GRID_TILE == 11,
               "the planner's grid runs fit k_grid");
+static_assert(BLOCK_MAX_STEPS == BLOCK_STEPS && BLOCK_STEPS <= CHAIN_STEPS, "the planner's blocks fit k_block");
 
 namespace {
 
@@ -44,12 +45,13 @@ struct DevLayout {
   size_t ctr_off = 0;    // counter of the persistent launch's fused assembly (zero in the image)
   size_t fail_off = 0;   // failure word of the grid runs (zero in the image)
   size_t flags_off = 0;  // barrier flags of the grid runs (zero in the image)
-  size_t grid_bytes = 0; // bytes of the workspace that only the grid runs use
+  size_t grid_bytes = 0; // bytes of the workspace that only the grid runs and the blocks use
   std::vector<size_t> leaf_off;                           // per component with sliced wires: its leaf buffer
   std::vector<int> lds_comps;                             // components run by the persistent kernel
   int lds_steps = 0;
   std::vector<std::vector<size_t>> step_desc;             // per component, per step: descriptor offset
   std::vector<std::vector<size_t>> chain_desc;            // per component, per chain: descriptor offset
+  std::vector<std::vector<size_t>> block_desc;            // per component, per block
   std::vector<std::vector<size_t>> run_desc;              // per component, per grid run: its steps' GridSteps
   std::vector<std::vector<std::vector<size_t>>> step_b;   // per component, step, variant: B offset
   std::vector<std::vector<size_t>> level_buf;             // per component: 2 buffers per level, offsets in
@@ -83,6 +85,7 @@ struct DevState {
   // per component, per grid run: 1 = run its steps launch by launch (the autotuner found the run
   // slower, or a kernel variant was forced)
   std::vector<std::vector<char>> run_off;
+  std::vector<std::vector<char>> block_off;  // the same for blocks
   long long grid_wait = 200000000;          // longest wait of a grid barrier: 2 s of the 100 MHz wall clock
   bool validated = false;                   // the program passed validate_program (plans are immutable)
   hipEvent_t ev_order = nullptr, ev0 = nullptr, ev1 = nullptr;
@@ -305,6 +308,67 @@ std::vector<GridStep> grid_descriptors(const ComponentProgram& cp, const GridRun
   return out;
 }
 
+// The device descriptor of a block.
+BlockDesc block_descriptor(const ComponentProgram& cp, const Block& b) {
+  BlockTables tb;
+  block_tables(cp, b, tb);
+  const int entry = cp.steps[b.first].compute == C_F64 ? 16 : 8;
+  auto local = [&](const std::vector<int>& bits, long long i) {
+    int o = 0;
+    for (size_t k = 0; k < bits.size(); ++k)
+      if ((i >> k) & 1) o ^= bits[k];
+    return (unsigned short)(o * entry);
+  };
+  auto place = [](const std::vector<int>& pos, long long i) {
+    long long o = 0;
+    for (size_t k = 0; k < pos.size(); ++k) o |= ((i >> k) & 1LL) << pos[k];
+    return o;
+  };
+  BlockDesc d;
+  std::memset(&d, 0, sizeof(d));
+  d.nTiles = b.nTiles;
+  d.nsteps = b.last - b.first;
+  d.T = b.T;
+  d.Tin = int(b.Pin.size());
+  d.Tout = int(b.Pout.size());
+  d.f64 = cp.steps[b.first].compute == C_F64;
+  for (int i = 0; i < 48; ++i) {
+    const long long l = (long long)(i & 15) << (4 * (i >> 4));  // digit i >> 4 of an element index
+    d.gIn[i] = place(b.Pin, l);
+    d.gOut[i] = place(b.Pout, l);
+    d.lIn[i] = local(tb.lin, l);
+    d.lOut[i] = local(tb.lout, l);
+  }
+  for (int k = 0; k < 16; ++k) {
+    const long long l = (long long)k * BLOCK_NT;
+    d.gInK[k] = place(b.Pin, l);
+    d.gOutK[k] = place(b.Pout, l);
+    d.lInK[k] = local(tb.lin, l);
+    d.lOutK[k] = local(tb.lout, l);
+  }
+  for (int i = 0; i < DMAXHI / 4 * 16; ++i) {
+    const long long t = (long long)(i & 15) << (4 * (i >> 4));
+    d.hbA[i] = place(b.hiA, t);
+    d.hbC[i] = place(b.hiC, t);
+  }
+  for (int j = 0; j < d.nsteps; ++j) {
+    const Step& st = cp.steps[b.first + j];
+    BlockStepDesc& s = d.st[j];
+    s.kS = st.kS;
+    s.kN = st.kN;
+    s.F = int(tb.f[j].size());
+    s.boff = d.ops;
+    d.ops += std::max(1, (1 << st.kS) >> 2) * std::max(1, (1 << st.kN) >> 4) * 64;
+    for (int i = 0; i < 64; ++i) {
+      const int g = (i >> 2) & 3, r = i & 3;
+      s.s[i] = local(tb.s[j], 4 * (i & 15) + (i >> 4));
+      s.n[i] = local(tb.n[j], (i & 48) + (d.f64 ? 4 * r + g : 4 * g + r));
+    }
+    for (int i = 0; i < 48; ++i) s.f[i] = local(tb.f[j], (long long)(i & 15) << (4 * (i >> 4)));
+  }
+  return d;
+}
+
 void build_layout(const Program& P, DevState& S) {
   DevLayout& L = S.lay;
   size_t off = 0;
@@ -353,9 +417,12 @@ void build_layout(const Program& P, DevState& S) {
   L.ctr_off = off;
   L.fail_off = off + 128;
   off += 256;
-  // grid runs: descriptors and barrier flags, at most kGridTableBytes (else the plan runs without)
+  // grid runs: descriptors and barrier flags; blocks: descriptors.  At most kGridTableBytes (else the
+  // plan runs without)
   L.run_desc.resize(P.comps.size());
   S.run_off.resize(P.comps.size());
+  L.block_desc.resize(P.comps.size());
+  S.block_off.resize(P.comps.size());
   size_t table = GRID_WGS * GRID_FLAG_STRIDE * sizeof(unsigned);
   bool any_run = false;
   for (auto& cp : P.comps)
@@ -364,6 +431,11 @@ void build_layout(const Program& P, DevState& S) {
         table += align256(size_t(r.last - r.first) * sizeof(GridStep));
         any_run = true;
       }
+  for (auto& cp : P.comps)
+    if (!cp.lds_resident) {
+      table += cp.blocks.size() * align256(sizeof(BlockDesc));
+      any_run = any_run || !cp.blocks.empty();
+    }
   if (any_run && table <= kGridTableBytes) {
     L.grid_bytes = table;
     L.flags_off = off;
@@ -374,6 +446,11 @@ void build_layout(const Program& P, DevState& S) {
       for (const GridRun& r : P.comps[c].runs) {
         L.run_desc[c].push_back(off);
         off += align256(size_t(r.last - r.first) * sizeof(GridStep));
+      }
+      S.block_off[c].assign(P.comps[c].blocks.size(), 0);
+      for (size_t q = 0; q < P.comps[c].blocks.size(); ++q) {
+        L.block_desc[c].push_back(off);
+        off += align256(sizeof(BlockDesc));
       }
     }
   }
@@ -518,6 +595,11 @@ void build_layout(const Program& P, DevState& S) {
     for (size_t q = 0; q < L.run_desc[c].size(); ++q) {
       const std::vector<GridStep> d = grid_descriptors(P.comps[c], P.comps[c].runs[q]);
       std::memcpy(&S.host_image[L.run_desc[c][q]], d.data(), d.size() * sizeof(GridStep));
+    }
+  for (size_t c = 0; c < P.comps.size(); ++c)
+    for (size_t q = 0; q < L.block_desc[c].size(); ++q) {
+      const BlockDesc d = block_descriptor(P.comps[c], P.comps[c].blocks[q]);
+      std::memcpy(&S.host_image[L.block_desc[c][q]], &d, sizeof(d));
     }
   double one = 1.0, zero = 0.0;
   float onef = 1.0f, zerof = 0.0f;
@@ -704,6 +786,18 @@ int run_starting_at(const ComponentProgram& cp, int si) {
   return -1;
 }
 
+// The block that runs from step si on, or -1; and whether such a block takes any step of a chain.
+int block_starting_at(const ComponentProgram& cp, const DevState& S, const DevLayout& L, size_t c, int si) {
+  for (size_t q = 0; q < L.block_desc[c].size(); ++q)
+    if (cp.blocks[q].first == si && !S.block_off[c][q]) return int(q);
+  return -1;
+}
+bool chain_taken(const ComponentProgram& cp, const DevState& S, const DevLayout& L, size_t c, const Chain& ch) {
+  for (size_t q = 0; q < L.block_desc[c].size(); ++q)
+    if (!S.block_off[c][q] && cp.blocks[q].first < ch.last && ch.first < cp.blocks[q].last) return true;
+  return false;
+}
+
 // The buffer that holds a grid run's output: the steps that write memory alternate between the
 // level's buffers as k_grid does.
 const void* grid_output(const GridArgs& a) {
@@ -718,17 +812,17 @@ jf_status enqueue_steps(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipS
                         int from, int to, const std::vector<int>& vv, const void* cur, long long base, const void** end,
                         Prof* prof, Tune* tune, GridUse* gu);
 
-// Process-wide cache of grid-run decisions (1 = launch by launch), keyed by the steps' shapes.
+// Process-wide cache of the decisions on grid runs and blocks (1 = launch by launch), keyed by the
+// steps' shapes.
 std::map<std::vector<long long>, int> g_run_cache;
 
-// Time a grid run against its steps' own launches (tuned, chains included) and keep the faster.
-jf_status tune_run(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipStream_t stream, size_t c, int lv, int q,
-                   const std::vector<int>& vv, const void* in, long long base, int reps) {
-  DevState& S = state_of(p);
+// Time steps [first, last) as one launch (a grid run or a block, switched off by `off`) against their
+// own launches (tuned, chains included) and keep the faster.
+jf_status tune_joint(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipStream_t stream, size_t c, int lv, int first,
+                     int last, char& off, bool block, const std::vector<int>& vv, const void* in, long long base, int reps) {
   const ComponentProgram& cp = p->prog.comps[c];
-  const GridRun& run = cp.runs[q];
-  std::vector<long long> key;
-  for (int s = run.first; s < run.last; ++s) {
+  std::vector<long long> key = {block ? 1LL : 0LL};
+  for (int s = first; s < last; ++s) {
     const Step& st = cp.steps[s];
     for (long long v : {(long long)st.kS, (long long)st.kN, (long long)st.rA, (long long)st.rC, (long long)mode_of(st),
                         (long long)st.chain >= 0 ? 1LL : 0LL, (long long)st.final_step})
@@ -738,7 +832,7 @@ jf_status tune_run(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipStream
     std::lock_guard<std::mutex> g(g_tune_mu);
     auto it = g_run_cache.find(key);
     if (it != g_run_cache.end()) {
-      S.run_off[c][q] = char(it->second);
+      off = char(it->second);
       return JF_OK;
     }
   }
@@ -747,22 +841,22 @@ jf_status tune_run(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipStream
   JF_HIP(hipEventCreate(&ev.b));
   float ms[2] = {0, 0};
   for (int mode = 0; mode < 2; ++mode) {
-    S.run_off[c][q] = char(mode);
+    off = char(mode);
     const void* end = nullptr;
     GridUse gu;
     for (int r = 0; r <= reps; ++r) {  // the first is the warm-up
       if (r == 1) JF_HIP(hipEventRecord(ev.a, stream));
-      const jf_status st = enqueue_steps(p, ws, bufs, stream, c, lv, run.first, run.last, vv, in, base, &end, nullptr,
-                                         nullptr, &gu);
+      const jf_status st = enqueue_steps(p, ws, bufs, stream, c, lv, first, last, vv, in, base, &end, nullptr, nullptr,
+                                         block ? nullptr : &gu);
       if (st != JF_OK) return st;
     }
     JF_HIP(hipEventRecord(ev.b, stream));
     JF_HIP(hipEventSynchronize(ev.b));
     JF_HIP(hipEventElapsedTime(&ms[mode], ev.a, ev.b));
   }
-  S.run_off[c][q] = ms[0] <= ms[1] ? 0 : 1;
+  off = ms[0] <= ms[1] ? 0 : 1;
   std::lock_guard<std::mutex> g(g_tune_mu);
-  g_run_cache[key] = S.run_off[c][q];
+  g_run_cache[key] = off;
   return JF_OK;
 }
 
@@ -821,7 +915,51 @@ jf_status enqueue_steps(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipS
         continue;
       }
     }
-    if (st.chain >= 0 && cp.chains[st.chain].first == si && (tune || !S.chain_off[c][st.chain])) {
+    const int bq = tune ? -1 : block_starting_at(cp, S, L, c, si);
+    if (bq >= 0) {
+      // a block: steps [first, last) in one launch, from one level buffer to the other
+      const Block& blk = cp.blocks[bq];
+      void* dst = cur == b0 ? b1 : b0;
+      ChainOps ops = {};
+      for (int q = blk.first; q < blk.last; ++q)
+        ops.B[q - blk.first] = ws + L.step_b[c][q][variant_index(cp, cp.steps[q], vv)];
+      const BlockDesc* dd = reinterpret_cast<const BlockDesc*>(ws + L.block_desc[c][bq]);
+      const BlockDesc& hd = *reinterpret_cast<const BlockDesc*>(&S.host_image[L.block_desc[c][bq]]);
+      if (prof) {
+        hipEvent_t a = nullptr, b = nullptr;
+        JF_HIP(hipEventCreate(&a));
+        prof->ev.push_back(a);
+        JF_HIP(hipEventCreate(&b));
+        prof->ev.push_back(b);
+        set_launch_events(a, b);
+        const hipError_t le = launch_block(dd, hd, cur, dst, ops, stream);
+        set_launch_events(nullptr, nullptr);
+        JF_HIP(le);
+        prof->bytes += blk.bytes;
+        prof->flops += blk.flops;
+        jf_step_profile r = {};
+        r.flops = blk.flops;
+        r.bytes = blk.bytes;
+        for (int j = 0; j < hd.nsteps; ++j) {
+          r.kS = std::max(r.kS, hd.st[j].kS);
+          r.kN = std::max(r.kN, hd.st[j].kN);
+        }
+        r.L = hd.T;
+        r.mode = hd.f64 ? KM_F64 : KM_F32;
+        r.variant = KV_BLOCK;
+        r.component = int(c);
+        r.steps = hd.nsteps;
+        r.threads = BLOCK_NT;
+        prof->rec.push_back(r);
+      } else {
+        JF_HIP(launch_block(dd, hd, cur, dst, ops, stream));
+      }
+      cur = dst;
+      si = blk.last - 1;
+      continue;
+    }
+    if (st.chain >= 0 && cp.chains[st.chain].first == si && (tune || !S.chain_off[c][st.chain]) &&
+        (tune || !chain_taken(cp, S, L, c, cp.chains[st.chain]))) {
       // a chain: steps [first, last) in one launch, in place when the input is this level's
       const Chain& ch = cp.chains[st.chain];
       void* dst = (cur == b0 || cur == b1) ? const_cast<void*>(cur) : b0;
@@ -933,7 +1071,7 @@ jf_status enqueue_steps(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipS
 }
 
 // Enqueue the steps of level lv from `parent` (nullptr: the constant 1 of the first step's precision).
-// On the first visit of a tuning pass the level's grid runs are timed too, after their steps.
+// On the first visit of a tuning pass the level's grid runs and blocks are timed too, after their steps.
 jf_status enqueue_level(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipStream_t stream, size_t c, int lv,
                         const std::vector<int>& vv, const void* parent, long long base, const void** end, Prof* prof,
                         Tune* tune, GridUse* gu) {
@@ -949,18 +1087,20 @@ jf_status enqueue_level(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipS
   const void* start = cur;
   jf_status st = enqueue_steps(p, ws, bufs, stream, c, lv, lev.first, lev.last, vv, cur, base, end, prof, tune,
                                prof || tune ? nullptr : gu);
-  if (st != JF_OK || !tune || !gu) return st;
-  for (size_t q = 0; q < L.run_desc[c].size(); ++q) {
-    const GridRun& run = cp.runs[q];
-    if (run.first < lev.first || run.last > lev.last || tune->done[c][run.first] == 2) continue;
-    // the run's input: the level's, or what an earlier step of the level left in a level buffer (the
-    // data is garbage by now, which the timing does not see)
-    const void* in = run.first == lev.first ? start : bufs + L.level_buf[c][2 * lv + 1];
-    st = tune_run(p, ws, bufs, stream, c, lv, int(q), vv, in, base, tune->reps);
-    if (st != JF_OK) return st;
-    tune->done[c][run.first] = 2;
-  }
-  return JF_OK;
+  if (st != JF_OK || !tune) return st;
+  auto joint = [&](int first, int last, char& off, bool block) {
+    if (first < lev.first || last > lev.last || tune->done[c][first] == 2) return JF_OK;
+    // the input: the level's, or what an earlier step of the level left in a level buffer (the data
+    // is garbage by now, which the timing does not see)
+    const void* in = first == lev.first ? start : bufs + L.level_buf[c][2 * lv + 1];
+    tune->done[c][first] = 2;
+    return tune_joint(p, ws, bufs, stream, c, lv, first, last, off, block, vv, in, base, tune->reps);
+  };
+  for (size_t q = 0; q < L.run_desc[c].size() && gu && st == JF_OK; ++q)
+    st = joint(cp.runs[q].first, cp.runs[q].last, S.run_off[c][q], false);
+  for (size_t q = 0; q < L.block_desc[c].size() && st == JF_OK; ++q)
+    st = joint(cp.blocks[q].first, cp.blocks[q].last, S.block_off[c][q], true);
+  return st;
 }
 
 // Clear component c's output and walk its levels depth first: every prefix is computed once and
@@ -1527,7 +1667,8 @@ extern "C" jf_status jf_set_kernel_variant(jf_plan* p, int variant) {
   // chains repeat; AUTO brings the chains back
   const bool keep = variant == KV_AUTO || variant == KV_GAUSS_256 || variant == KV_GAUSS_512;
   for (auto& v : S.chain_off) std::fill(v.begin(), v.end(), char(!keep));
-  for (auto& v : S.run_off) std::fill(v.begin(), v.end(), char(variant != KV_AUTO));
+  for (auto* off : {&S.run_off, &S.block_off})
+    for (auto& v : *off) std::fill(v.begin(), v.end(), char(variant != KV_AUTO));
   S.variant_gen = g_variant_gen.fetch_add(1);
   return JF_OK;
 }

@@ -173,6 +173,32 @@ struct GridTables {
   unsigned digA[GRID_DIGITS][16] = {}, digC[GRID_DIGITS][16] = {};
 };
 
+// A block: consecutive steps of one level [first, last), size-changing ones among them, applied to one
+// LDS tile per HBM pass (k_block).  The tile holds every leg that the steps contract and that is
+// there at the block's input, plus the lowest other legs; a leg has one bit of the tile's local
+// index while it lives, and a step's new legs take the bits of the legs it contracts and then free
+// ones, so every step works in place on the tile.
+constexpr int BLOCK_MAX_STEPS = 6;
+struct Block {
+  int first = 0, last = 0;
+  int T = 0;                     // bits of the local index: 2^T elements of LDS
+  std::vector<int> Pin, Pout;    // tile positions in the input and in the output tensor, ascending
+  std::vector<int> hiA, hiC;     // the other positions, of the input (ascending) and of the output
+  long long nTiles = 1;
+  double flops = 0, bytes = 0;   // algorithmic cost of one launch (input read and output written once)
+};
+// Addressing of a block.  Element l of the tile's input lies in the tensor at the scatter of l over
+// Pin (output: Pout), in LDS at the XOR of lin (lout) over l's bits; row f, summed index s and new
+// index n of a step at the XOR of the step's f, s and n entries over their bits.  Local indices are
+// swizzled (block_swizzle), which is linear in the bits.
+struct BlockTables {
+  std::vector<int> lin, lout;                  // per bit of the input / output tile index
+  std::vector<std::vector<int>> f, s, n;       // per step, per bit
+};
+// The low four bits select 16 consecutive entries: XORing the higher nibbles into them spreads any
+// four index bits that differ modulo 4 over 16 entries, so over distinct LDS banks.
+inline int block_swizzle(int l) { return l ^ ((l >> 4) & 15) ^ ((l >> 8) & 15) ^ ((l >> 12) & 15); }
+
 struct Level {
   int first = 0, last = 0;       // steps [first, last)
   int site = -1;                 // sliced Kraus site iterated at this level (-1: none)
@@ -207,7 +233,18 @@ struct ComponentProgram {
   bool lds_resident = false;
   std::vector<Chain> chains;
   std::vector<GridRun> runs;     // by first step, ascending
+  std::vector<Block> blocks;     // by first step, ascending
 };
+
+// The tile of the block [i, j) of cp's steps; false where the steps do not form one.
+bool block_tile(const ComponentProgram& cp, int i, int j, Block& out);
+void block_tables(const ComponentProgram& cp, const Block& b, BlockTables& out);
+// whether a block takes any step of the chain (which then runs only where the block does not)
+inline bool chain_in_block(const ComponentProgram& cp, const Chain& ch) {
+  for (const Block& b : cp.blocks)
+    if (b.first < ch.last && ch.first < b.last) return true;
+  return false;
+}
 
 void grid_tables(const Step& st, GridTables& out);
 // whether a step may join a grid run (sizes and operator)

@@ -46,6 +46,7 @@ enum KernelVariant {
   KV_GAUSS_512 = 7,   // the same, 512 threads
   KV_COUNT = 8,
   KV_CHAIN = 8,       // (profiles only) a chain of steps in one launch, k_chain
+  KV_BLOCK = 9,       // (profiles only) a block of steps in one launch, k_block
 };
 
 // Whether a variant can run the step described by h (mode, kS, kN, L).
@@ -121,6 +122,33 @@ struct ChainOps {
 };
 // A and C may alias (in place): a tile is read whole before any of it is written.
 hipError_t launch_chain(const ChainDesc* d_desc, const ChainDesc& h_desc, const void* A, void* C, const ChainOps& ops,
+                        hipStream_t stream);
+
+// Blocks: consecutive steps, size-changing ones among them, applied to one LDS tile per HBM pass
+// (k_block).  The tile's local index has T bits; input element l of a tile lies at tile base A + the
+// sum of the gIn entries of l's digits and in LDS at the XOR of its lIn entries (digits: bits 0-3,
+// 4-7, 8 of l in gIn, bits 9 on in gInK), output elements likewise; a tile base is the OR over 4-bit
+// digits of the tile index of hbA (hbC).  The LDS entries are byte offsets.  Row f of a step lies at the XOR of the f entries of its
+// 4-bit digits, s and n at the entries of s and n.  Operators sit in LDS in matrix-core order, step j
+// from entry boff on.
+constexpr int BLOCK_STEPS = 6;
+constexpr int BLOCK_NT = 512;
+struct BlockStepDesc {
+  int kS, kN, F, boff;
+  unsigned short s[64];   // s = 4 t + g at 16 g + t: a lane group's entries are consecutive
+  unsigned short n[64];   // output n = 16 mb + (matrix-core row of lane group g, register r) at 16 mb + 4 g + r
+  unsigned short f[48];   // 4-bit digits of the row
+};
+struct BlockDesc {
+  long long nTiles;
+  int nsteps, T, Tin, Tout, ops, f64;
+  long long gIn[48], gInK[16], gOut[48], gOutK[16];
+  unsigned short lIn[48], lInK[16], lOut[48], lOutK[16];
+  long long hbA[DMAXHI / 4 * 16], hbC[DMAXHI / 4 * 16];
+  BlockStepDesc st[BLOCK_STEPS];
+};
+// A and C may not overlap.
+hipError_t launch_block(const BlockDesc* d_desc, const BlockDesc& h_desc, const void* A, void* C, const ChainOps& ops,
                         hipStream_t stream);
 
 // Persistent executor of small component programs (every intermediate <= 2^11 elements, one

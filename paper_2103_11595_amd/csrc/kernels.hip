@@ -1119,6 +1119,185 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
   chain_body<NT, true>(d, A, C, ops);
 }
 
+// ----------------------------------------------------------------------------- blocks ---
+// One step of a block on the LDS tile: the Gauss-form products of k_absorb_mfma_gauss (lane group g
+// of k-step t supplies s = 4 t + g, the MFMA rows of block mb are n = 16 mb + 0..15).  A unit is 16
+// rows; it overwrites the elements it read and bits of the local index that no leg holds, after the
+// wave has read all of them.  op: entry (t MB + mb) 64 + lane feeds lane's product.  The tables hold
+// byte offsets, so that an address is one XOR.
+template <typename T, int KQ, int MB>
+__device__ __forceinline__ void block_step(unsigned char* tile, const typename Mfma<T>::c2* __restrict__ op,
+                                           const BlockStepDesc& sd) {
+  using M = Mfma<T>;
+  using C2 = typename M::c2;
+  constexpr int NW = BLOCK_NT / 64;
+  const int lane = threadIdx.x & 63, g = lane >> 4, l16 = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int K = 1 << sd.kS, Nn = 1 << sd.kN, units = 1 << (sd.F - 4);
+  if (wave >= units) return;
+  // offsets two to a register (K < 4: the groups past K read group 0's place and multiply zero)
+  unsigned so[(KQ + 1) / 2], no[2 * MB];
+  const unsigned* sp = reinterpret_cast<const unsigned*>(&sd.s[KQ > 1 || g < K ? 16 * g : 0]);
+  const unsigned* np = reinterpret_cast<const unsigned*>(&sd.n[4 * g]);
+#pragma unroll
+  for (int t = 0; t < (KQ + 1) / 2; ++t) so[t] = sp[t];
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) {
+    no[2 * mb] = np[8 * mb];
+    no[2 * mb + 1] = np[8 * mb + 1];
+  }
+  const unsigned fl0 = sd.f[l16];
+  op += lane;
+#pragma unroll 1
+  for (int u = wave; u < units; u += NW) {
+    asm volatile("" ::: "memory");  // the operator is read unit by unit: held in registers it spills
+    const unsigned fl = fl0 ^ sd.f[16 + (u & 15)] ^ sd.f[32 + ((u >> 4) & 15)];  // F <= 12
+    C2 a[KQ];
+#pragma unroll
+    for (int t = 0; t < KQ; ++t) {
+      a[t] = *reinterpret_cast<const C2*>(tile + (fl ^ ((t & 1) ? so[t >> 1] >> 16 : so[t >> 1] & 0xffffu)));
+      if (KQ == 1 && g >= K) a[t] = C2{0, 0};
+    }
+    typename M::acc_t acc[3][MB];
+#pragma unroll
+    for (int x = 0; x < 3; ++x)
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) acc[x][mb] = typename M::acc_t{0, 0, 0, 0};
+#pragma unroll
+    for (int t = 0; t < KQ; ++t) {
+      const T ar = a[t].x, ai = a[t].y, as = ar + ai;
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) {
+        const C2 b = op[(t * MB + mb) * 64];
+        acc[0][mb] = M::op(b.x, ar, acc[0][mb]);
+        acc[1][mb] = M::op(b.y, ai, acc[1][mb]);
+        acc[2][mb] = M::op(b.x + b.y, as, acc[2][mb]);
+      }
+    }
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        C2 o;
+        o.x = acc[0][mb][r] - acc[1][mb][r];
+        o.y = acc[2][mb][r] - acc[0][mb][r] - acc[1][mb][r];
+        const unsigned w = no[2 * mb + (r >> 1)];
+        // MB > 1: Nn is 16 MB
+        if (MB > 1 || M::row_of(g, r) < Nn)
+          *reinterpret_cast<C2*>(tile + (fl ^ ((r & 1) ? w >> 16 : w & 0xffffu))) = o;
+      }
+  }
+}
+
+// A block of steps, one HBM pass.  What bounds such steps run one launch each is the traffic of the
+// tensors between them: an expanding step writes four times what it reads, and its successors read
+// that again.  One 512-thread workgroup a compute unit (the tile takes 64 KB of its LDS beside the
+// operators' 8 or 16 KB a step; two waves a SIMD leave 256 registers for the prefetched tile beside
+// the accumulators of a 64-output step) loops over tiles: the prefetched input goes into LDS, the
+// next tile's loads are issued, every step runs in place on the tile, the output elements go back to
+// HBM.  Measured on MI355X, complex64: 2^24 -> 2^26 -> 2^24 elements (16 x 64 and 64 x 16 operators)
+// 193 us, 89 TFLOP/s, where the two steps' own launches take 264 us at 4.6-5.6 TB/s; of a tile's
+// 14,500 cycles the two steps take 10,700, 6,100 of them products of the matrix cores, the rest
+// the operators' and tile's LDS reads and writes at a step's two ends, which the barriers keep
+// together, and 3,000 the accesses to memory.  Not kept: the finished tile in registers and its
+// stores, with the next loads, issued by one wave of a SIMD under the other's products (214 us), and
+// the operators held in registers over a step's units (209 to 256 registers, spills in complex128).
+template <typename T, int EPT>
+__global__ __launch_bounds__(BLOCK_NT) __attribute__((amdgpu_waves_per_eu(2))) void k_block(
+    const BlockDesc* __restrict__ d, const typename Mfma<T>::c2* __restrict__ A, typename Mfma<T>::c2* __restrict__ C,
+    ChainOps ops) {
+  using C2 = typename Mfma<T>::c2;
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ __align__(16) BlockStepDesc sd[BLOCK_STEPS];
+  __shared__ long long hb[2][NDIG * 16], gK[2][16];
+  __shared__ unsigned short lK[2][16];
+  const int tid = threadIdx.x;
+  const int nsteps = d->nsteps, Tin = d->Tin, Tout = d->Tout;
+  const long long nTiles = d->nTiles;
+  unsigned char* tile = smem;
+  C2* sOp = reinterpret_cast<C2*>(smem) + (1 << d->T);
+  for (int i = tid; i < NDIG * 16; i += BLOCK_NT) {
+    hb[0][i] = d->hbA[i];
+    hb[1][i] = d->hbC[i];
+  }
+  if (tid < 16) {
+    gK[0][tid] = d->gInK[tid];
+    gK[1][tid] = d->gOutK[tid];
+    lK[0][tid] = d->lInK[tid];
+    lK[1][tid] = d->lOutK[tid];
+  }
+  for (int i = tid; i < int(sizeof(BlockStepDesc) / 4) * nsteps; i += BLOCK_NT)
+    reinterpret_cast<int*>(sd)[i] = reinterpret_cast<const int*>(d->st)[i];
+  const int d0 = tid & 15, d1 = 16 + ((tid >> 4) & 15), d2 = 32 + (tid >> 8);
+  const long long ownA = d->gIn[d0] + d->gIn[d1] + d->gIn[d2], ownC = d->gOut[d0] + d->gOut[d1] + d->gOut[d2];
+  const int lA = d->lIn[d0] ^ d->lIn[d1] ^ d->lIn[d2], lC = d->lOut[d0] ^ d->lOut[d1] ^ d->lOut[d2];
+  for (int j = 0; j < nsteps; ++j) {
+    const int kS = d->st[j].kS, kN = d->st[j].kN, K = 1 << kS, Nn = 1 << kN;
+    const int kq = K <= 4 ? 1 : K >> 2, mbs = Nn <= 16 ? 1 : Nn >> 4;
+    const C2* B = static_cast<const C2*>(ops.B[j]);
+    C2* dst = sOp + d->st[j].boff;
+    const int per = kq * mbs * 64;
+    for (int i = tid; i < per; i += BLOCK_NT) {
+      const int lane = i & 63, mb = (i >> 6) & (mbs - 1), t = (i >> 6) / mbs;
+      const int s = 4 * t + (lane >> 4), n = 16 * mb + (lane & 15);
+      dst[i] = s < K && n < Nn ? B[s * Nn + n] : C2{0, 0};
+    }
+  }
+  __syncthreads();
+  auto base = [&](const long long* h, long long t) {
+    long long b = 0;
+    for (int c = 0; (nTiles - 1) >> (4 * c); ++c) b |= h[16 * c + ((t >> (4 * c)) & 15)];
+    return b;
+  };
+  // rounds of BLOCK_NT elements in and out (a tile smaller than that: the first threads)
+  const int nin = Tin > 9 ? 1 << (Tin - 9) : 1, nout = Tout > 9 ? 1 << (Tout - 9) : 1;
+  const bool in = tid < (1 << Tin), out = tid < (1 << Tout);
+  C2 pre[EPT];
+  auto fetch = [&](long long t) {
+    const C2* p = A + (base(hb[0], t) + ownA);
+#pragma unroll
+    for (int k = 0; k < EPT; ++k)
+      if (k < nin && in) pre[k] = ld_stream(&p[gK[0][k]]);
+  };
+  // the two waves of a SIMD come out of every barrier together: with one of them preferred, its
+  // outputs are formed under the other's products
+  if (tid < BLOCK_NT / 2) __builtin_amdgcn_s_setprio(1);
+  long long t = blockIdx.x;
+  if (t < nTiles) fetch(t);
+  for (; t < nTiles; t += gridDim.x) {
+#pragma unroll
+    for (int k = 0; k < EPT; ++k)
+      if (k < nin && in) *reinterpret_cast<C2*>(tile + (lA ^ lK[0][k])) = pre[k];
+    __syncthreads();  // the whole tile is in LDS
+    if (t + gridDim.x < nTiles) fetch(t + gridDim.x);
+    for (int j = 0; j < nsteps; ++j) {
+      const BlockStepDesc& s = sd[j];
+      const C2* op = sOp + s.boff;
+      const int kq = s.kS <= 2 ? 0 : s.kS - 2, mb = s.kN <= 4 ? 0 : s.kN - 4;
+      switch (4 * kq + mb) {
+        case 0: block_step<T, 1, 1>(tile, op, s); break;
+        case 1: block_step<T, 1, 2>(tile, op, s); break;
+        case 2: block_step<T, 1, 4>(tile, op, s); break;
+        case 4: block_step<T, 2, 1>(tile, op, s); break;
+        case 5: block_step<T, 2, 2>(tile, op, s); break;
+        case 6: block_step<T, 2, 4>(tile, op, s); break;
+        case 8: block_step<T, 4, 1>(tile, op, s); break;
+        case 9: block_step<T, 4, 2>(tile, op, s); break;
+        case 10: block_step<T, 4, 4>(tile, op, s); break;
+        case 12: block_step<T, 8, 1>(tile, op, s); break;
+        case 13: block_step<T, 8, 2>(tile, op, s); break;
+        default: block_step<T, 16, 1>(tile, op, s); break;
+      }
+      __syncthreads();  // step j complete on the whole tile
+    }
+    C2* q = C + (base(hb[1], t) + ownC);
+#pragma unroll 4
+    for (int k = 0; k < nout; ++k)
+      if (out) st_stream(&q[gK[1][k]], *reinterpret_cast<const C2*>(tile + (lC ^ lK[1][k])));
+    __syncthreads();  // the tile is free (another thread may fill the places that this one stored)
+  }
+}
+
 // ---------------------------------------------------------------------- small kernels ---
 __global__ void k_zero(double2* out, long long n) {
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x)
@@ -2162,6 +2341,31 @@ hipError_t launch_chain(const ChainDesc* d_desc, const ChainDesc& h, const void*
               (const float2*)A, (float2*)C, ops);
   }
   return hipGetLastError();
+}
+
+template <typename T, int EPT>
+static hipError_t launch_block_ept(const BlockDesc* d_desc, const BlockDesc& h, const void* A, void* C, const ChainOps& ops,
+                                   hipStream_t stream) {
+  using C2 = typename Mfma<T>::c2;
+  const size_t sm = ((size_t(1) << h.T) + size_t(h.ops)) * sizeof(C2);
+  const void* k = reinterpret_cast<const void*>(k_block<T, EPT>);
+  JF_LAUNCH((k_block<T, EPT>), dim3(resident_grid(k, BLOCK_NT, sm, h.nTiles)), dim3(BLOCK_NT), sm, stream, d_desc,
+            (const C2*)A, (C2*)C, ops);
+  return hipGetLastError();
+}
+
+hipError_t launch_block(const BlockDesc* d_desc, const BlockDesc& h, const void* A, void* C, const ChainOps& ops,
+                        hipStream_t stream) {
+  const int most = h.f64 ? 12 : 13;  // 16-bit byte offsets
+  if (h.nsteps < 1 || h.nsteps > BLOCK_STEPS || h.T < 4 || h.T > most || h.Tin > h.T || h.Tout > h.T || A == C)
+    return hipErrorInvalidValue;
+  for (int j = 0; j < h.nsteps; ++j) {
+    const BlockStepDesc& s = h.st[j];
+    if (s.kS < 1 || s.kS > 6 || s.kN < 1 || s.kN > 6 || s.kS + s.kN > 10 || s.F < 4 || s.F + s.kS > h.T || s.F + s.kN > h.T)
+      return hipErrorInvalidValue;
+  }
+  if (h.f64) return launch_block_ept<double, 8>(d_desc, h, A, C, ops, stream);
+  return launch_block_ept<float, 16>(d_desc, h, A, C, ops, stream);
 }
 
 hipError_t launch_grid(const GridArgs& a, hipStream_t stream) {

@@ -397,6 +397,204 @@ static void build_level_runs(ComponentProgram& cp, int first, int last) {
   }
 }
 
+// ------------------------------------------------------------------------------ blocks ---
+namespace {
+
+// Positions of a step's untouched legs in its input and output, ascending in the input.
+std::vector<std::pair<int, int>> step_rows(const Step& st) {
+  std::vector<std::pair<int, int>> r;
+  for (int i = 0; i < st.L; ++i)
+    r.push_back({__builtin_ctzll((unsigned long long)st.offR_A[size_t(1) << i]),
+                 __builtin_ctzll((unsigned long long)st.offR_C[size_t(1) << i])});
+  for (size_t i = 0; i < st.hiA.size(); ++i) r.push_back({st.hiA[i], st.hiC[i]});
+  return r;
+}
+std::vector<int> step_n_positions(const Step& st) {
+  std::vector<int> pos;
+  for (int i = 0; i < st.kN; ++i) pos.push_back(__builtin_ctzll((unsigned long long)st.offN_C[size_t(1) << i]));
+  return pos;
+}
+
+// A step that k_block runs: single FP32 operators on complex64 storage or FP64 throughout, a shape of
+// the Gauss-form products.
+bool block_step_ok(const Step& st) {
+  const bool f32 = st.compute == C_F32 && st.in_prec == P_C64 && st.out_prec == P_C64;
+  const bool f64 = st.compute == C_F64 && st.in_prec == P_C128 && st.out_prec == P_C128;
+  return (f32 || f64) && !st.two_term && !st.final_step && st.kS >= 1 && st.kN >= 1 && st.kS <= 6 && st.kN <= 6 && st.kS + st.kN <= 10;
+}
+
+// LDS entries of a step's operator in matrix-core order (block_step, kernels.hip).
+int block_step_ops(const Step& st) {
+  const int kq = st.kS <= 2 ? 1 : 1 << (st.kS - 2), mb = st.kN <= 4 ? 1 : 1 << (st.kN - 4);
+  return kq * mb * 64;
+}
+
+// LDS of a block: 160 KB a compute unit, less its tables and a margin.
+constexpr int kBlockLds = 150 * 1024;
+constexpr int kBlockMinLog2 = 21;
+constexpr int kBlockMaxT32 = 13, kBlockMaxT64 = 12;  // 64 KB: 16-bit byte offsets
+
+}  // namespace
+
+bool block_tile(const ComponentProgram& cp, int i, int j, Block& out) {
+  if (j - i < 2 || j - i > BLOCK_MAX_STEPS) return false;
+  const Step& s0 = cp.steps[i];
+  const bool f64 = s0.compute == C_F64;
+  const int e = f64 ? 16 : 8, low = f64 ? 3 : 4;
+  int ops = 0;
+  for (int q = i; q < j; ++q) {
+    const Step& st = cp.steps[q];
+    if (!block_step_ok(st) || (st.compute == C_F64) != f64) return false;
+    ops += block_step_ops(st);
+  }
+  // legs by name: input position p is leg p, new legs are named on from rA
+  const int rA = s0.rA;
+  std::vector<int> at(rA);  // leg at each position of the current tensor
+  for (int p = 0; p < rA; ++p) at[p] = p;
+  std::vector<char> tile(rA, 0);
+  int name = rA;
+  for (int q = i; q < j; ++q) {
+    const Step& st = cp.steps[q];
+    std::vector<int> to(st.rC, -1);
+    for (int p : step_s_positions(st))
+      if (at[p] < rA) tile[at[p]] = 1;
+    for (auto& r : step_rows(st)) to[r.second] = at[r.first];
+    for (int p : step_n_positions(st)) to[p] = name++;
+    at = to;
+  }
+  const int rC = int(at.size());
+  // whole 128-byte lines on both sides
+  for (int p = 0; p < low && p < rA; ++p) tile[p] = 1;
+  for (int p = 0; p < low && p < rC; ++p)
+    if (at[p] < rA) tile[at[p]] = 1;
+  int tin = 0;
+  for (int p = 0; p < rA; ++p) tin += tile[p];
+  int grow = 0, w = 0, least = 64;  // peak over the input's width; the fewest rows of a step
+  for (int q = i; q < j; ++q) {
+    least = std::min(least, tin + w - cp.steps[q].kS);
+    w += cp.steps[q].kN - cp.steps[q].kS;
+    grow = std::max(grow, w);
+  }
+  const int maxT = f64 ? kBlockMaxT64 : kBlockMaxT32;
+  // rows: the lowest other legs, 16 at least for every step, then up to the full tile while there
+  // are four tiles for every compute unit
+  auto fits = [&](int extra) { return ((e << (tin + grow + extra)) + ops * e <= kBlockLds) && tin + grow + extra <= maxT; };
+  int extra = std::max(0, 4 - least);
+  if (tin + extra > rA || !fits(extra)) return false;
+  while (tin + extra < rA - 10 && fits(extra + 1)) ++extra;
+  for (int p = 0; p < rA && extra > 0; ++p)
+    if (!tile[p]) {
+      tile[p] = 1;
+      --extra;
+      ++tin;
+    }
+  out = Block();
+  out.first = i;
+  out.last = j;
+  out.T = tin + grow;
+  for (int p = 0; p < rA; ++p) (tile[p] ? out.Pin : out.hiA).push_back(p);
+  std::vector<int> where(rA, -1);
+  for (int p = 0; p < rC; ++p) {
+    if (at[p] >= rA || tile[at[p]]) out.Pout.push_back(p);
+    else where[at[p]] = p;
+  }
+  for (int p : out.hiA) out.hiC.push_back(where[p]);
+  out.nTiles = 1LL << out.hiA.size();
+  out.bytes = e * (std::ldexp(1.0, rA) + std::ldexp(1.0, rC));
+  for (int q = i; q < j; ++q) out.flops += cp.steps[q].flops;
+  return int(out.hiA.size()) <= MAXHI;
+}
+
+void block_tables(const ComponentProgram& cp, const Block& b, BlockTables& out) {
+  out = BlockTables();
+  std::vector<int> loc(cp.steps[b.first].rA, -1);  // local bit of each position of the current tensor
+  std::vector<int> spare;                          // unused local bits, ascending
+  for (size_t i = 0; i < b.Pin.size(); ++i) {
+    loc[b.Pin[i]] = int(i);
+    out.lin.push_back(block_swizzle(1 << i));
+  }
+  for (int i = int(b.Pin.size()); i < b.T; ++i) spare.push_back(i);
+  for (int q = b.first; q < b.last; ++q) {
+    const Step& st = cp.steps[q];
+    std::vector<int> to(st.rC, -1), s, n, f, freed;
+    for (int p : step_s_positions(st)) {
+      freed.push_back(loc[p]);
+      s.push_back(block_swizzle(1 << loc[p]));
+    }
+    for (auto& r : step_rows(st)) {
+      to[r.second] = loc[r.first];
+      if (loc[r.first] >= 0) f.push_back(loc[r.first]);
+    }
+    for (int p : step_n_positions(st)) {
+      std::vector<int>& from = freed.empty() ? spare : freed;
+      to[p] = from.front();
+      from.erase(from.begin());
+      n.push_back(block_swizzle(1 << to[p]));
+    }
+    spare.insert(spare.end(), freed.begin(), freed.end());
+    std::sort(spare.begin(), spare.end());
+    std::sort(f.begin(), f.end());
+    for (int& x : f) x = block_swizzle(1 << x);
+    out.s.push_back(s);
+    out.n.push_back(n);
+    out.f.push_back(f);
+    loc = to;
+  }
+  for (int p : b.Pout) out.lout.push_back(block_swizzle(1 << loc[p]));
+}
+
+// Blocks of one level: the cheapest partition of its steps into launches -- single steps, the
+// chains as they stand, blocks -- by a model of the launches measured on MI355X.  Single steps as the
+// path search prices them; chains of 2^26 elements run at 112 TFLOP/s and 3.5 TB/s.  Blocks: complex64
+// ones take the sum of 4.8 TB/s for the bytes and 165 TFLOP/s for the products (2^24 -> 2^26 -> 2^24,
+// 268 MB and 17.2 GFLOP, 193 us where its two steps take 264; 671 MB and 42.9 GFLOP in three steps 387
+// us; but 2^28 -> 2^26 -> 2^24, 2.3 GB and 42.9 GFLOP, 829 us where its steps take 640), complex128
+// ones the longer of 4 TB/s and 33 TFLOP/s (2^24 -> 2^26 -> 2^24, 300 us for 499; two in-place steps of
+// 2^24, 150 for 197).  Blocks are for large tensors: min_log2 is the least size of the largest one
+// in a block (below, a launch's own time decides, and FP32 chains hold their own).
+static void build_level_blocks(ComponentProgram& cp, int first, int last, double step_flops, int min_log2) {
+  const double bw = 5.2e12, tile_bw = 4.0e12, launch = 7e-6, chain_flops = 112e12;
+  const int n = last - first;
+  std::vector<double> best(n + 1, 1e300);
+  std::vector<int> from(n + 1, 0);
+  std::vector<Block> how(n + 1);
+  best[0] = 0;
+  auto relax = [&](int i, int j, double t, const Block& b) {
+    if (best[i] + t < best[j]) {
+      best[j] = best[i] + t;
+      from[j] = i;
+      how[j] = b;
+    }
+  };
+  std::vector<char> in_run(cp.steps.size(), 0);
+  for (const GridRun& r : cp.runs)
+    for (int q = r.first; q < r.last; ++q) in_run[q] = 1;
+  for (int i = 0; i < n; ++i) {
+    const Step& st = cp.steps[first + i];
+    relax(i, i + 1, std::max(st.bytes / bw, st.flops / step_flops) + launch, Block());
+    if (st.chain >= 0 && cp.chains[st.chain].first == first + i) {
+      const Chain& ch = cp.chains[st.chain];
+      relax(i, ch.last - first, std::max(ch.bytes / tile_bw, ch.flops / chain_flops) + launch, Block());
+    }
+    int top = std::max(st.rA, st.rC);
+    for (int j = i + 1; j <= n && j - i <= BLOCK_MAX_STEPS; ++j) {
+      const Step& sj = cp.steps[first + j - 1];
+      if (in_run[first + j - 1]) break;
+      top = std::max({top, sj.rA, sj.rC});
+      Block b;
+      if (j - i < 2 || top < min_log2) continue;
+      if (!block_tile(cp, first + i, first + j, b)) continue;
+      const double t = st.compute == C_F64 ? std::max(b.bytes / tile_bw, b.flops / 33e12)
+                                           : b.bytes / 4.8e12 + b.flops / 165e12;
+      relax(i, j, t + launch, b);
+    }
+  }
+  std::vector<Block> got;
+  for (int j = n; j > 0; j = from[j])
+    if (how[j].last > 0) got.push_back(how[j]);
+  cp.blocks.insert(cp.blocks.end(), got.rbegin(), got.rend());
+}
+
 Program plan_program(const jf_circuit& c, const PlanOptions& opt) {
   auto t0 = std::chrono::steady_clock::now();
   Program P;
@@ -1277,7 +1475,9 @@ Program plan_program(const jf_circuit& c, const PlanOptions& opt) {
       Lv.last = int(cp.steps.size());
       if (!(opt.flags & JF_FLAG_NO_CHAIN)) {
         P.est_seconds += mult * build_level_chains(cp, Lv.first, Lv.last, cm);
-        build_level_runs(cp, Lv.first, Lv.last);
+        const bool all = (opt.flags & JF_FLAG_SMALL_BLOCKS) != 0;
+        if (!all) build_level_runs(cp, Lv.first, Lv.last);
+        build_level_blocks(cp, Lv.first, Lv.last, cm.flops, all ? 0 : kBlockMinLog2);
       }
       Lv.max_log2 = level_maxw[lv];
       Lv.buf_bytes = std::max<size_t>(level_bytes[lv], 256);

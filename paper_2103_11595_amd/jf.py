@@ -22,6 +22,7 @@ LIB_PATH = os.environ.get("JF_LIB") or os.path.join(HERE, "libjf.so")
 JF_C128, JF_C64, JF_C64_BF16X6 = 0, 1, 2
 DTYPES = {"c128": JF_C128, "c64": JF_C64, "bf16x6": JF_C64_BF16X6}
 JF_FLAG_NO_CANCEL, JF_FLAG_NO_FUSE, JF_FLAG_NO_BATCH, JF_FLAG_GRAPH, JF_FLAG_NO_CHAIN = 1, 2, 4, 8, 16
+JF_FLAG_SMALL_BLOCKS = 32  # test aid: blocks at any size, no grid runs
 
 
 def JF_FLAG_EFFORT(e: int) -> int:
@@ -103,6 +104,7 @@ class jf_decision(C.Structure):
 # jf_kernel_variant
 KV_AUTO, KV_STAGED_256, KV_STAGED_512, KV_DIRECT_256, KV_DIRECT_512, KV_FMA, KV_GAUSS_256, KV_GAUSS_512 = range(8)
 KV_CHAIN = 8  # profiles only: a chain of steps in one launch
+KV_BLOCK = 9  # profiles only: a block of steps (size-changing ones among them) in one launch
 KERNEL_VARIANTS = {"auto": KV_AUTO, "staged256": KV_STAGED_256, "staged512": KV_STAGED_512,
                    "direct256": KV_DIRECT_256, "direct512": KV_DIRECT_512, "fma": KV_FMA,
                    "gauss256": KV_GAUSS_256, "gauss512": KV_GAUSS_512}
