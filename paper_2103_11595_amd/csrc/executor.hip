@@ -97,6 +97,11 @@ struct DevState {
   // enqueued or captured after that writes it
   double* pinned_res = nullptr;
   double* pinned_res_dev = nullptr;  // its device address (hipHostGetDevicePointer)
+  // pinned host landing area of per-tuple traces: behind the result in its page where they fit, else
+  // its own, up to 2 kTermChunk of them in two halves (the events: a half has landed)
+  double2* pinned_terms = nullptr;
+  double2* pinned_terms_dev = nullptr;
+  hipEvent_t ev_terms[2] = {nullptr, nullptr};
 };
 
 std::atomic<unsigned> g_variant_gen{1};
@@ -1298,24 +1303,74 @@ jf_status pinned_sums(jf_plan* p, double** out) {
   return JF_OK;
 }
 
-// Coherent (fine-grained) pinned memory: the assembly kernel's four stores reach the host without
-// any cache flush, and the host reads them after the stream synchronisation.
+// Coherent (fine-grained) pinned memory and its device address: kernels' stores reach the host
+// without any cache flush, and the host reads them after a synchronisation.
+jf_status pinned_coherent(size_t bytes, void** host, void** dev) {
+  void *h = nullptr, *d = nullptr;
+  JF_HIP(hipHostMalloc(&h, bytes, hipHostMallocCoherent));
+  const hipError_t e = hipHostGetDevicePointer(&d, h, 0);
+  if (e != hipSuccess || !d) {
+    (void)hipHostFree(h);
+    set_error(std::string("hipHostGetDevicePointer: ") + hipGetErrorString(e));
+    return JF_E_HIP;
+  }
+  *host = h;
+  *dev = d;
+  return JF_OK;
+}
+
+constexpr long long kTermsWithRes = 254;   // traces that share the result's page
+constexpr long long kTermChunk = 1 << 15;  // traces per half of the landing area (512 KB)
+
+// The landing area of the result (and of few traces).
 jf_status pinned_res_of(jf_plan* p) {
   DevState& S = state_of(p);
-  if (!S.pinned_res) {
-    double* h = nullptr;
-    JF_HIP(hipHostMalloc(reinterpret_cast<void**>(&h), 4 * sizeof(double), hipHostMallocCoherent));
-    void* d = nullptr;
-    const hipError_t e = hipHostGetDevicePointer(&d, h, 0);
-    if (e != hipSuccess || !d) {
-      (void)hipHostFree(h);
-      set_error(std::string("hipHostGetDevicePointer: ") + hipGetErrorString(e));
-      return JF_E_HIP;
-    }
-    S.pinned_res = h;
-    S.pinned_res_dev = static_cast<double*>(d);
+  if (S.pinned_res) return JF_OK;
+  void *h = nullptr, *d = nullptr;
+  const jf_status st = pinned_coherent(4 * sizeof(double) + kTermsWithRes * sizeof(double2), &h, &d);
+  S.pinned_res = static_cast<double*>(h);
+  S.pinned_res_dev = static_cast<double*>(d);
+  return st;
+}
+
+
+// Arguments of the traces' kernel; false where the plan does not fit them (the host gathers then).
+bool term_args(jf_plan* p, unsigned char* ws, TermArgs& a) {
+  const Program& P = p->prog;
+  if (P.site_nk.size() > size_t(TERM_SITES) || P.comps.size() > size_t(TERM_COMPS)) return false;
+  std::memset(&a, 0, sizeof(a));
+  a.out = reinterpret_cast<const double2*>(ws + state_of(p).lay.out_off);
+  a.sites = int(P.site_nk.size());
+  a.comps = int(P.comps.size());
+  const cd s = std::exp2(P.log2_scale) * P.scalar;
+  a.re = s.real();
+  a.im = s.imag();
+  for (size_t c = 0; c < P.comps.size(); ++c) a.comp_off[c] = P.comps[c].out_off;
+  for (size_t i = 0; i < P.site_nk.size(); ++i) {
+    if (P.site_nk[i] < 1 || P.site_nk[i] > 16) return false;
+    a.nk[i] = (unsigned char)P.site_nk[i];
+    a.comp[i] = (unsigned char)(P.site_comp[i] < 0 ? 255 : P.site_comp[i]);
+    if (P.site_comp[i] < 0) continue;
+    const std::vector<int>& ob = P.comps[P.site_comp[i]].out_bit[i];
+    if (ob.size() > 4) return false;
+    for (size_t b = 0; b < 4; ++b) a.bit[i][b] = (unsigned char)(b < ob.size() ? ob[b] : 0);
   }
-  return JF_OK;
+  return true;
+}
+
+// The landing area of the traces and its events (made on first use).
+jf_status pinned_terms_of(jf_plan* p) {
+  DevState& S = state_of(p);
+  const long long n = std::min(p->prog.kraus_terms, 2 * kTermChunk);
+  if (n > kTermChunk)
+    for (hipEvent_t& e : S.ev_terms)
+      if (!e) JF_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+  if (S.pinned_terms || n <= kTermsWithRes) return JF_OK;
+  void *h = nullptr, *d = nullptr;
+  const jf_status st = pinned_coherent(size_t(n) * sizeof(double2), &h, &d);
+  S.pinned_terms = static_cast<double2*>(h);
+  S.pinned_terms_dev = static_cast<double2*>(d);
+  return st;
 }
 
 // Wait for the run and read F_J back (with terms, also the per-tuple outputs).  With pinned, the
@@ -1329,8 +1384,23 @@ jf_status read_results(jf_plan* p, unsigned char* ws, hipStream_t stream, jf_res
   double res[4];
   const bool on_host = pinned && S.pinned_res;
   if (!on_host) JF_HIP(hipMemcpyAsync(res, ws + S.lay.res_off, sizeof(res), hipMemcpyDeviceToHost, stream));
+  // the traces: put in order on the device, chunk by chunk through a pinned landing area (half of it
+  // fills while the other is copied out); without host allocations, gathered on the host
+  TermArgs ta;
+  const long long total = terms ? P.kraus_terms : 0;
+  const bool on_device = terms && on_host && term_args(p, ws, ta);
+  double2 *land = nullptr, *land_dev = nullptr;
+  if (on_device) {
+    const jf_status st = pinned_terms_of(p);
+    if (st != JF_OK) return st;
+    const bool with_res = total <= kTermsWithRes;
+    land = with_res ? reinterpret_cast<double2*>(S.pinned_res + 4) : S.pinned_terms;
+    land_dev = with_res ? reinterpret_cast<double2*>(S.pinned_res_dev + 4) : S.pinned_terms_dev;
+    JF_HIP(launch_terms(ta, 0, std::min(total, kTermChunk), land_dev, stream));
+    if (total > kTermChunk) JF_HIP(hipEventRecord(S.ev_terms[0], stream));
+  }
   std::vector<std::vector<cd>> co;
-  if (terms) {
+  if (terms && !on_device) {
     for (auto& cp : P.comps) {
       std::vector<cd> v(size_t(cp.out_len));
       JF_HIP(hipMemcpyAsync(v.data(), ws + S.lay.out_off + size_t(cp.out_off) * 16, size_t(cp.out_len) * 16,
@@ -1338,7 +1408,8 @@ jf_status read_results(jf_plan* p, unsigned char* ws, hipStream_t stream, jf_res
       co.push_back(std::move(v));
     }
   }
-  JF_HIP(hipStreamSynchronize(stream));
+  if (total > kTermChunk && on_device) JF_HIP(hipEventSynchronize(S.ev_terms[0]));
+  else JF_HIP(hipStreamSynchronize(stream));
   if (on_host) std::memcpy(res, S.pinned_res, sizeof(res));
   *gave_up = res[3] != 0.0;
   if (*gave_up) return JF_OK;
@@ -1348,7 +1419,16 @@ jf_status read_results(jf_plan* p, unsigned char* ws, hipStream_t stream, jf_res
   r.one_minus_fj = res[1];
   r.imag_residual = res[2];
   *out = r;
-  if (terms) gather_terms(P, co, terms);
+  if (terms && !on_device) gather_terms(P, co, terms);
+  for (long long at = 0, half = 0; on_device && at < total; at += kTermChunk, half ^= 1) {
+    const long long next = at + kTermChunk;
+    if (next < total) {
+      JF_HIP(launch_terms(ta, next, std::min(total - next, kTermChunk), land_dev + (half ^ 1) * kTermChunk, stream));
+      JF_HIP(hipEventRecord(S.ev_terms[half ^ 1], stream));
+    }
+    if (at) JF_HIP(hipEventSynchronize(S.ev_terms[half]));
+    std::memcpy(terms + 2 * at, land + half * kTermChunk, size_t(std::min(total - at, kTermChunk)) * sizeof(double2));
+  }
   return JF_OK;
 }
 
@@ -2049,10 +2129,11 @@ extern "C" void jf_free_plan(jf_plan* p) {
       hipStreamSynchronize(s->side_stream);
       hipStreamDestroy(s->side_stream);
     }
-    for (hipEvent_t e : {s->ev0, s->ev1, s->ev_order, s->ev_fork, s->ev_join})
+    for (hipEvent_t e : {s->ev0, s->ev1, s->ev_order, s->ev_fork, s->ev_join, s->ev_terms[0], s->ev_terms[1]})
       if (e) hipEventDestroy(e);
     if (s->pinned_sums) hipHostFree(s->pinned_sums);
     if (s->pinned_res) hipHostFree(s->pinned_res);
+    if (s->pinned_terms) hipHostFree(s->pinned_terms);
     {
       std::lock_guard<std::mutex> g(g_upload_mu);
       for (auto it = g_last_upload.begin(); it != g_last_upload.end();)

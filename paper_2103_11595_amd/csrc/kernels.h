@@ -253,6 +253,19 @@ bool grid_fits_device();
 // to stop): the events then bracket the kernel execution itself.
 void set_launch_events(hipEvent_t start, hipEvent_t stop);
 
+// Per-tuple traces of an Algorithm I run, in tuple order (the first site most significant):
+// term[i] = scale prod_c out[comp_off[c] + offset of tuple first + i in component c], a site's index j
+// setting the offset bits bit[b] of its component for the bits b of j.
+constexpr int TERM_SITES = 48, TERM_COMPS = 48;
+struct TermArgs {
+  const double2* out;
+  int sites, comps;
+  double re, im;  // scale
+  long long comp_off[TERM_COMPS];
+  unsigned char comp[TERM_SITES], nk[TERM_SITES], bit[TERM_SITES][4];  // comp 255: in no component
+};
+hipError_t launch_terms(const TermArgs& a, long long first, long long count, double2* term, hipStream_t stream);
+
 // out[i] = 0 for i < n (double2 entries)
 hipError_t launch_zero(void* out, long long n_double2, hipStream_t stream);
 // Streaming copy of bytes (a multiple of bpl = 8 or 16 bytes per lane, nontemporal, resident grid)

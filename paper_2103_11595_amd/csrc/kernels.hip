@@ -21,6 +21,7 @@
 //   k_sumsq_part/_final  the FP64 double-double sum of |t|^2 (two fixed-tree passes); k_sumsq_one
 //                        the same for a small output in one launch
 //   k_assemble           F_J and 1 - F_J from the components' sums (device and pinned host)
+//   k_terms              the per-tuple traces in tuple order, from the components' outputs
 //   k_accumulate, k_zero a wire-sliced leaf's partial traces into the output; a graph-safe fill
 //   k_stream_copy        the streaming copy that measures the HBM ceiling
 // launch_step picks the kernel of a step (its variant, or the fixed rule).
@@ -2493,6 +2494,36 @@ __global__ void k_assemble(AssembleArgs as) {
 
 hipError_t launch_assemble(const AssembleArgs& as, hipStream_t stream) {
   hipLaunchKernelGGL(k_assemble, dim3(1), dim3(64), 0, stream, as);
+  return hipGetLastError();
+}
+
+// Per-tuple traces from the components' outputs.  Bound by the link to the host (`term` is pinned host
+// memory; 16 bytes a trace; the outputs sit in the caches), so consecutive threads write consecutive
+// traces.  A call with 65536 traces took 1264 us with the outputs copied to pageable memory and the
+// traces gathered on the host, and takes 270 us; one with 16 traces 50 and 32 us.
+__global__ __launch_bounds__(256) void k_terms(TermArgs a, long long first, long long count, double2* term) {
+  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= count) return;
+  double2 t = make_double2(a.re, a.im);
+  for (int c = 0; c < a.comps; ++c) {
+    long long rest = first + i, o = a.comp_off[c];
+    for (int s = a.sites - 1; s >= 0; --s) {
+      const int nk = a.nk[s];
+      const int j = (nk & (nk - 1)) ? int(rest % nk) : int(rest & (nk - 1));
+      rest = (nk & (nk - 1)) ? rest / nk : rest >> (31 - __builtin_clz(nk));
+      if (a.comp[s] != c) continue;
+      for (int b = 0; b < 4; ++b)
+        if ((j >> b) & 1) o += 1LL << a.bit[s][b];
+    }
+    const double2 v = a.out[o];
+    t = make_double2(t.x * v.x - t.y * v.y, t.x * v.y + t.y * v.x);
+  }
+  term[i] = t;
+}
+
+hipError_t launch_terms(const TermArgs& a, long long first, long long count, double2* term, hipStream_t stream) {
+  if (count <= 0 || a.sites > TERM_SITES || a.comps > TERM_COMPS) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_terms, dim3(unsigned((count + 255) / 256)), dim3(256), 0, stream, a, first, count, term);
   return hipGetLastError();
 }
 

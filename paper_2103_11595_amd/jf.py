@@ -358,23 +358,26 @@ def _stream_ptr(stream):
 
 
 def jf_fidelity_alg1(plan: Plan, ws=None, stream=None, want_terms: bool = False) -> dict:
-    import numpy as np
-    info = plan.info()
-    with _ws(ws, lambda: info["workspace_bytes"]) as ws:
+    with _ws(ws, lambda: plan.info()["workspace_bytes"]) as ws:
         r = jf_result()
-        terms = (C.c_double * (2 * info["kraus_terms"]))() if want_terms else None
+        terms, ptr = _terms_buffer(plan) if want_terms else (None, None)
         _check(lib().jf_fidelity_alg1(plan.ptr, C.c_void_p(ws.data_ptr()), ws.numel(), _stream_ptr(stream),
-                                      C.byref(r), terms))
+                                      C.byref(r), ptr))
         d = r.as_dict()
         if want_terms:
-            a = np.frombuffer(terms, dtype=np.float64).copy()
-            d["terms"] = a[0::2] + 1j * a[1::2]
+            d["terms"] = terms
         return d
 
 
+def _terms_buffer(plan: Plan):
+    """An array for one complex trace per Kraus tuple, and its pointer: the library writes into it."""
+    import numpy as np
+    terms = np.empty(plan.info()["kraus_terms"], dtype=np.complex128)
+    return terms, terms.ctypes.data_as(C.POINTER(C.c_double))
+
+
 def jf_fidelity_alg2(plan: Plan, ws=None, stream=None) -> dict:
-    info = plan.info()
-    with _ws(ws, lambda: info["workspace_bytes"]) as ws:
+    with _ws(ws, lambda: plan.info()["workspace_bytes"]) as ws:
         r = jf_result()
         _check(lib().jf_fidelity_alg2(plan.ptr, C.c_void_p(ws.data_ptr()), ws.numel(), _stream_ptr(stream), C.byref(r)))
         return r.as_dict()
@@ -386,14 +389,12 @@ JF_NOALLOC_BYTES = 128 << 20  # the library's static per-GPU scratch (include/jf
 def jf_fidelity_noalloc(plan: Plan, stream=None, want_terms: bool = False) -> dict:
     """The no-allocation entry point: the plan runs on the library's static device scratch (no
     workspace argument; plans whose workspace exceeds JF_NOALLOC_BYTES are rejected)."""
-    import numpy as np
     r = jf_result()
-    terms = (C.c_double * (2 * plan.info()["kraus_terms"]))() if want_terms else None
-    _check(lib().jf_fidelity_noalloc(plan.ptr, _stream_ptr(stream), C.byref(r), terms))
+    terms, ptr = _terms_buffer(plan) if want_terms else (None, None)
+    _check(lib().jf_fidelity_noalloc(plan.ptr, _stream_ptr(stream), C.byref(r), ptr))
     d = r.as_dict()
     if want_terms:
-        a = np.frombuffer(terms, dtype=np.float64).copy()
-        d["terms"] = a[0::2] + 1j * a[1::2]
+        d["terms"] = terms
     return d
 
 
