@@ -233,15 +233,16 @@ jf_status jf_fidelity_alg2(jf_plan* plan, void* dev_ws, size_t ws_bytes, void* s
 
 /*
  * jf_fidelity_batch -- run n plans (Alg I or Alg II, any mix, one dtype per plan) as one
- * batched submission (the networks are independent, Section IV-A): small components execute
- * LDS-resident, one workgroup each, in a single persistent launch on a second stream (forked from
- * and joined back to the caller's stream by events) beside the larger ones' step programs, which
- * run back to back; the whole submission is captured once into a hipGraph (cached on
- * the first plan, keyed by the plans, the workspace and the stream) and replayed.  Each plan keeps
- * its tables, outputs and sums in a region of its own; since the programs run one after another,
- * their level buffers share one region sized for the largest, so the workspace is the sum of the
- * plans' small parts plus the largest buffer set.  out[i] receives plan i's result.  The workspace
- * must hold jf_batch_workspace bytes.
+ * batched submission (the networks are independent, Section IV-A).  Small components of all plans
+ * execute LDS-resident, one workgroup each, in a single persistent launch.  The larger plans' step
+ * programs run in up to four lanes beside each other: streams of the library, forked from and joined
+ * back to the caller's stream by events.  On a stream each lane is captured once into a hipGraph
+ * (cached on the first plan, keyed by the plans, the workspace and the stream) and replayed.  Each
+ * plan keeps its tables, outputs and sums in a region of its own; the programs of a lane run one
+ * after another and share one buffer region sized for the largest of them.  Plans with more than
+ * 64 MB of buffers all run in the first lane, so the workspace is the sum of the plans' small parts,
+ * the largest buffer set and at most 192 MB.  out[i] receives plan i's result.  The workspace must
+ * hold jf_batch_workspace bytes; one that holds only a single lane's runs everything in that.
  */
 jf_status jf_batch_workspace(jf_plan* const* plans, int n, size_t* workspace_bytes);
 jf_status jf_fidelity_batch(jf_plan* const* plans, int n, void* dev_ws, size_t ws_bytes,

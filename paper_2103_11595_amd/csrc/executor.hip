@@ -58,16 +58,20 @@ struct DevLayout {
                                                           // the buffer region [buf_off, total)
 };
 
+constexpr int BATCH_LANES = 4;               // hardware queues of a process
+constexpr size_t kLaneBytes = size_t(64) << 20;  // level buffers of a member that shares the device
+
 struct DevState {
   DevLayout lay;
   std::vector<unsigned char> host_image;  // descriptors + pools + constants, uploaded as one copy
   const void* uploaded_to = nullptr;
   size_t uploaded_bytes = 0;
-  hipGraphExec_t graph = nullptr;
+  hipGraphExec_t graph[BATCH_LANES] = {};       // a captured batch, one graph per lane
   const void* graph_ws = nullptr;
   hipStream_t graph_stream = nullptr;
   std::vector<unsigned long long> graph_plans;  // uids of the batch the cached graph was captured for
   std::vector<unsigned> graph_gens;         // and the kernel-choice generation of each plan
+  int graph_lanes = 0;                          // 0: none captured
   unsigned variant_gen = 0;                 // bumped whenever a step's kernel choice changes
   // single-plan runs: the step program captured once per (workspace, stream, kernel choice)
   hipGraphExec_t run_graph = nullptr;
@@ -79,6 +83,10 @@ struct DevState {
   // components' steps (fork and join by events, also inside a captured graph)
   hipStream_t side_stream = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
+  // the members of a batch run in lanes beside each other: the streams of the lanes after the first,
+  // and the events that start them (the first) and end them
+  hipStream_t lane_stream[BATCH_LANES - 1] = {};
+  hipEvent_t ev_lane[BATCH_LANES] = {};
   // per component, per chain: 1 = run its steps one launch each (the autotuner found the chain
   // slower, or a kernel variant was forced on every step)
   std::vector<std::vector<char>> chain_off;
@@ -476,8 +484,8 @@ void build_layout(const Program& P, DevState& S) {
   off += 256;
   L.sumsq_off = off;
   off += align256(2 * SUMSQ_BLOCKS * sizeof(double));
-  // the level buffers last: the members of a batch, which run one after another on one stream,
-  // share one buffer region (jf_fidelity_batch)
+  // the level buffers last: the members of a batch that run one after another share one buffer
+  // region (jf_fidelity_batch)
   L.buf_off = off;
   size_t maxbuf = 0;
   L.level_buf.resize(P.comps.size());
@@ -1918,31 +1926,64 @@ extern "C" jf_status jf_fidelity_alg2(jf_plan* p, void* ws, size_t ws_bytes, voi
 }
 
 // A batch shares one workspace: each plan keeps its tables, outputs and sums in a region of its
-// own, and since the plans run one after another on one stream, their level buffers share one
-// region sized for the largest; the persistent kernel's item and step tables follow.
+// own.  The members run in lanes beside each other, one after another within a lane: the level
+// buffers of a lane's members share one region sized for the largest; the persistent kernel's item
+// and step tables follow.  Most steps of small and medium members are bound by launches and by the
+// few workgroups they have, so lanes overlap; a member with buffers beyond kLaneBytes fills the
+// device by itself, and all of those share the first lane, so that the workspace grows by at most
+// BATCH_LANES - 1 times kLaneBytes.  Longest members first, each to the lane with the least work.
+// 40 uneven circuits of up to 11 qubits took 2645 us in one lane, 1822 as branches of one graph (its
+// nodes are submitted branch after branch), 1490 with a graph per lane and 1540 launched call by call;
+// 96 circuits of four qubits 320 us with an assembly launch each and 135 with one for all.
 namespace jf {
 namespace {
+bool has_steps(jf_plan* p) { return state_of(p).lay.lds_comps.size() < p->prog.comps.size(); }
+
 struct BatchLayout {
   std::vector<size_t> base;  // each plan's region
-  size_t bufs = 0, items = 0, steps = 0, total = 0;
+  std::vector<int> lane;     // each plan's lane
+  size_t lane_bufs[BATCH_LANES] = {};
+  size_t bufs = 0, items = 0, steps = 0, assembles = 0, total = 0;
 };
-BatchLayout batch_layout(jf_plan* const* plans, int n) {
+BatchLayout batch_layout(jf_plan* const* plans, int n, int lanes) {
   BatchLayout b;
-  size_t off = 0, maxbuf = 0, items = 0, steps = 0;
+  size_t off = 0, items = 0, steps = 0;
+  std::vector<int> order(n);
   for (int i = 0; i < n; ++i) {
     const DevLayout& L = state_of(plans[i]).lay;
     b.base.push_back(off);
     off += align256(L.buf_off);
-    maxbuf = std::max(maxbuf, L.total - L.buf_off);
     items += L.lds_comps.size();
     steps += L.lds_steps;
+    order[i] = i;
+  }
+  auto buf_bytes = [&](int i) { return state_of(plans[i]).lay.total - state_of(plans[i]).lay.buf_off; };
+  auto cost = [&](int i) { return has_steps(plans[i]) ? plans[i]->prog.est_seconds : 0.0; };
+  std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
+    const bool bx = buf_bytes(x) > kLaneBytes, by = buf_bytes(y) > kLaneBytes;
+    return bx != by ? bx : cost(x) > cost(y);
+  });
+  b.lane.assign(n, 0);
+  double load[BATCH_LANES] = {};
+  if (items) load[lanes - 1] = 3e-5;  // the persistent launch (20 to 50 us) runs ahead in the last lane
+  size_t most[BATCH_LANES] = {};
+  for (int i : order) {
+    const int l = buf_bytes(i) > kLaneBytes ? 0 : int(std::min_element(load, load + lanes) - load);
+    b.lane[i] = l;
+    load[l] += cost(i);
+    most[l] = std::max(most[l], buf_bytes(i));
   }
   b.bufs = off;
-  off += align256(maxbuf);
+  for (int l = 0; l < lanes; ++l) {
+    b.lane_bufs[l] = off;
+    off += align256(most[l]);
+  }
   b.items = off;
   off += align256(items * sizeof(LdsItem));
   b.steps = off;
   off += align256(steps * sizeof(LdsStep));
+  b.assembles = off;
+  off += align256(size_t(n) * sizeof(AssembleArgs));
   b.total = off;
   return b;
 }
@@ -1959,7 +2000,7 @@ extern "C" jf_status jf_batch_workspace(jf_plan* const* plans, int n, size_t* by
       set_error("jf_batch_workspace: NULL plan");
       return JF_E_ARG;
     }
-  *bytes = batch_layout(plans, n).total;
+  *bytes = batch_layout(plans, n, BATCH_LANES).total;
   return JF_OK;
 }
 
@@ -1987,19 +2028,19 @@ extern "C" jf_status jf_fidelity_batch(jf_plan* const* plans, int n, void* ws, s
     set_error("jf_fidelity_batch: bad output or workspace");
     return JF_E_ARG;
   }
-  if (ws_bytes < need) {
+  hipStream_t stream = static_cast<hipStream_t>(stream_v);
+  const int lanes = ws_bytes >= need ? BATCH_LANES : 1;
+  const BatchLayout bl = batch_layout(plans, n, lanes);
+  if (ws_bytes < bl.total) {
     set_error("jf_fidelity_batch: workspace too small");
     return JF_E_OOM;
   }
-  hipStream_t stream = static_cast<hipStream_t>(stream_v);
-  const BatchLayout bl = batch_layout(plans, n);
   unsigned char* w = static_cast<unsigned char*>(ws);
-  unsigned char* bufs = w + bl.bufs;
   {
     // the shared buffers and the persistent tables are written by this call: no plan's tables
     // uploaded there before survive it
     std::lock_guard<std::mutex> g(g_upload_mu);
-    const auto a = reinterpret_cast<uintptr_t>(bufs);
+    const auto a = reinterpret_cast<uintptr_t>(w + bl.bufs);
     forget_uploads(a, a + (bl.total - bl.bufs));
   }
   std::vector<unsigned char*> base(n);
@@ -2012,22 +2053,22 @@ extern "C" jf_status jf_fidelity_batch(jf_plan* const* plans, int n, void* ws, s
     st = pinned_res_of(plans[i]);  // before the capture: each member's assembly writes its result there
     if (st != JF_OK) return st;
   }
-  // every small component of every plan in one persistent launch
-  std::vector<LdsItem> items;
-  std::vector<LdsStep> lsteps;
+  // every small component of every plan in one persistent launch, and one launch for the assembly
+  // of all plans that have some
+  std::vector<unsigned char> tables(bl.total - bl.items);
+  LdsItem* items = reinterpret_cast<LdsItem*>(tables.data());
+  LdsStep* lsteps = reinterpret_cast<LdsStep*>(tables.data() + (bl.steps - bl.items));
+  AssembleArgs* assembles = reinterpret_cast<AssembleArgs*>(tables.data() + (bl.assembles - bl.items));
+  int n_items = 0, n_lsteps = 0, n_assembles = 0;
   for (int i = 0; i < n; ++i) {
     const DevLayout& L = state_of(plans[i]).lay;
-    std::vector<LdsItem> it(L.lds_comps.size());
-    std::vector<LdsStep> ss(L.lds_steps);
-    fill_lds_tables(plans[i]->prog, L, base[i], it.data(), ss.data(), int(lsteps.size()));
-    items.insert(items.end(), it.begin(), it.end());
-    lsteps.insert(lsteps.end(), ss.begin(), ss.end());
+    fill_lds_tables(plans[i]->prog, L, base[i], items + n_items, lsteps + n_lsteps, n_lsteps);
+    n_items += int(L.lds_comps.size());
+    n_lsteps += L.lds_steps;
+    if (!has_steps(plans[i]) || !L.lds_comps.empty()) assembles[n_assembles++] = assemble_args(plans[i], base[i]);
   }
-  unsigned char* items_dev = w + bl.items;
-  unsigned char* steps_dev = w + bl.steps;
-  if (!items.empty()) {
-    JF_HIP(hipMemcpyAsync(items_dev, items.data(), items.size() * sizeof(LdsItem), hipMemcpyHostToDevice, stream));
-    JF_HIP(hipMemcpyAsync(steps_dev, lsteps.data(), lsteps.size() * sizeof(LdsStep), hipMemcpyHostToDevice, stream));
+  if (n_assembles) {
+    JF_HIP(hipMemcpyAsync(w + bl.items, tables.data(), tables.size(), hipMemcpyHostToDevice, stream));
     JF_HIP(hipStreamSynchronize(stream));
   }
   EventPair ev;
@@ -2035,78 +2076,104 @@ extern "C" jf_status jf_fidelity_batch(jf_plan* const* plans, int n, void* ws, s
   JF_HIP(hipEventCreate(&ev.b));
   hipEvent_t e0 = ev.a, e1 = ev.b;
   DevState& S0 = state_of(plans[0]);
-  const bool use_graph = n > 0 && stream != nullptr;
-  // the small members' persistent launch beside the larger members' programs
+  // a lane of its own for the persistent launch where the members have only one
+  bool used[BATCH_LANES] = {};
   bool large = false;
-  for (int i = 0; i < n; ++i) large = large || state_of(plans[i]).lay.lds_comps.size() < plans[i]->prog.comps.size();
-  hipStream_t side = nullptr;
-  if (!items.empty() && large) {
-    st = side_of(plans[0], &side);
-    if (st != JF_OK) return st;
+  for (int i = 0; i < n; ++i)
+    if (has_steps(plans[i])) used[bl.lane[i]] = large = true;
+  const int small_lane = !n_items ? -1 : !large ? 0 : lanes > 1 ? lanes - 1 : 1;
+  if (small_lane >= 0) used[small_lane] = true;
+  hipStream_t lane[BATCH_LANES] = {stream};
+  for (int l = 0; l < BATCH_LANES; ++l) {
+    if (!S0.ev_lane[l]) JF_HIP(hipEventCreateWithFlags(&S0.ev_lane[l], hipEventDisableTiming));
+    if (!l) continue;
+    if (!S0.lane_stream[l - 1]) JF_HIP(hipStreamCreateWithFlags(&S0.lane_stream[l - 1], hipStreamNonBlocking));
+    lane[l] = S0.lane_stream[l - 1];
   }
+  // the launches of one lane, or of all (which = -1)
+  auto enqueue_lane = [&](int which) -> jf_status {
+    if (small_lane >= 0 && (which < 0 || which == small_lane))
+      JF_HIP(launch_persistent(reinterpret_cast<const LdsItem*>(w + bl.items), n_items,
+                               reinterpret_cast<const LdsStep*>(w + bl.steps), lane[small_lane]));
+    for (int i = 0; i < n; ++i) {
+      const int l = bl.lane[i];
+      if ((which >= 0 && which != l) || !has_steps(plans[i])) continue;
+      const jf_status ms = enqueue_program(plans[i], base[i], lane[l], nullptr, true, nullptr, w + bl.lane_bufs[l],
+                                           nullptr, state_of(plans[i]).lay.lds_comps.empty());
+      if (ms != JF_OK) return ms;
+    }
+    return JF_OK;
+  };
   std::vector<unsigned long long> key(n);
   for (int i = 0; i < n; ++i) key[i] = plans[i]->uid;
   std::vector<unsigned> gens(n);
   for (int i = 0; i < n; ++i) gens[i] = state_of(plans[i]).variant_gen;
-  if (use_graph && (S0.graph == nullptr || S0.graph_ws != ws || S0.graph_stream != stream || S0.graph_plans != key ||
-                    S0.graph_gens != gens)) {
-    if (S0.graph) {
-      hipGraphExecDestroy(S0.graph);
-      S0.graph = nullptr;
+  const bool graphs = stream != nullptr && large;
+  if (graphs && (!S0.graph_lanes || S0.graph_ws != ws || S0.graph_stream != stream || S0.graph_plans != key ||
+                 S0.graph_gens != gens || S0.graph_lanes != lanes)) {
+    S0.graph_lanes = 0;
+    for (int l = 0; l < BATCH_LANES; ++l) {
+      if (S0.graph[l]) hipGraphExecDestroy(S0.graph[l]);
+      S0.graph[l] = nullptr;
+      if (!used[l]) continue;
+      hipGraph_t g = nullptr;
+      JF_HIP(hipStreamBeginCapture(lane[l], hipStreamCaptureModeThreadLocal));
+      st = enqueue_lane(l);
+      const hipError_t ce = hipStreamEndCapture(lane[l], &g);
+      if (st != JF_OK) {
+        if (ce == hipSuccess && g) hipGraphDestroy(g);
+        return st;
+      }
+      if (ce != hipSuccess) {
+        set_error(std::string("hipStreamEndCapture: ") + hipGetErrorString(ce));
+        return JF_E_HIP;
+      }
+      const hipError_t ie = hipGraphInstantiate(&S0.graph[l], g, nullptr, nullptr, 0);
+      hipGraphDestroy(g);
+      if (ie != hipSuccess) {
+        S0.graph[l] = nullptr;
+        set_error(std::string("hipGraphInstantiate: ") + hipGetErrorString(ie));
+        return JF_E_HIP;
+      }
     }
-    hipGraph_t g = nullptr;
-    JF_HIP(hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal));
-    if (!items.empty())
-      st = launch_persistent_beside(reinterpret_cast<const LdsItem*>(items_dev), int(items.size()),
-                                    reinterpret_cast<const LdsStep*>(steps_dev), stream, side, S0.ev_fork, S0.ev_join);
-    // with the persistent launch beside them, every member's assembly (which reads its small
-    // components' sums) waits for it
-    for (int i = 0; i < n && st == JF_OK; ++i)
-      st = enqueue_program(plans[i], base[i], stream, nullptr, true, nullptr, bufs, nullptr, side == nullptr);
-    if (st == JF_OK && side) {
-      if (hipStreamWaitEvent(stream, S0.ev_join, 0) != hipSuccess) st = JF_E_HIP;
-      for (int i = 0; i < n && st == JF_OK; ++i) st = enqueue_assemble(plans[i], base[i], stream);
-    }
-    hipError_t ce = hipStreamEndCapture(stream, &g);
-    if (st != JF_OK) {
-      if (ce == hipSuccess && g) hipGraphDestroy(g);
-      return st;
-    }
-    if (ce != hipSuccess) {
-      set_error(std::string("hipStreamEndCapture: ") + hipGetErrorString(ce));
-      return JF_E_HIP;
-    }
-    JF_HIP(hipGraphInstantiate(&S0.graph, g, nullptr, nullptr, 0));
-    JF_HIP(hipGraphDestroy(g));
     S0.graph_ws = ws;
     S0.graph_stream = stream;
     S0.graph_plans = key;
     S0.graph_gens = gens;
+    S0.graph_lanes = lanes;
   }
-  JF_HIP(hipEventRecord(e0, stream));
-  if (use_graph) {
-    JF_HIP(hipGraphLaunch(S0.graph, stream));
-  } else {
-    if (!items.empty()) {
-      st = launch_persistent_beside(reinterpret_cast<const LdsItem*>(items_dev), int(items.size()),
-                                    reinterpret_cast<const LdsStep*>(steps_dev), stream, side, S0.ev_fork, S0.ev_join);
-      if (st != JF_OK) return st;
+  auto run = [&]() -> jf_status {
+    JF_HIP(hipEventRecord(e0, stream));
+    bool beside = false;
+    for (int l = 1; l < BATCH_LANES; ++l) beside = beside || used[l];
+    if (beside) JF_HIP(hipEventRecord(S0.ev_lane[0], stream));
+    for (int l = 1; l < BATCH_LANES; ++l)
+      if (used[l]) JF_HIP(hipStreamWaitEvent(lane[l], S0.ev_lane[0], 0));
+    if (graphs) {
+      for (int l = 0; l < BATCH_LANES; ++l)
+        if (used[l]) JF_HIP(hipGraphLaunch(S0.graph[l], lane[l]));
+    } else {
+      const jf_status ls = enqueue_lane(-1);
+      if (ls != JF_OK) return ls;
     }
-    for (int i = 0; i < n; ++i) {
-      st = enqueue_program(plans[i], base[i], stream, nullptr, true, nullptr, bufs, nullptr, side == nullptr);
-      if (st != JF_OK) return st;
+    for (int l = 1; l < BATCH_LANES; ++l) {
+      if (!used[l]) continue;
+      JF_HIP(hipEventRecord(S0.ev_lane[l], lane[l]));
+      JF_HIP(hipStreamWaitEvent(stream, S0.ev_lane[l], 0));
     }
-    if (side) {
-      JF_HIP(hipStreamWaitEvent(stream, S0.ev_join, 0));
-      for (int i = 0; i < n; ++i) {
-        st = enqueue_assemble(plans[i], base[i], stream);
-        if (st != JF_OK) return st;
-      }
-    }
+    if (n_assembles)
+      JF_HIP(launch_assembles(reinterpret_cast<const AssembleArgs*>(w + bl.assembles), n_assembles, stream));
+    JF_HIP(hipEventRecord(e1, stream));
+    return JF_OK;
+  };
+  st = run();
+  if (st != JF_OK) {  // nothing still runs in a lane when the caller gets its workspace back
+    for (hipStream_t l : lane)
+      if (l) (void)hipStreamSynchronize(l);
+    return st;
   }
-  JF_HIP(hipEventRecord(e1, stream));
   for (int i = 0; i < n; ++i) {
-    st = finish_pass(plans[i], base[i], stream, &out[i], nullptr, true, bufs, true);
+    st = finish_pass(plans[i], base[i], stream, &out[i], nullptr, true, w + bl.lane_bufs[bl.lane[i]], true);
     if (st != JF_OK) return st;
   }
   float ms = 0;
@@ -2119,7 +2186,8 @@ extern "C" void jf_free_plan(jf_plan* p) {
   if (!p) return;
   if (p->dev) {
     auto* s = static_cast<DevState*>(p->dev);
-    if (s->graph) hipGraphExecDestroy(s->graph);
+    for (hipGraphExec_t g : s->graph)
+      if (g) hipGraphExecDestroy(g);
     if (s->run_graph) hipGraphExecDestroy(s->run_graph);
     if (s->own_stream) {
       hipStreamSynchronize(s->own_stream);
@@ -2129,6 +2197,13 @@ extern "C" void jf_free_plan(jf_plan* p) {
       hipStreamSynchronize(s->side_stream);
       hipStreamDestroy(s->side_stream);
     }
+    for (hipStream_t l : s->lane_stream)
+      if (l) {
+        hipStreamSynchronize(l);
+        hipStreamDestroy(l);
+      }
+    for (hipEvent_t e : s->ev_lane)
+      if (e) hipEventDestroy(e);
     for (hipEvent_t e : {s->ev0, s->ev1, s->ev_order, s->ev_fork, s->ev_join, s->ev_terms[0], s->ev_terms[1]})
       if (e) hipEventDestroy(e);
     if (s->pinned_sums) hipHostFree(s->pinned_sums);

@@ -276,6 +276,7 @@ hipError_t launch_stream_copy(const void* src, void* dst, size_t bytes, int bpl,
 // double-double sum of |t|^2, first entry): the product over components on the device; host, if not
 // null, is pinned host memory that receives the same four values
 hipError_t launch_assemble(const AssembleArgs& as, hipStream_t stream);
+hipError_t launch_assembles(const AssembleArgs* as, int n, hipStream_t stream);  // a table on the device
 // out[i] += part[i] for i < n (double2 entries): a leaf's partial result of sliced wires
 hipError_t launch_accumulate(void* out, const void* part, long long n_double2, hipStream_t stream);
 

@@ -21,6 +21,7 @@
 //   k_sumsq_part/_final  the FP64 double-double sum of |t|^2 (two fixed-tree passes); k_sumsq_one
 //                        the same for a small output in one launch
 //   k_assemble           F_J and 1 - F_J from the components' sums (device and pinned host)
+//   k_assembles          the same for many plans of a batch, from a table
 //   k_terms              the per-tuple traces in tuple order, from the components' outputs
 //   k_accumulate, k_zero a wire-sliced leaf's partial traces into the output; a graph-safe fill
 //   k_stream_copy        the streaming copy that measures the HBM ceiling
@@ -2494,6 +2495,16 @@ __global__ void k_assemble(AssembleArgs as) {
 
 hipError_t launch_assemble(const AssembleArgs& as, hipStream_t stream) {
   hipLaunchKernelGGL(k_assemble, dim3(1), dim3(64), 0, stream, as);
+  return hipGetLastError();
+}
+
+__global__ void k_assembles(const AssembleArgs* as) {
+  if (threadIdx.x == 0) assemble_result(as[blockIdx.x]);
+}
+
+hipError_t launch_assembles(const AssembleArgs* as, int n, hipStream_t stream) {
+  if (n < 1 || !as) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_assembles, dim3(n), dim3(64), 0, stream, as);
   return hipGetLastError();
 }
 
