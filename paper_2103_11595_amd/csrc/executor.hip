@@ -45,6 +45,10 @@ struct DevLayout {
   size_t ctr_off = 0;    // counter of the persistent launch's fused assembly (zero in the image)
   size_t fail_off = 0;   // failure word of the grid runs (zero in the image)
   size_t flags_off = 0;  // barrier flags of the grid runs (zero in the image)
+  // the variants of a sliced component's first sliced level run in slice_lanes lanes: the level
+  // buffers of the lanes after the first, lane_stride apart, lie behind total
+  int slice_lanes = 1;
+  size_t lane_off = 0, lane_stride = 0, lanes_total = 0;
   size_t grid_bytes = 0; // bytes of the workspace that only the grid runs and the blocks use
   std::vector<size_t> leaf_off;                           // per component with sliced wires: its leaf buffer
   std::vector<int> lds_comps;                             // components run by the persistent kernel
@@ -83,7 +87,7 @@ struct DevState {
   // components' steps (fork and join by events, also inside a captured graph)
   hipStream_t side_stream = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
-  // the members of a batch run in lanes beside each other: the streams of the lanes after the first,
+  // the members of a batch, or the slices of a plan, run in lanes beside each other: the streams of the lanes after the first,
   // and the events that start them (the first) and end them
   hipStream_t lane_stream[BATCH_LANES - 1] = {};
   hipEvent_t ev_lane[BATCH_LANES] = {};
@@ -113,6 +117,28 @@ struct DevState {
 };
 
 std::atomic<unsigned> g_variant_gen{1};
+
+// The first level of a component that iterates variants (-1: none).
+int first_sliced(const ComponentProgram& cp) {
+  for (size_t lv = 0; lv < cp.levels.size(); ++lv)
+    if (cp.levels[lv].nvar > 1) return int(lv);
+  return -1;
+}
+
+// The lanes of a plan's slices: 1 where nothing is sliced, where leaves add into one output (sliced
+// wires), and where a lane's level buffers are large enough to fill the device.
+int slice_lanes_of(const Program& P) {
+  int lanes = 1;
+  for (const ComponentProgram& cp : P.comps) {
+    if (cp.lds_resident) continue;
+    size_t bytes = 0;
+    for (const Level& lv : cp.levels) bytes += 2 * lv.buf_bytes;
+    if (bytes > kLaneBytes) return 1;
+    const int lv = first_sliced(cp);
+    if (lv >= 0 && !cp.accumulate) lanes = std::max(lanes, std::min(BATCH_LANES, cp.levels[lv].nvar));
+  }
+  return lanes;
+}
 
 std::mutex g_upload_mu;
 // Plans whose tables a workspace holds: start address -> (plan, bytes of the plan's whole region:
@@ -436,7 +462,9 @@ void build_layout(const Program& P, DevState& S) {
   S.run_off.resize(P.comps.size());
   L.block_desc.resize(P.comps.size());
   S.block_off.resize(P.comps.size());
-  size_t table = GRID_WGS * GRID_FLAG_STRIDE * sizeof(unsigned);
+  L.slice_lanes = slice_lanes_of(P);
+  const size_t flag_bytes = size_t(L.slice_lanes) * GRID_WGS * GRID_FLAG_STRIDE * sizeof(unsigned);
+  size_t table = flag_bytes;
   bool any_run = false;
   for (auto& cp : P.comps)
     if (!cp.lds_resident)
@@ -452,7 +480,7 @@ void build_layout(const Program& P, DevState& S) {
   if (any_run && table <= kGridTableBytes) {
     L.grid_bytes = table;
     L.flags_off = off;
-    off += GRID_WGS * GRID_FLAG_STRIDE * sizeof(unsigned);
+    off += flag_bytes;
     for (size_t c = 0; c < P.comps.size(); ++c) {
       if (P.comps[c].lds_resident) continue;
       S.run_off[c].assign(P.comps[c].runs.size(), 0);
@@ -504,6 +532,9 @@ void build_layout(const Program& P, DevState& S) {
     maxbuf = std::max(maxbuf, o);
   }
   L.total = off + maxbuf;
+  L.lane_off = align256(L.total);
+  L.lane_stride = align256(maxbuf);
+  L.lanes_total = L.slice_lanes > 1 ? L.lane_off + size_t(L.slice_lanes - 1) * L.lane_stride : L.total;
 
   // host image of descriptors, pools and constants
   S.host_image.assign(L.image_end, 0);
@@ -791,6 +822,7 @@ struct GridUse {
   bool assemble = false;   // nothing is left to do before the assembly once this component is summed
   bool summed = false;     // the component's sum of |t|^2 is done
   bool assembled = false;  // and the assembly
+  int lane = 0;            // runs beside each other have flags of their own
 };
 
 int run_starting_at(const ComponentProgram& cp, int si) {
@@ -897,7 +929,7 @@ jf_status enqueue_steps(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipS
         a.in = cur;
         a.buf[0] = b0;
         a.buf[1] = b1;
-        a.flags = reinterpret_cast<unsigned*>(ws + L.flags_off);
+        a.flags = reinterpret_cast<unsigned*>(ws + L.flags_off) + gu->lane * GRID_WGS * GRID_FLAG_STRIDE;
         a.fail = reinterpret_cast<unsigned*>(ws + L.fail_off);
         a.limit = S.grid_wait;
         const GridStep* hs = reinterpret_cast<const GridStep*>(&S.host_image[L.run_desc[c][q]]);
@@ -1116,12 +1148,31 @@ jf_status enqueue_level(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipS
   return st;
 }
 
+// The streams of lanes 1 .. n - 1 and all lanes' events (made on first use, default priority).
+jf_status lanes_of(jf_plan* p, int n, hipStream_t stream, hipStream_t* lane) {
+  DevState& S = state_of(p);
+  lane[0] = stream;
+  for (int l = 0; l < n; ++l) {
+    if (!S.ev_lane[l]) JF_HIP(hipEventCreateWithFlags(&S.ev_lane[l], hipEventDisableTiming));
+    if (!l) continue;
+    if (!S.lane_stream[l - 1]) JF_HIP(hipStreamCreateWithFlags(&S.lane_stream[l - 1], hipStreamNonBlocking));
+    lane[l] = S.lane_stream[l - 1];
+  }
+  return JF_OK;
+}
+
 // Clear component c's output and walk its levels depth first: every prefix is computed once and
 // kept in its level buffer while the Kraus operators of the next sliced site are iterated.
+// lanes > 1: the variants of the first sliced level, with all below them, are dealt to that many
+// lanes beside each other (a step of one of them is bound by its launch or by the 64 workgroups of
+// its grid run), each with level buffers and barrier flags of its own; the launches go out to the
+// lanes in turn.  A plan of 16 leaves of 2^16 elements took 1280 us one leaf after another and takes
+// 533 in four lanes.
 jf_status enqueue_component(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipStream_t stream, size_t c, Prof* prof,
-                            Tune* tune, GridUse* gu) {
+                            Tune* tune, GridUse* gu, int lanes = 1) {
   const ComponentProgram& cp = p->prog.comps[c];
-  const DevLayout& L = state_of(p).lay;
+  DevState& S = state_of(p);
+  const DevLayout& L = S.lay;
   // Every output entry is written by the final steps of the leaves, except where leaves add
   // partial traces into it (sliced wires) or a site's Kraus count is no power of two (padded
   // variants): only then is the output cleared first.
@@ -1133,24 +1184,56 @@ jf_status enqueue_component(jf_plan* p, unsigned char* ws, unsigned char* bufs, 
   if (clear) JF_HIP(launch_zero(ws + L.out_off + size_t(cp.out_off) * 16, cp.out_len, stream));
   struct Frame {
     int lv;
-    int v;
+    int v, by;  // the variant and the distance to the lane's next one
     const void* parent;
     long long base;
   };
-  std::vector<int> vv(cp.levels.size(), 0);  // the values of the levels on the current path
-  std::vector<Frame> stack;
-  stack.push_back({0, 0, nullptr, 0});
-  while (!stack.empty()) {
-    Frame f = stack.back();
-    stack.pop_back();
-    const Level& lev = cp.levels[f.lv];
-    if (f.v + 1 < lev.nvar) stack.push_back({f.lv, f.v + 1, f.parent, f.base});
-    vv[f.lv] = f.v;
-    const long long base = f.base + f.v * lev.out_stride;
-    const void* cur = nullptr;
-    jf_status st = enqueue_level(p, ws, bufs, stream, c, f.lv, vv, f.parent, base, &cur, prof, tune, gu);
+  const int split = first_sliced(cp);
+  lanes = split < 0 || cp.accumulate ? 1 : std::min(lanes, cp.levels[split].nvar);
+  hipStream_t lane[BATCH_LANES] = {stream};
+  std::vector<int> vv[BATCH_LANES];  // the values of the levels on a lane's current path
+  std::vector<Frame> stack[BATCH_LANES];
+  if (lanes > 1) {
+    const jf_status st = lanes_of(p, lanes, stream, lane);
     if (st != JF_OK) return st;
-    if (f.lv + 1 < (int)cp.levels.size()) stack.push_back({f.lv + 1, 0, cur, base});
+  }
+  auto descend = [&](int l, int lv, const void* parent, long long base) -> jf_status {
+    if (lv != split || lanes == 1) {
+      stack[l].push_back({lv, 0, 1, parent, base});
+      return JF_OK;
+    }
+    JF_HIP(hipEventRecord(S.ev_lane[0], stream));  // reached once: no level above it has variants
+    for (int k = 0; k < lanes; ++k) {
+      if (k) JF_HIP(hipStreamWaitEvent(lane[k], S.ev_lane[0], 0));
+      stack[k].push_back({lv, k, lanes, parent, base});
+    }
+    return JF_OK;
+  };
+  for (auto& v : vv) v.assign(cp.levels.size(), 0);
+  jf_status st = descend(0, 0, nullptr, 0);
+  if (st != JF_OK) return st;
+  for (bool more = true; more;) {
+    more = false;
+    for (int l = 0; l < lanes; ++l) {
+      if (stack[l].empty()) continue;
+      more = true;
+      Frame f = stack[l].back();
+      stack[l].pop_back();
+      const Level& lev = cp.levels[f.lv];
+      if (f.v + f.by < lev.nvar) stack[l].push_back({f.lv, f.v + f.by, f.by, f.parent, f.base});
+      vv[l][f.lv] = f.v;
+      const long long base = f.base + f.v * lev.out_stride;
+      const void* cur = nullptr;
+      if (gu) gu->lane = l;
+      st = enqueue_level(p, ws, l ? ws + L.lane_off + size_t(l - 1) * L.lane_stride : bufs, lane[l], c, f.lv, vv[l],
+                         f.parent, base, &cur, prof, tune, gu);
+      if (st == JF_OK && f.lv + 1 < (int)cp.levels.size()) st = descend(l, f.lv + 1, cur, base);
+      if (st != JF_OK) return st;
+    }
+  }
+  for (int l = 1; l < lanes; ++l) {
+    JF_HIP(hipEventRecord(S.ev_lane[l], lane[l]));
+    JF_HIP(hipStreamWaitEvent(stream, S.ev_lane[l], 0));
   }
   return JF_OK;
 }
@@ -1214,7 +1297,7 @@ jf_status enqueue_assemble(jf_plan* p, unsigned char* ws, hipStream_t stream) {
 
 jf_status enqueue_program(jf_plan* p, unsigned char* ws, hipStream_t stream, Prof* prof = nullptr,
                           bool skip_lds = false, Tune* tune = nullptr, unsigned char* bufs = nullptr,
-                          hipStream_t side = nullptr, bool assemble = true, bool grid = true) {
+                          hipStream_t side = nullptr, bool assemble = true, bool grid = true, int lanes = 1) {
   const Program& P = p->prog;
   DevState& S = state_of(p);
   const DevLayout& L = S.lay;
@@ -1246,7 +1329,7 @@ jf_status enqueue_program(jf_plan* p, unsigned char* ws, hipStream_t stream, Pro
     if (cp.lds_resident) continue;
     GridUse gu;
     gu.assemble = assemble && !side && c == last;
-    jf_status st = enqueue_component(p, ws, bufs, stream, c, prof, tune, grid ? &gu : nullptr);
+    jf_status st = enqueue_component(p, ws, bufs, stream, c, prof, tune, grid ? &gu : nullptr, lanes);
     if (st != JF_OK) return st;
     if (!gu.summed)
       JF_HIP(launch_sumsq(ws + L.out_off + size_t(cp.out_off) * 16, cp.out_len,
@@ -1266,7 +1349,7 @@ jf_status upload(jf_plan* p, void* ws, hipStream_t stream, size_t region = 0) {
   std::lock_guard<std::mutex> g(g_upload_mu);
   if (S.uploaded_to == ws) {
     auto it = g_last_upload.find(ws);
-    if (it != g_last_upload.end() && it->second.plan == p) return JF_OK;
+    if (it != g_last_upload.end() && it->second.plan == p && it->second.bytes >= region) return JF_OK;
   }
   fill_lds_tables(p->prog, S.lay, static_cast<unsigned char*>(ws),
                   reinterpret_cast<LdsItem*>(&S.host_image[S.lay.lds_items_off]),
@@ -1452,8 +1535,9 @@ jf_status finish_pass(jf_plan* p, unsigned char* ws, hipStream_t stream, jf_resu
   const DevLayout& L = S.lay;
   // the failure word and the barrier flags as they were uploaded: zero
   JF_HIP(hipMemcpyAsync(ws + L.fail_off, &S.host_image[L.fail_off], sizeof(unsigned), hipMemcpyHostToDevice, stream));
-  JF_HIP(hipMemcpyAsync(ws + L.flags_off, &S.host_image[L.flags_off], GRID_WGS * GRID_FLAG_STRIDE * sizeof(unsigned),
-                        hipMemcpyHostToDevice, stream));
+  JF_HIP(hipMemcpyAsync(ws + L.flags_off, &S.host_image[L.flags_off],
+                        size_t(L.slice_lanes) * GRID_WGS * GRID_FLAG_STRIDE * sizeof(unsigned), hipMemcpyHostToDevice,
+                        stream));
   st = enqueue_program(p, ws, stream, nullptr, skip_lds, nullptr, bufs, nullptr, true, false);
   if (st != JF_OK) return st;
   return read_results(p, ws, stream, out, terms, pinned, &gave_up);
@@ -1466,18 +1550,20 @@ jf_status finish_pass(jf_plan* p, unsigned char* ws, hipStream_t stream, jf_resu
 jf_status run_one(jf_plan* p, void* ws, size_t ws_bytes, hipStream_t stream, jf_result* out, double* terms) {
   jf_status st = check_ws(p, ws, ws_bytes);
   if (st != JF_OK) return st;
-  st = upload(p, ws, stream);
+  DevState& S = state_of(p);
+  const bool graph = (p->prog.opt.flags & JF_FLAG_GRAPH) != 0;
+  // a graph keeps one lane: it submits its branches one after another
+  const int lanes = !graph && ws_bytes >= S.lay.lanes_total ? S.lay.slice_lanes : 1;
+  st = upload(p, ws, stream, lanes > 1 ? S.lay.lanes_total : 0);
   if (st != JF_OK) return st;
   st = pinned_res_of(p);  // before any enqueue or capture: the assembly writes the result there
   if (st != JF_OK) return st;
-  DevState& S = state_of(p);
   if (!S.ev0) {
     JF_HIP(hipEventCreate(&S.ev0));
     JF_HIP(hipEventCreate(&S.ev1));
     JF_HIP(hipEventCreateWithFlags(&S.ev_order, hipEventDisableTiming));
   }
   unsigned char* w = static_cast<unsigned char*>(ws);
-  const bool graph = (p->prog.opt.flags & JF_FLAG_GRAPH) != 0;
   hipStream_t s = stream;
   if (graph && stream == nullptr) {
     if (!S.own_stream) JF_HIP(hipStreamCreateWithFlags(&S.own_stream, hipStreamNonBlocking));
@@ -1522,8 +1608,12 @@ jf_status run_one(jf_plan* p, void* ws, size_t ws_bytes, hipStream_t stream, jf_
   if (graph) {
     JF_HIP(hipGraphLaunch(S.run_graph, s));
   } else {
-    st = enqueue_program(p, w, s, nullptr, false, nullptr, nullptr, side);
-    if (st != JF_OK) return st;
+    st = enqueue_program(p, w, s, nullptr, false, nullptr, nullptr, side, true, true, lanes);
+    if (st != JF_OK) {  // nothing still runs in a lane when the caller gets its workspace back
+      for (int l = 1; l < lanes; ++l)
+        if (S.lane_stream[l - 1]) (void)hipStreamSynchronize(S.lane_stream[l - 1]);
+      return st;
+    }
   }
   JF_HIP(hipEventRecord(S.ev1, s));
   jf_result r;
@@ -1538,7 +1628,7 @@ jf_status run_one(jf_plan* p, void* ws, size_t ws_bytes, hipStream_t stream, jf_
 
 }  // namespace
 
-size_t plan_workspace_bytes(jf_plan* p) { return state_of(p).lay.total; }
+size_t plan_workspace_bytes(jf_plan* p) { return state_of(p).lay.lanes_total; }
 
 }  // namespace jf
 
@@ -2083,13 +2173,9 @@ extern "C" jf_status jf_fidelity_batch(jf_plan* const* plans, int n, void* ws, s
     if (has_steps(plans[i])) used[bl.lane[i]] = large = true;
   const int small_lane = !n_items ? -1 : !large ? 0 : lanes > 1 ? lanes - 1 : 1;
   if (small_lane >= 0) used[small_lane] = true;
-  hipStream_t lane[BATCH_LANES] = {stream};
-  for (int l = 0; l < BATCH_LANES; ++l) {
-    if (!S0.ev_lane[l]) JF_HIP(hipEventCreateWithFlags(&S0.ev_lane[l], hipEventDisableTiming));
-    if (!l) continue;
-    if (!S0.lane_stream[l - 1]) JF_HIP(hipStreamCreateWithFlags(&S0.lane_stream[l - 1], hipStreamNonBlocking));
-    lane[l] = S0.lane_stream[l - 1];
-  }
+  hipStream_t lane[BATCH_LANES] = {};
+  st = lanes_of(plans[0], BATCH_LANES, stream, lane);
+  if (st != JF_OK) return st;
   // the launches of one lane, or of all (which = -1)
   auto enqueue_lane = [&](int which) -> jf_status {
     if (small_lane >= 0 && (which < 0 || which == small_lane))
