@@ -673,6 +673,12 @@ void fill_lds_tables(const Program& P, const DevLayout& L, unsigned char* ws, Ld
       e.B = ws + L.step_b[c][k][0];
       e.mode = mode_of(cp.steps[k]);
       e.final_step = cp.steps[k].final_step ? 1 : 0;
+      e.kS = cp.steps[k].kS;
+      e.kN = cp.steps[k].kN;
+      e.L = cp.steps[k].L;
+      e.nHi = int(cp.steps[k].hiA.size());
+      e.log2_out = e.nHi + e.L + e.kN;
+      e.pad = 0;
       steps[si++] = e;
     }
   }

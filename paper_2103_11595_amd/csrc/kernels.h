@@ -162,6 +162,9 @@ struct LdsStep {
   const void* B;
   int mode;
   int final_step;
+  int kS, kN, L, nHi;  // of the descriptor
+  int log2_out;        // log2 of the step's output elements
+  int pad;
 };
 struct LdsItem {
   int first, count;   // steps [first, first + count) of the step table

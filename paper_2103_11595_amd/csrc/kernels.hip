@@ -1400,7 +1400,7 @@ __global__ __launch_bounds__(256) void k_sumsq_final(const double* part, int G, 
 // ------------------------------------------------------------ persistent LDS executor ---
 // Items are whole component programs whose tensors fit in LDS.  Each workgroup takes items
 // blockIdx.x, blockIdx.x + gridDim.x, ... (static assignment: deterministic results).  A step
-// computes every output element with one thread (no in-place: the two buffers alternate).
+// reads one buffer and writes the other (no in-place).
 __device__ __forceinline__ double2 load_op(const void* B, int mode, int idx, int KN) {
   if (mode == KM_F64 || mode == KM_F32_TO_F64) return reinterpret_cast<const double2*>(B)[idx];
   if (mode == KM_SPLIT || mode == KM_SPLIT4) {  // the sum of the pieces
@@ -1422,7 +1422,103 @@ __device__ __forceinline__ double2 load_op(const void* B, int mode, int idx, int
   return v;
 }
 
-constexpr int PERSIST_NT = 1024;  // 16 waves: the FP64 products of one component hide each other's latency
+constexpr int PERSIST_LOG2 = 10;
+constexpr int PERSIST_NT = 1 << PERSIST_LOG2;  // 16 waves: the FP64 products of one component hide each other's latency
+constexpr int LDS_HEADERS = 32;                // step headers held in LDS at a time
+constexpr int LDS_OPS = DMAXK * DMAXK / PERSIST_NT;
+
+// One thread's share of a step's tables and (FP64) operator, on its way from memory.  Global loads by
+// address space: a flat load would be waited for by every LDS access behind it.
+struct LdsFetch {
+  int s, n, ra, rc, ha, hc;
+  f64v2 b[LDS_OPS];
+};
+template <typename T>
+__device__ __forceinline__ T ld_global(const void* p, int i) {
+  return reinterpret_cast<const __attribute__((address_space(1))) T*>(reinterpret_cast<uintptr_t>(p))[i];
+}
+__device__ __forceinline__ void lds_fetch(const LdsStep& h, int tid, LdsFetch& f) {
+  const int K = 1 << h.kS, Nn = 1 << h.kN, R = 1 << h.L;
+  const StepDesc* d = h.desc;
+  if (tid < K) f.s = int(ld_global<long long>(d->offS_A, tid));
+  if (tid < Nn) f.n = int(ld_global<long long>(d->offN_C, tid));
+  if (tid < R) {
+    f.ra = int(ld_global<long long>(d->offR_A, tid));
+    f.rc = int(ld_global<long long>(d->offR_C, tid));
+  }
+  if (tid < h.nHi) {
+    f.ha = ld_global<int>(d->hiA, tid);
+    f.hc = ld_global<int>(d->hiC, tid);
+  }
+  if (h.mode == KM_F64) {
+#pragma unroll
+    for (int j = 0; j < LDS_OPS; ++j)
+      if (tid + j * PERSIST_NT < K * Nn) f.b[j] = ld_global<f64v2>(h.B, tid + j * PERSIST_NT);
+  }
+}
+
+// The products of one step on the matrix cores: units of 16 rows and 8 outputs, a wave each, in the real
+// embedding (2 sums per instruction); few units share their sum between waves, through red
+// (2 PERSIST_NT doubles).  A thread per output read 36 bytes of LDS for every complex product, which
+// took 3.9 us for 1024 outputs of 32 products.  With the fetch of the next step's tables during the
+// current one, a launch whose longest component has nine steps of up to 2^10 elements went from 46 us
+// (38 with the fetch alone) to 28.
+template <typename EMIT>
+__device__ __forceinline__ void lds_products(int kS, int kN, int L, int nHi, const double2* A, const double2* sB,
+                                             const int* offS, const int* offN, const int* offRA, const int* offRC,
+                                             const int* hiA, const int* hiC, double* red, EMIT emit) {
+  using M = Mfma<double>;
+  constexpr int NW = PERSIST_NT / 64;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 4, l16 = lane & 15;
+  const int R = 1 << L, Nn = 1 << kN, ksteps = 1 << (kS - 1), lmb = kN - 3;
+  const int units = 1 << (lmb + nHi + L - 4);
+  int lks = 0;
+  while ((units << (lks + 1)) <= NW && units * ((2 << lks) - 1) <= NW / 2 && (ksteps >> (lks + 1)) >= 2) ++lks;
+  const int per = ksteps >> lks, c = M::c_of(l16), nl = M::n_of(l16), pt = g & 1;
+  const double sign = c == 0 && pt ? -1.0 : 1.0;
+  auto tile = [&](int row, const int* hix) {
+    int b = 0;
+    for (int k = 0; k < nHi; ++k)
+      if ((row >> (L + k)) & 1) b |= 1 << hix[k];
+    return b;
+  };
+  auto product = [&](int v, int t0) {
+    const int row = ((v >> lmb) << 4) + l16;
+    const double* ap = reinterpret_cast<const double*>(A + tile(row, hiA) + offRA[row & (R - 1)]) + pt;
+    const double* bp = reinterpret_cast<const double*>(sB + ((v & ((1 << lmb) - 1)) << 3) + nl) + (pt ^ c);
+    doublex4 acc = {0, 0, 0, 0}, acd = {0, 0, 0, 0};
+#pragma unroll 2
+    for (int t = t0; t < t0 + per; t += 2) {
+      const int s0 = 2 * t + (g >> 1), s1 = s0 + 2;
+      acc = M::op(sign * bp[2 * s0 * Nn], ap[2 * offS[s0]], acc);
+      acd = M::op(sign * bp[2 * s1 * Nn], ap[2 * offS[s1]], acd);
+    }
+    return acc + acd;
+  };
+  auto place = [&](int v, doublex4 acc) {
+    const int row = ((v >> lmb) << 4) + l16, n = ((v & ((1 << lmb) - 1)) << 3) + g;
+    const int oc = tile(row, hiC) + offRC[row & (R - 1)];
+    emit(oc + offN[n], make_double2(acc[0], acc[1]));
+    emit(oc + offN[n + 4], make_double2(acc[2], acc[3]));
+  };
+  if (lks == 0) {
+    for (int v = wave; v < units; v += NW) place(v, product(v, 0));
+    return;
+  }
+  const int share = (1 << lks) - 1, v = wave >> lks, part = wave & share;
+  doublex4 acc = {0, 0, 0, 0};
+  if (v < units) {
+    acc = product(v, part * per);
+    if (part)
+      for (int q = 0; q < 4; ++q) red[((v * share + part - 1) * 4 + q) * 64 + lane] = acc[q];
+  }
+  __syncthreads();
+  if (v < units && part == 0) {
+    for (int p = 0; p < share; ++p)
+      for (int q = 0; q < 4; ++q) acc[q] += red[((v * share + p) * 4 + q) * 64 + lane];
+    place(v, acc);
+  }
+}
 
 __device__ void assemble_result(const AssembleArgs& as);
 
@@ -1432,62 +1528,54 @@ __global__ __launch_bounds__(PERSIST_NT) void k_persistent(const LdsItem* __rest
   __shared__ double2 sB[DMAXK * DMAXK];  // the step's operator, in FP64 (read K times per output)
   // the step's offset tables; LDS-resident tensors have at most 2^LDS_RESIDENT_LOG2 elements
   __shared__ int offS[DMAXK], offN[DMAXK], offRA[DMAXR], offRC[DMAXR], hiA[DMAXHI], hiC[DMAXHI];
-  __shared__ double rh[PERSIST_NT], rl[PERSIST_NT];
+  __shared__ double rh[2 * PERSIST_NT];  // the sums' reduction; during a step, products shared by waves
+  double* rl = rh + PERSIST_NT;
   __shared__ double2 first;
+  __shared__ LdsStep hdr[LDS_HEADERS];
+  static_assert(sizeof(LdsStep) % 16 == 0 && DMAXR <= PERSIST_NT, "copied in 16-byte pieces; a table entry per thread");
   const int tid = threadIdx.x;
   for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
     const LdsItem item = items[it];
     int cur = -1;  // -1: the scalar 1
     double hi = 0.0, lo = 0.0;
     if (tid == 0) first = make_double2(0.0, 0.0);
+    LdsFetch nx;
     for (int q = 0; q < item.count; ++q) {
-      const LdsStep st = steps[item.first + q];
-      const StepDesc* d = st.desc;
-      const int kS = d->kS, kN = d->kN, L = d->L, nHi = d->nHi;
-      const int K = 1 << kS, Nn = 1 << kN, R = 1 << L;
+      const int h = q & (LDS_HEADERS - 1);
       __syncthreads();  // previous step complete before its tables and operator are replaced
-      for (int i = tid; i < K; i += PERSIST_NT) offS[i] = int(d->offS_A[i]);
-      for (int i = tid; i < Nn; i += PERSIST_NT) offN[i] = int(d->offN_C[i]);
-      for (int i = tid; i < R; i += PERSIST_NT) {
-        offRA[i] = int(d->offR_A[i]);
-        offRC[i] = int(d->offR_C[i]);
+      if (h == 0) {  // the headers of the next steps, so that no step's fetch waits for its own
+        const int4* from = reinterpret_cast<const int4*>(steps + item.first + q);
+        const int n16 = min(item.count - q, LDS_HEADERS) * int(sizeof(LdsStep) / 16);
+        for (int i = tid; i < n16; i += PERSIST_NT) reinterpret_cast<int4*>(hdr)[i] = from[i];
+        __syncthreads();
+        lds_fetch(hdr[0], tid, nx);
       }
-      for (int i = tid; i < nHi; i += PERSIST_NT) {
-        hiA[i] = d->hiA[i];
-        hiC[i] = d->hiC[i];
+      LdsStep st = hdr[h];
+      for (int* v : {&st.mode, &st.final_step, &st.kS, &st.kN, &st.L, &st.nHi, &st.log2_out})
+        *v = __builtin_amdgcn_readfirstlane(*v);
+      const int K = 1 << st.kS, Nn = 1 << st.kN, R = 1 << st.L, nHi = st.nHi;
+      if (tid < K) offS[tid] = nx.s;
+      if (tid < Nn) offN[tid] = nx.n;
+      if (tid < R) {
+        offRA[tid] = nx.ra;
+        offRC[tid] = nx.rc;
       }
-      for (int i = tid; i < K * Nn; i += PERSIST_NT) sB[i] = load_op(st.B, st.mode, i, K * Nn);
+      if (tid < nHi) {
+        hiA[tid] = nx.ha;
+        hiC[tid] = nx.hc;
+      }
+      if (st.mode == KM_F64) {
+#pragma unroll
+        for (int j = 0; j < LDS_OPS; ++j)
+          if (tid + j * PERSIST_NT < K * Nn) sB[tid + j * PERSIST_NT] = make_double2(nx.b[j].x, nx.b[j].y);
+      } else {
+        for (int i = tid; i < K * Nn; i += PERSIST_NT) sB[i] = load_op(st.B, st.mode, i, K * Nn);
+      }
       __syncthreads();
+      if (h + 1 < LDS_HEADERS && q + 1 < item.count) lds_fetch(hdr[h + 1], tid, nx);  // during this step
       const int dst = cur == 0 ? 1 : 0;
-      const int total = int(d->nTiles << (kN + L));
       const double2* A = cur < 0 ? nullptr : buf[cur];
-      for (int o = tid; o < total; o += PERSIST_NT) {
-        const int r = o & (R - 1);
-        const int n = (o >> L) & (Nn - 1);
-        const int t = o >> (L + kN);
-        int bA = 0, bC = 0;
-        for (int b = 0; b < nHi; ++b)
-          if ((t >> b) & 1) {
-            bA |= 1 << hiA[b];
-            bC |= 1 << hiC[b];
-          }
-        double2 acc;
-        if (!A) {  // the input is the scalar 1 (a first step: K = 1)
-          acc = make_double2(0.0, 0.0);
-          for (int s2 = 0; s2 < K; ++s2) acc = make_double2(acc.x + sB[s2 * Nn + n].x, acc.y + sB[s2 * Nn + n].y);
-        } else {
-          // two independent running sums (even / odd s) keep two FMA chains in flight
-          const int a0 = bA + offRA[r];
-          double2 e = make_double2(0.0, 0.0), f = make_double2(0.0, 0.0);
-          int s2 = 0;
-          for (; s2 + 1 < K; s2 += 2) {
-            e = cfma(e, A[a0 + offS[s2]], sB[s2 * Nn + n]);
-            f = cfma(f, A[a0 + offS[s2 + 1]], sB[(s2 + 1) * Nn + n]);
-          }
-          if (s2 < K) e = cfma(e, A[a0 + offS[s2]], sB[s2 * Nn + n]);
-          acc = make_double2(e.x + f.x, e.y + f.y);
-        }
-        const int oc = bC + offN[n] + offRC[r];
+      auto emit = [&](int oc, double2 acc) {
         if (st.final_step) {
           item.out[oc] = acc;
           const double p = fma(acc.x, acc.x, acc.y * acc.y);
@@ -1499,10 +1587,57 @@ __global__ __launch_bounds__(PERSIST_NT) void k_persistent(const LdsItem* __rest
         } else {
           buf[dst][oc] = acc;
         }
+      };
+      const int lrows = nHi + st.L;
+      if (A && st.kS >= 2 && st.kN >= 3 && lrows >= 4) {
+        lds_products(st.kS, st.kN, st.L, nHi, A, sB, offS, offN, offRA, offRC, hiA, hiC, rh, emit);
+        cur = dst;
+        continue;
+      }
+      // a step with fewer outputs than threads splits each sum over 2^ps neighbouring lanes
+      const int ps = max(0, min(min(PERSIST_LOG2 - st.log2_out, st.kS - 1), 4));
+      const int part = tid & ((1 << ps) - 1);
+      const int total = 1 << st.log2_out;
+      // with ps > 0 the outputs fit in one pass of all threads, so a wave's lanes stay together
+      for (int o = tid >> ps; o < total; o += PERSIST_NT) {
+        const int r = o & (R - 1);
+        const int n = (o >> st.L) & (Nn - 1);
+        const int t = o >> (st.L + st.kN);
+        int bA = 0, bC = 0;
+        for (int b = 0; b < nHi; ++b)
+          if ((t >> b) & 1) {
+            bA |= 1 << hiA[b];
+            bC |= 1 << hiC[b];
+          }
+        double2 acc;
+        if (!A) {  // the input is the scalar 1 (a first step: K = 1)
+          acc = make_double2(0.0, 0.0);
+          for (int s2 = part; s2 < K; s2 += 1 << ps)
+            acc = make_double2(acc.x + sB[s2 * Nn + n].x, acc.y + sB[s2 * Nn + n].y);
+        } else {
+          // two independent running sums keep two FMA chains in flight
+          const int a0 = bA + offRA[r];
+          double2 e = make_double2(0.0, 0.0), f = make_double2(0.0, 0.0);
+          int s2 = part;
+          const int by = 1 << ps;
+          for (; s2 + by < K; s2 += 2 * by) {
+            e = cfma(e, A[a0 + offS[s2]], sB[s2 * Nn + n]);
+            f = cfma(f, A[a0 + offS[s2 + by]], sB[(s2 + by) * Nn + n]);
+          }
+          if (s2 < K) e = cfma(e, A[a0 + offS[s2]], sB[s2 * Nn + n]);
+          acc = make_double2(e.x + f.x, e.y + f.y);
+        }
+        for (int w = 1; w < (1 << ps); w <<= 1) {
+          acc.x += __shfl_xor(acc.x, w, 64);
+          acc.y += __shfl_xor(acc.y, w, 64);
+        }
+        if (part) continue;
+        emit(bC + offN[n] + offRC[r], acc);
       }
       cur = dst;
     }
     // double-double reduction of the |t|^2 partial sums (fixed tree)
+    __syncthreads();  // the last step's shared products are read
     rh[tid] = hi;
     rl[tid] = lo;
     __syncthreads();
