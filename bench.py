@@ -283,9 +283,9 @@ def run_batch(args, torch, gen, jf, stream):
     """The 512-circuit batch under the budget rule: plan every member (reduced search effort, size
     cap 2^32; members wider than the cap slice wire legs), spend more search on the costliest ones
     within --replan-s of host time (keeping the cheaper plan), then run the cheapest members whose
-    estimated time fits --budget-s as ONE jf_fidelity_batch submission -- one hipGraph: the
-    LDS-resident members in one persistent launch, the others' step programs back to back sharing
-    one buffer region -- and project the rest from the planner's cost model.  Parity: the same
+    estimated time fits --budget-s as ONE jf_fidelity_batch submission -- the LDS-resident
+    members in one persistent launch, the others' step programs in up to four lanes, a hipGraph and a
+    buffer region each -- and project the rest from the planner's cost model.  Parity: the same
     members as complex128 plans in one more batch, member by member."""
     insts = gen.config4()
     cap = args.batch_cap

@@ -220,7 +220,11 @@ long long jf_plan_describe(const jf_plan* plan, char* buf, long long len);
  * components runs the former's persistent launch on a second stream of the plan's own, forked
  * from and joined back to the run's stream by events (inside the graph too).  The first call
  * allocates a small pinned host landing area per plan (held until jf_free_plan), into which the
- * device writes F_J; the call synchronises before returning.
+ * device writes F_J, and the first call with more than 254 traces one of at most 1 MB for those; the
+ * call synchronises before returning.  The variants of a plan's first sliced Kraus index run in up
+ * to four lanes beside each other (streams of the plan's own) where the workspace has the size
+ * jf_plan_info reports; a smaller one that holds a single lane runs them one after another, as do
+ * captured plans.
  * Errors: JF_E_ARG (not an Alg I plan), JF_E_OOM (workspace too small), JF_E_HIP.
  */
 jf_status jf_fidelity_alg1(jf_plan* plan, void* dev_ws, size_t ws_bytes, void* stream,

@@ -1,13 +1,14 @@
 // GPU executor: uploads a plan's step descriptors and operator blocks into the caller's
 // workspace, walks the depth-first tree of sliced Kraus sites (every prefix computed once and
-// kept in its level buffer), launches one step kernel per step, reduces each component's output
-// in FP64 and assembles F_J on the host from the few FP64 numbers copied back.  Also here: the
-// batched submission (one persistent launch for the small components, hipGraph capture), the
+// kept in its level buffer), launches the steps (one each, or several as a chain, a block or a grid
+// run), reduces each component's output in FP64 and assembles F_J on the device.  Also here: the
+// batched submission (one persistent launch for the small components, hipGraph capture, lanes), the
 // kernel autotuner, per-launch profiling, the early Definition 1 decision, and the FP32 rounding
 // of operator blocks.
 //
 // Workspace layout (every region 256-byte aligned):
-//   [step descriptors][operator pools][constants][level buffers][component outputs][sums]
+//   [descriptors][grid-run tables and flags][operator pools][constants][persistent tables]
+//   [component outputs][sums][level buffers][level buffers of further lanes]
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -15,6 +15,8 @@
 //                        piece products) on BF16 matrix cores, register-direct
 //   k_chain, k_chain_pairs, k_chain_split  several in-place FP32 (single or FP32-pair operators)
 //                        / split-form steps applied to one LDS tile per HBM pass
+//   k_block              steps that change the tensor's size too (FP32 single operators, FP64), on one
+//                        LDS tile per HBM pass
 //   k_persistent         whole small components in one workgroup's LDS (and, for a plan made
 //                        of them only, the assembly of F_J by the last workgroup)
 //   k_grid               runs of small steps in one launch, a grid barrier between them
