@@ -386,6 +386,16 @@ jf_status jf_set_kernel_variant(jf_plan* plan, int variant);
  */
 jf_status jf_set_grid_wait(jf_plan* plan, long long ticks);
 
+/*
+ * jf_last_pass -- test aid: how the plan's last pass ran.  Host only.  Errors: JF_E_ARG.
+ */
+typedef struct {
+  int grid_launches; /* launches that run several small steps, in the program last enqueued or captured */
+  int lanes;         /* lanes that its slices were dealt to (1: none beside each other) */
+  int reruns;        /* 1: a barrier gave up and the pass was run again with one launch per step */
+} jf_pass;
+jf_status jf_last_pass(jf_plan* plan, jf_pass* out);
+
 /* Definition 1: C1 and C2 are epsilon-equivalent iff F_J > 1 - eps (strict). Returns 1/0,
  * or -1 for a NULL result. */
 int jf_is_equivalent(const jf_result* result, double eps);

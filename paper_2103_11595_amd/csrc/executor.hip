@@ -102,6 +102,7 @@ struct DevState {
   long long grid_wait = 200000000;          // longest wait of a grid barrier: 2 s of the 100 MHz wall clock
   bool validated = false;                   // the program passed validate_program (plans are immutable)
   hipEvent_t ev_order = nullptr, ev0 = nullptr, ev1 = nullptr;
+  int grid_launches = 0, lanes = 1, reruns = 0;  // of the last pass (jf_last_pass)
   // pinned host landing area of the component sums (4 doubles each): a pageable destination
   // costs the runtime a staging copy on every call, which small programs feel
   double* pinned_sums = nullptr;
@@ -957,6 +958,7 @@ jf_status enqueue_steps(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipS
           }
         }
         JF_HIP(launch_grid(a, stream));
+        ++S.grid_launches;
         if (fs.final_step) {
           if (cp.accumulate) JF_HIP(launch_accumulate(out + size_t(base) * 16, a.out, cp.leaf_len, stream));
           cur = a.out;
@@ -1327,6 +1329,8 @@ jf_status enqueue_program(jf_plan* p, unsigned char* ws, hipStream_t stream, Pro
     if (st != JF_OK) return st;
   }
   grid = grid && L.grid_bytes > 0 && grid_fits_device();
+  S.grid_launches = 0;
+  S.lanes = lanes;
   size_t last = 0;  // the last component on this stream
   for (size_t c = 0; c < P.comps.size(); ++c)
     if (!P.comps[c].lds_resident) last = c;
@@ -1530,6 +1534,13 @@ jf_status read_results(jf_plan* p, unsigned char* ws, hipStream_t stream, jf_res
   return JF_OK;
 }
 
+// Before a pass: its result is not there until its assembly has written it, and a pass that ends
+// without one reads as void.
+void await_result(DevState& S) {
+  S.reruns = 0;
+  if (S.pinned_res) static_cast<volatile double*>(S.pinned_res)[3] = 1.0;
+}
+
 // Wait for a pass and read it back; a pass whose grid runs gave up waiting (their workgroups were not
 // resident together: the device was held by others) is run again with a launch per step.  bufs and
 // skip_lds as in enqueue_program (a batch member).
@@ -1538,16 +1549,23 @@ jf_status finish_pass(jf_plan* p, unsigned char* ws, hipStream_t stream, jf_resu
   bool gave_up = false;
   jf_status st = read_results(p, ws, stream, out, terms, pinned, &gave_up);
   if (st != JF_OK || !gave_up) return st;
-  const DevState& S = state_of(p);
+  DevState& S = state_of(p);
   const DevLayout& L = S.lay;
   // the failure word and the barrier flags as they were uploaded: zero
   JF_HIP(hipMemcpyAsync(ws + L.fail_off, &S.host_image[L.fail_off], sizeof(unsigned), hipMemcpyHostToDevice, stream));
   JF_HIP(hipMemcpyAsync(ws + L.flags_off, &S.host_image[L.flags_off],
                         size_t(L.slice_lanes) * GRID_WGS * GRID_FLAG_STRIDE * sizeof(unsigned), hipMemcpyHostToDevice,
                         stream));
+  await_result(S);
+  S.reruns = 1;
   st = enqueue_program(p, ws, stream, nullptr, skip_lds, nullptr, bufs, nullptr, true, false);
   if (st != JF_OK) return st;
-  return read_results(p, ws, stream, out, terms, pinned, &gave_up);
+  st = read_results(p, ws, stream, out, terms, pinned, &gave_up);
+  if (st == JF_OK && gave_up) {
+    set_error("the pass ended without a result");
+    return JF_E_HIP;
+  }
+  return st;
 }
 
 // One run of a plan.  With JF_FLAG_GRAPH the step program is captured into a hipGraph on the first
@@ -1612,6 +1630,7 @@ jf_status run_one(jf_plan* p, void* ws, size_t ws_bytes, hipStream_t stream, jf_
     S.run_graph_gen = S.variant_gen;
   }
   JF_HIP(hipEventRecord(S.ev0, s));
+  await_result(S);
   if (graph) {
     JF_HIP(hipGraphLaunch(S.run_graph, s));
   } else {
@@ -1709,6 +1728,7 @@ extern "C" jf_status jf_fidelity_noalloc(jf_plan* p, void* stream_v, jf_result* 
   const auto t0 = std::chrono::steady_clock::now();
   st = upload(p, ws, stream);  // a copy of the plan's tables (every plan shares the scratch)
   if (st != JF_OK) return st;
+  await_result(state_of(p));
   st = enqueue_program(p, static_cast<unsigned char*>(ws), stream);  // eager: no graph, no events
   if (st != JF_OK) return st;
   jf_result r;
@@ -1826,6 +1846,18 @@ extern "C" jf_status jf_autotune(jf_plan* p, void* ws, size_t ws_bytes, void* st
   return JF_OK;
 }
 
+extern "C" jf_status jf_last_pass(jf_plan* p, jf_pass* out) {
+  if (!p || !out) {
+    set_error("jf_last_pass: bad argument");
+    return JF_E_ARG;
+  }
+  const DevState& S = state_of(p);
+  out->grid_launches = S.grid_launches;
+  out->lanes = S.lanes;
+  out->reruns = S.reruns;
+  return JF_OK;
+}
+
 extern "C" jf_status jf_set_grid_wait(jf_plan* p, long long ticks) {
   if (!p || ticks < 0) {
     set_error("jf_set_grid_wait: bad argument");
@@ -1907,6 +1939,7 @@ extern "C" jf_status jf_decide_equivalence(jf_plan* p, double eps, void* ws, siz
   if (last < 0) {  // one pass computes every term
     st = pinned_res_of(p);
     if (st != JF_OK) return st;
+    await_result(state_of(p));
     st = enqueue_program(p, w, stream);
     if (st != JF_OK) return st;
     jf_result r;
@@ -2236,6 +2269,7 @@ extern "C" jf_status jf_fidelity_batch(jf_plan* const* plans, int n, void* ws, s
     S0.graph_lanes = lanes;
   }
   auto run = [&]() -> jf_status {
+    for (int i = 0; i < n; ++i) await_result(state_of(plans[i]));
     JF_HIP(hipEventRecord(e0, stream));
     bool beside = false;
     for (int l = 1; l < BATCH_LANES; ++l) beside = beside || used[l];

@@ -101,6 +101,10 @@ class jf_decision(C.Structure):
         return {k: getattr(self, k) for k, _ in self._fields_}
 
 
+class jf_pass(C.Structure):
+    _fields_ = [("grid_launches", C.c_int), ("lanes", C.c_int), ("reruns", C.c_int)]
+
+
 # jf_kernel_variant
 KV_AUTO, KV_STAGED_256, KV_STAGED_512, KV_DIRECT_256, KV_DIRECT_512, KV_FMA, KV_GAUSS_256, KV_GAUSS_512 = range(8)
 KV_CHAIN = 8  # profiles only: a chain of steps in one launch
@@ -113,7 +117,8 @@ EXPORTS = ["jf_load_circuit", "jf_plan_contraction", "jf_plan_info", "jf_plan_st
            "jf_fidelity_alg1", "jf_fidelity_alg2", "jf_batch_workspace", "jf_fidelity_batch",
            "jf_is_equivalent", "jf_free_circuit", "jf_free_plan", "jf_last_error", "jf_emulate_plan",
            "jf_profile_run", "jf_plan_describe", "jf_profile_steps", "jf_autotune", "jf_set_kernel_variant",
-           "jf_decide_equivalence", "jf_workspace_release", "jf_fidelity_noalloc", "jf_stream_copy", "jf_set_grid_wait"]
+           "jf_decide_equivalence", "jf_workspace_release", "jf_fidelity_noalloc", "jf_stream_copy", "jf_set_grid_wait",
+           "jf_last_pass"]
 
 _lib = None
 
@@ -154,6 +159,7 @@ def lib():
     L.jf_autotune.argtypes = [vp, vp, sz, vp, C.c_int]
     L.jf_set_kernel_variant.argtypes = [vp, C.c_int]
     L.jf_set_grid_wait.argtypes = [vp, C.c_longlong]
+    L.jf_last_pass.argtypes = [vp, C.POINTER(jf_pass)]
     L.jf_decide_equivalence.argtypes = [vp, C.c_double, vp, sz, vp, C.POINTER(jf_decision)]
     L.jf_workspace_release.argtypes = [vp, sz]
     L.jf_fidelity_noalloc.argtypes = [vp, vp, C.POINTER(jf_result), C.POINTER(C.c_double)]
@@ -209,6 +215,12 @@ class Plan:
         s = jf_plan_stats()
         _check(lib().jf_plan_stats_get(self.ptr, C.byref(s)))
         return s.as_dict()
+
+    def last_pass(self):
+        """How the last pass ran (test aid): launches of several small steps, lanes, reruns."""
+        s = jf_pass()
+        _check(lib().jf_last_pass(self.ptr, C.byref(s)))
+        return {k: getattr(s, k) for k, _ in s._fields_}
 
     def describe(self):
         """Per-step shapes of the lowered program (list of dicts)."""

@@ -1,0 +1,89 @@
+"""GPU tests of passes whose grid barrier gives up: with a wait of 0 every workgroup leaves at its first
+barrier, and the result has to come from the pass that is run again with a launch per step, also on a
+plan, a workspace and a landing area that no pass has written before (a stale answer cannot pass).
+Tolerances: complex128 1e-12, complex64 and the split form 1e-6 (the bars of their forms)."""
+import numpy as np
+import pytest
+
+from oracle import dense
+from paper_2103_11595_amd import instances as gen
+from paper_2103_11595_amd import jf
+
+pytestmark = pytest.mark.gpu
+TOL = {"c128": 1e-12, "c64": 1e-6, "bf16x6": 1e-6}
+QUICK = jf.JF_FLAG_EFFORT(1)  # little path search
+PLAIN = QUICK | jf.JF_FLAG_NO_FUSE | jf.JF_FLAG_NO_CANCEL  # one step per tensor: more than one run of small steps
+CASES = {"one run": (8, 220, 3, 22, QUICK), "several runs": (7, 60, 2, 18, PLAIN)}
+DEFAULT_WAIT = 200000000
+
+
+def _case(name):
+    n, gates, sites, seed, flags = CASES[name]
+    inst = gen.random_circuit(n, gates, sites, 1e-3, 0.2, seed)
+    ref = dense.fidelity_alg1(inst, want_terms=True)
+    return inst, flags, ref["fj"], np.array([ref["terms"][k] for k in sorted(ref["terms"])])
+
+
+def _workspace(nbytes):
+    import torch
+    ws = jf.workspace(nbytes)
+    ws.fill_(255)  # NaN wherever a launch leaves something unwritten
+    jf.jf_workspace_release(ws)
+    torch.cuda.synchronize()
+    return ws
+
+
+def _never_waits(p):
+    assert jf.lib().jf_set_grid_wait(p.ptr, 0) == 0
+    return p
+
+
+def _run(p, alg, ws, stream=None):
+    return jf.jf_fidelity_alg1(p, ws, stream, want_terms=True) if alg == 1 else jf.jf_fidelity_alg2(p, ws, stream)
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64", "bf16x6"])
+@pytest.mark.parametrize("name", CASES)
+def test_a_first_pass_whose_barrier_gives_up(name, dtype):
+    import torch
+    inst, flags, fj, terms = _case(name)
+    side = torch.cuda.Stream()
+    for alg in (1, 2):
+        for graph in (0, jf.JF_FLAG_GRAPH):
+            print("[gpu-test] void pass", name, dtype, "alg", alg, "graph", bool(graph), flush=True)
+            p = _never_waits(jf.plan(inst, alg, dtype, flags=flags | graph))
+            ws = _workspace(p.info()["workspace_bytes"])
+            got = _run(p, alg, ws, side if graph else None)
+            assert p.last_pass()["reruns"] == 1
+            assert abs(got["fj"] - fj) <= TOL[dtype]
+            if alg == 1:
+                assert np.max(np.abs(got["terms"] - terms)) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_a_void_pass_on_the_shared_scratch(name):
+    """The scratch of jf_fidelity_noalloc holds another plan's result when the barrier gives up."""
+    inst, flags, fj, terms = _case(name)
+    other = jf.plan(gen.random_circuit(8, 220, 3, 1e-3, 0.2, 20), 1, "c128", flags=QUICK)
+    p = _never_waits(jf.plan(inst, 1, "c128", flags=flags))
+    print("[gpu-test] void pass without allocations", name, flush=True)
+    jf.jf_fidelity_noalloc(other)
+    got = jf.jf_fidelity_noalloc(p, want_terms=True)
+    assert p.last_pass()["reruns"] == 1
+    assert abs(got["fj"] - fj) <= 1e-12 and np.max(np.abs(got["terms"] - terms)) <= 1e-12
+
+
+def test_void_passes_in_a_batch_and_a_decision():
+    import torch
+    cases = [_case(name) for name in CASES]
+    for stream in (torch.cuda.Stream(), None):
+        print("[gpu-test] void passes in a batch", "stream" if stream else "null", flush=True)
+        plans = [_never_waits(jf.plan(c[0], 1, "c128", flags=c[1])) for c in cases]
+        ws = _workspace(jf.jf_batch_workspace(plans))
+        for p, c, r in zip(plans, cases, jf.jf_fidelity_batch(plans, ws, stream)):
+            assert p.last_pass()["reruns"] == 1 and abs(r["fj"] - c[2]) <= 1e-12
+    inst, flags, fj, _ = cases[0]
+    p = _never_waits(jf.plan(inst, 1, "c128", flags=flags))
+    print("[gpu-test] void pass of a decision", flush=True)
+    d = jf.jf_decide_equivalence(p, 1 - fj + 0.01, _workspace(p.info()["workspace_bytes"]))
+    assert p.last_pass()["reruns"] == 1 and d["decision"] == 1 and abs(d["fj_lower"] - fj) <= 1e-12
