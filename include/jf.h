@@ -247,6 +247,8 @@ jf_status jf_fidelity_alg2(jf_plan* plan, void* dev_ws, size_t ws_bytes, void* s
  * 64 MB of buffers all run in the first lane, so the workspace is the sum of the plans' small parts,
  * the largest buffer set and at most 192 MB.  out[i] receives plan i's result.  The workspace must
  * hold jf_batch_workspace bytes; one that holds only a single lane's runs everything in that.
+ * A plan may stand in the batch more than once.  The first plan keeps a pinned host landing area of 32
+ * bytes an entry.
  */
 jf_status jf_batch_workspace(jf_plan* const* plans, int n, size_t* workspace_bytes);
 jf_status jf_fidelity_batch(jf_plan* const* plans, int n, void* dev_ws, size_t ws_bytes,
@@ -392,7 +394,8 @@ jf_status jf_set_grid_wait(jf_plan* plan, long long ticks);
 typedef struct {
   int grid_launches; /* launches that run several small steps, in the program last enqueued or captured */
   int lanes;         /* lanes that its slices were dealt to (1: none beside each other) */
-  int reruns;        /* 1: a barrier gave up and the pass was run again with one launch per step */
+  int reruns;        /* times that the call ran the plan's pass again with one launch per step, after a
+                        barrier gave up (a plan stands in a batch more than once: of all its entries) */
 } jf_pass;
 jf_status jf_last_pass(jf_plan* plan, jf_pass* out);
 

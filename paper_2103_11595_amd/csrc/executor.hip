@@ -66,6 +66,14 @@ struct DevLayout {
 constexpr int BATCH_LANES = 4;               // hardware queues of a process
 constexpr size_t kLaneBytes = size_t(64) << 20;  // level buffers of a member that shares the device
 
+// Where a pass leaves its result (four doubles): pinned host memory and its device address, or nowhere
+// (the result is copied out of the workspace).
+struct Landing {
+  double* host = nullptr;
+  double* dev = nullptr;
+  Landing entry(int i) const { return {host + 4 * i, dev + 4 * i}; }
+};
+
 struct DevState {
   DevLayout lay;
   std::vector<unsigned char> host_image;  // descriptors + pools + constants, uploaded as one copy
@@ -109,8 +117,11 @@ struct DevState {
   // pinned host landing area of F_J, 1 - F_J, |Im| (4 doubles), written by the assembly kernel
   // itself: allocated before the first enqueue of the allocating entry points, so every program
   // enqueued or captured after that writes it
-  double* pinned_res = nullptr;
-  double* pinned_res_dev = nullptr;  // its device address (hipHostGetDevicePointer)
+  Landing res;
+  // the results of a batch (of which this is the first plan): one per entry, since a plan may stand in
+  // it twice
+  Landing batch_res;
+  int batch_entries = 0;
   // pinned host landing area of per-tuple traces: behind the result in its page where they fit, else
   // its own, up to 2 kTermChunk of them in two halves (the events: a half has landed)
   double2* pinned_terms = nullptr;
@@ -830,6 +841,7 @@ struct GridUse {
   bool assemble = false;   // nothing is left to do before the assembly once this component is summed
   bool summed = false;     // the component's sum of |t|^2 is done
   bool assembled = false;  // and the assembly
+  double* host = nullptr;  // where the assembly leaves the result (Landing::dev)
   int lane = 0;            // runs beside each other have flags of their own
 };
 
@@ -860,7 +872,7 @@ const void* grid_output(const GridArgs& a) {
   return cur;
 }
 
-AssembleArgs assemble_args(jf_plan* p, unsigned char* ws);
+AssembleArgs assemble_args(jf_plan* p, unsigned char* ws, double* host);
 jf_status enqueue_steps(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipStream_t stream, size_t c, int lv,
                         int from, int to, const std::vector<int>& vv, const void* cur, long long base, const void** end,
                         Prof* prof, Tune* tune, GridUse* gu);
@@ -952,7 +964,7 @@ jf_status enqueue_steps(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipS
             a.sums = reinterpret_cast<double*>(ws + L.sums_off) + 4 * c;
             gu->summed = true;
             if (gu->assemble) {
-              a.as = assemble_args(p, ws);
+              a.as = assemble_args(p, ws, gu->host);
               gu->assembled = true;
             }
           }
@@ -1279,7 +1291,7 @@ jf_status launch_persistent_beside(const LdsItem* items, int n, const LdsStep* s
 // components, which then overlaps the other components' steps (one workgroup per component, so
 // it leaves the rest of the device to them); null runs everything on `stream` in order.
 // Arguments of the assembly of a plan's F_J from its component sums (device addresses in ws).
-AssembleArgs assemble_args(jf_plan* p, unsigned char* ws) {
+AssembleArgs assemble_args(jf_plan* p, unsigned char* ws, double* host) {
   const Program& P = p->prog;
   const DevState& S = state_of(p);
   const double s = std::exp2(P.log2_scale);  // exact: an integer power of two
@@ -1292,32 +1304,34 @@ AssembleArgs assemble_args(jf_plan* p, unsigned char* ws) {
   a.v0re = v0.real();
   a.v0im = v0.imag();
   a.res = reinterpret_cast<double*>(ws + S.lay.res_off);
-  a.host = S.pinned_res_dev;
+  a.host = host;
   a.fail = reinterpret_cast<const unsigned*>(ws + S.lay.fail_off);
   a.counter = reinterpret_cast<unsigned*>(ws + S.lay.ctr_off);
   return a;
 }
 
 // The product over components and 1 - F_J of a plan, on the device (after all its components).
-jf_status enqueue_assemble(jf_plan* p, unsigned char* ws, hipStream_t stream) {
-  JF_HIP(launch_assemble(assemble_args(p, ws), stream));
+jf_status enqueue_assemble(jf_plan* p, unsigned char* ws, hipStream_t stream, double* host) {
+  JF_HIP(launch_assemble(assemble_args(p, ws, host), stream));
   return JF_OK;
 }
 
-jf_status enqueue_program(jf_plan* p, unsigned char* ws, hipStream_t stream, Prof* prof = nullptr,
+jf_status enqueue_program(jf_plan* p, unsigned char* ws, hipStream_t stream, double* host, Prof* prof = nullptr,
                           bool skip_lds = false, Tune* tune = nullptr, unsigned char* bufs = nullptr,
                           hipStream_t side = nullptr, bool assemble = true, bool grid = true, int lanes = 1) {
   const Program& P = p->prog;
   DevState& S = state_of(p);
   const DevLayout& L = S.lay;
   if (!bufs) bufs = ws + L.buf_off;
+  S.grid_launches = 0;
+  S.lanes = lanes;
   const bool lds = !skip_lds && !L.lds_comps.empty();
   if (lds && assemble && L.lds_comps.size() == P.comps.size()) {
     // every component in the persistent launch, which also assembles: one launch per run
     JF_HIP(launch_persistent_assemble(reinterpret_cast<const LdsItem*>(ws + L.lds_items_off),
                                       int(L.lds_comps.size()),
-                                      reinterpret_cast<const LdsStep*>(ws + L.lds_steps_off), assemble_args(p, ws),
-                                      stream));
+                                      reinterpret_cast<const LdsStep*>(ws + L.lds_steps_off),
+                                      assemble_args(p, ws, host), stream));
     return JF_OK;
   }
   if (!lds) side = nullptr;
@@ -1329,8 +1343,6 @@ jf_status enqueue_program(jf_plan* p, unsigned char* ws, hipStream_t stream, Pro
     if (st != JF_OK) return st;
   }
   grid = grid && L.grid_bytes > 0 && grid_fits_device();
-  S.grid_launches = 0;
-  S.lanes = lanes;
   size_t last = 0;  // the last component on this stream
   for (size_t c = 0; c < P.comps.size(); ++c)
     if (!P.comps[c].lds_resident) last = c;
@@ -1340,6 +1352,7 @@ jf_status enqueue_program(jf_plan* p, unsigned char* ws, hipStream_t stream, Pro
     if (cp.lds_resident) continue;
     GridUse gu;
     gu.assemble = assemble && !side && c == last;
+    gu.host = host;
     jf_status st = enqueue_component(p, ws, bufs, stream, c, prof, tune, grid ? &gu : nullptr, lanes);
     if (st != JF_OK) return st;
     if (!gu.summed)
@@ -1349,7 +1362,7 @@ jf_status enqueue_program(jf_plan* p, unsigned char* ws, hipStream_t stream, Pro
     assembled = gu.assembled;
   }
   if (side) JF_HIP(hipStreamWaitEvent(stream, S.ev_join, 0));
-  return assemble && !assembled ? enqueue_assemble(p, ws, stream) : JF_OK;
+  return assemble && !assembled ? enqueue_assemble(p, ws, stream, host) : JF_OK;
 }
 
 // Copy the plan's tables into ws (unless they are there already).  region: the bytes from ws on
@@ -1427,14 +1440,26 @@ constexpr long long kTermChunk = 1 << 15;  // traces per half of the landing are
 // The landing area of the result (and of few traces).
 jf_status pinned_res_of(jf_plan* p) {
   DevState& S = state_of(p);
-  if (S.pinned_res) return JF_OK;
+  if (S.res.host) return JF_OK;
   void *h = nullptr, *d = nullptr;
   const jf_status st = pinned_coherent(4 * sizeof(double) + kTermsWithRes * sizeof(double2), &h, &d);
-  S.pinned_res = static_cast<double*>(h);
-  S.pinned_res_dev = static_cast<double*>(d);
+  S.res = {static_cast<double*>(h), static_cast<double*>(d)};
   return st;
 }
 
+// The landing areas of a batch of n entries, kept by its first plan; growing them voids its captured
+// lanes, which write the old ones.
+jf_status batch_res_of(DevState& S, int n) {
+  if (n <= S.batch_entries) return JF_OK;
+  void *h = nullptr, *d = nullptr;
+  const jf_status st = pinned_coherent(size_t(n) * 4 * sizeof(double), &h, &d);
+  if (st != JF_OK) return st;
+  if (S.batch_res.host) (void)hipHostFree(S.batch_res.host);
+  S.batch_res = {static_cast<double*>(h), static_cast<double*>(d)};
+  S.batch_entries = n;
+  S.graph_lanes = 0;
+  return JF_OK;
+}
 
 // Arguments of the traces' kernel; false where the plan does not fit them (the host gathers then).
 bool term_args(jf_plan* p, unsigned char* ws, TermArgs& a) {
@@ -1475,16 +1500,16 @@ jf_status pinned_terms_of(jf_plan* p) {
   return st;
 }
 
-// Wait for the run and read F_J back (with terms, also the per-tuple outputs).  With pinned, the
-// assembly kernel has written the result into the plan's pinned landing area (pinned_res_of before
-// the enqueue), so only the terms need a copy; without (the no-allocation entry point: no host
-// allocation by the library), the result is copied into pageable host memory.
-jf_status read_results(jf_plan* p, unsigned char* ws, hipStream_t stream, jf_result* out, double* terms, bool pinned,
-                       bool* gave_up) {
+// Wait for the run and read F_J back (with terms, also the per-tuple outputs).  With a landing
+// area the assembly kernel has written the result there, so only the terms need a copy; without (the
+// no-allocation entry point: no host allocation by the library), the result is copied into pageable
+// host memory.
+jf_status read_results(jf_plan* p, unsigned char* ws, hipStream_t stream, jf_result* out, double* terms,
+                       const Landing& res_at, bool* gave_up) {
   const Program& P = p->prog;
   DevState& S = state_of(p);
   double res[4];
-  const bool on_host = pinned && S.pinned_res;
+  const bool on_host = res_at.host != nullptr;
   if (!on_host) JF_HIP(hipMemcpyAsync(res, ws + S.lay.res_off, sizeof(res), hipMemcpyDeviceToHost, stream));
   // the traces: put in order on the device, chunk by chunk through a pinned landing area (half of it
   // fills while the other is copied out); without host allocations, gathered on the host
@@ -1496,8 +1521,8 @@ jf_status read_results(jf_plan* p, unsigned char* ws, hipStream_t stream, jf_res
     const jf_status st = pinned_terms_of(p);
     if (st != JF_OK) return st;
     const bool with_res = total <= kTermsWithRes;
-    land = with_res ? reinterpret_cast<double2*>(S.pinned_res + 4) : S.pinned_terms;
-    land_dev = with_res ? reinterpret_cast<double2*>(S.pinned_res_dev + 4) : S.pinned_terms_dev;
+    land = with_res ? reinterpret_cast<double2*>(S.res.host + 4) : S.pinned_terms;
+    land_dev = with_res ? reinterpret_cast<double2*>(S.res.dev + 4) : S.pinned_terms_dev;
     JF_HIP(launch_terms(ta, 0, std::min(total, kTermChunk), land_dev, stream));
     if (total > kTermChunk) JF_HIP(hipEventRecord(S.ev_terms[0], stream));
   }
@@ -1512,7 +1537,7 @@ jf_status read_results(jf_plan* p, unsigned char* ws, hipStream_t stream, jf_res
   }
   if (total > kTermChunk && on_device) JF_HIP(hipEventSynchronize(S.ev_terms[0]));
   else JF_HIP(hipStreamSynchronize(stream));
-  if (on_host) std::memcpy(res, S.pinned_res, sizeof(res));
+  if (on_host) std::memcpy(res, res_at.host, sizeof(res));
   *gave_up = res[3] != 0.0;
   if (*gave_up) return JF_OK;
   jf_result r;
@@ -1536,18 +1561,17 @@ jf_status read_results(jf_plan* p, unsigned char* ws, hipStream_t stream, jf_res
 
 // Before a pass: its result is not there until its assembly has written it, and a pass that ends
 // without one reads as void.
-void await_result(DevState& S) {
-  S.reruns = 0;
-  if (S.pinned_res) static_cast<volatile double*>(S.pinned_res)[3] = 1.0;
+void await_result(const Landing& at) {
+  if (at.host) static_cast<volatile double*>(at.host)[3] = 1.0;
 }
 
 // Wait for a pass and read it back; a pass whose grid runs gave up waiting (their workgroups were not
 // resident together: the device was held by others) is run again with a launch per step.  bufs and
 // skip_lds as in enqueue_program (a batch member).
 jf_status finish_pass(jf_plan* p, unsigned char* ws, hipStream_t stream, jf_result* out, double* terms,
-                      bool pinned = true, unsigned char* bufs = nullptr, bool skip_lds = false) {
+                      const Landing& at, unsigned char* bufs = nullptr, bool skip_lds = false) {
   bool gave_up = false;
-  jf_status st = read_results(p, ws, stream, out, terms, pinned, &gave_up);
+  jf_status st = read_results(p, ws, stream, out, terms, at, &gave_up);
   if (st != JF_OK || !gave_up) return st;
   DevState& S = state_of(p);
   const DevLayout& L = S.lay;
@@ -1556,11 +1580,11 @@ jf_status finish_pass(jf_plan* p, unsigned char* ws, hipStream_t stream, jf_resu
   JF_HIP(hipMemcpyAsync(ws + L.flags_off, &S.host_image[L.flags_off],
                         size_t(L.slice_lanes) * GRID_WGS * GRID_FLAG_STRIDE * sizeof(unsigned), hipMemcpyHostToDevice,
                         stream));
-  await_result(S);
-  S.reruns = 1;
-  st = enqueue_program(p, ws, stream, nullptr, skip_lds, nullptr, bufs, nullptr, true, false);
+  await_result(at);
+  ++S.reruns;
+  st = enqueue_program(p, ws, stream, at.dev, nullptr, skip_lds, nullptr, bufs, nullptr, true, false);
   if (st != JF_OK) return st;
-  st = read_results(p, ws, stream, out, terms, pinned, &gave_up);
+  st = read_results(p, ws, stream, out, terms, at, &gave_up);
   if (st == JF_OK && gave_up) {
     set_error("the pass ended without a result");
     return JF_E_HIP;
@@ -1608,7 +1632,7 @@ jf_status run_one(jf_plan* p, void* ws, size_t ws_bytes, hipStream_t stream, jf_
     }
     hipGraph_t g = nullptr;
     JF_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-    st = enqueue_program(p, w, s, nullptr, false, nullptr, nullptr, side);
+    st = enqueue_program(p, w, s, S.res.dev, nullptr, false, nullptr, nullptr, side);
     const hipError_t ce = hipStreamEndCapture(s, &g);
     if (st != JF_OK) {
       if (ce == hipSuccess && g) hipGraphDestroy(g);
@@ -1630,11 +1654,12 @@ jf_status run_one(jf_plan* p, void* ws, size_t ws_bytes, hipStream_t stream, jf_
     S.run_graph_gen = S.variant_gen;
   }
   JF_HIP(hipEventRecord(S.ev0, s));
-  await_result(S);
+  await_result(S.res);
+  S.reruns = 0;
   if (graph) {
     JF_HIP(hipGraphLaunch(S.run_graph, s));
   } else {
-    st = enqueue_program(p, w, s, nullptr, false, nullptr, nullptr, side, true, true, lanes);
+    st = enqueue_program(p, w, s, S.res.dev, nullptr, false, nullptr, nullptr, side, true, true, lanes);
     if (st != JF_OK) {  // nothing still runs in a lane when the caller gets its workspace back
       for (int l = 1; l < lanes; ++l)
         if (S.lane_stream[l - 1]) (void)hipStreamSynchronize(S.lane_stream[l - 1]);
@@ -1643,7 +1668,7 @@ jf_status run_one(jf_plan* p, void* ws, size_t ws_bytes, hipStream_t stream, jf_
   }
   JF_HIP(hipEventRecord(S.ev1, s));
   jf_result r;
-  st = finish_pass(p, w, s, &r, terms);
+  st = finish_pass(p, w, s, &r, terms, S.res);
   if (st != JF_OK) return st;
   float ms = 0;
   JF_HIP(hipEventElapsedTime(&ms, S.ev0, S.ev1));
@@ -1728,11 +1753,11 @@ extern "C" jf_status jf_fidelity_noalloc(jf_plan* p, void* stream_v, jf_result* 
   const auto t0 = std::chrono::steady_clock::now();
   st = upload(p, ws, stream);  // a copy of the plan's tables (every plan shares the scratch)
   if (st != JF_OK) return st;
-  await_result(state_of(p));
-  st = enqueue_program(p, static_cast<unsigned char*>(ws), stream);  // eager: no graph, no events
+  state_of(p).reruns = 0;
+  st = enqueue_program(p, static_cast<unsigned char*>(ws), stream, nullptr);  // eager: no graph, no events
   if (st != JF_OK) return st;
   jf_result r;
-  st = finish_pass(p, static_cast<unsigned char*>(ws), stream, &r, terms, false);
+  st = finish_pass(p, static_cast<unsigned char*>(ws), stream, &r, terms, Landing());
   if (st != JF_OK) return st;
   r.seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
   *out = r;
@@ -1778,7 +1803,7 @@ extern "C" jf_status jf_profile_run(jf_plan* p, void* ws, size_t ws_bytes, void*
   JF_HIP(hipEventCreate(&ev.b));
   hipEvent_t e0 = ev.a, e1 = ev.b;
   JF_HIP(hipEventRecord(e0, stream));
-  st = enqueue_program(p, static_cast<unsigned char*>(ws), stream, &prof);
+  st = enqueue_program(p, static_cast<unsigned char*>(ws), stream, nullptr, &prof);
   if (st != JF_OK) return st;
   JF_HIP(hipEventRecord(e1, stream));
   JF_HIP(hipStreamSynchronize(stream));
@@ -1811,7 +1836,7 @@ extern "C" jf_status jf_profile_steps(jf_plan* p, void* ws, size_t ws_bytes, voi
   st = upload(p, ws, stream);
   if (st != JF_OK) return st;
   Prof prof;
-  st = enqueue_program(p, static_cast<unsigned char*>(ws), stream, &prof);
+  st = enqueue_program(p, static_cast<unsigned char*>(ws), stream, nullptr, &prof);
   if (st != JF_OK) return st;
   JF_HIP(hipStreamSynchronize(stream));
   const int n = int(prof.rec.size());
@@ -1839,7 +1864,7 @@ extern "C" jf_status jf_autotune(jf_plan* p, void* ws, size_t ws_bytes, void* st
   tune.reps = reps > 0 ? reps : 3;
   tune.done.resize(p->prog.comps.size());
   for (size_t c = 0; c < p->prog.comps.size(); ++c) tune.done[c].assign(p->prog.comps[c].steps.size(), 0);
-  st = enqueue_program(p, static_cast<unsigned char*>(ws), stream, nullptr, false, &tune);
+  st = enqueue_program(p, static_cast<unsigned char*>(ws), stream, nullptr, nullptr, false, &tune);
   if (st != JF_OK) return st;
   JF_HIP(hipStreamSynchronize(stream));
   state_of(p).variant_gen = g_variant_gen.fetch_add(1);
@@ -1939,11 +1964,13 @@ extern "C" jf_status jf_decide_equivalence(jf_plan* p, double eps, void* ws, siz
   if (last < 0) {  // one pass computes every term
     st = pinned_res_of(p);
     if (st != JF_OK) return st;
-    await_result(state_of(p));
-    st = enqueue_program(p, w, stream);
+    const Landing& at = state_of(p).res;
+    await_result(at);
+    state_of(p).reruns = 0;
+    st = enqueue_program(p, w, stream, at.dev);
     if (st != JF_OK) return st;
     jf_result r;
-    st = finish_pass(p, w, stream, &r, nullptr);
+    st = finish_pass(p, w, stream, &r, nullptr, at);
     if (st != JF_OK) return st;
     d.fj_lower = d.fj_upper = r.fj;
     d.leaves_run = d.leaves_total;
@@ -2180,9 +2207,10 @@ extern "C" jf_status jf_fidelity_batch(jf_plan* const* plans, int n, void* ws, s
     if (st != JF_OK) return st;
     st = upload(plans[i], base[i], stream, state_of(plans[i]).lay.buf_off);
     if (st != JF_OK) return st;
-    st = pinned_res_of(plans[i]);  // before the capture: each member's assembly writes its result there
-    if (st != JF_OK) return st;
   }
+  DevState& S0 = state_of(plans[0]);
+  st = batch_res_of(S0, n);  // before the capture: each entry's assembly writes its result there
+  if (st != JF_OK) return st;
   // every small component of every plan in one persistent launch, and one launch for the assembly
   // of all plans that have some
   std::vector<unsigned char> tables(bl.total - bl.items);
@@ -2195,7 +2223,8 @@ extern "C" jf_status jf_fidelity_batch(jf_plan* const* plans, int n, void* ws, s
     fill_lds_tables(plans[i]->prog, L, base[i], items + n_items, lsteps + n_lsteps, n_lsteps);
     n_items += int(L.lds_comps.size());
     n_lsteps += L.lds_steps;
-    if (!has_steps(plans[i]) || !L.lds_comps.empty()) assembles[n_assembles++] = assemble_args(plans[i], base[i]);
+    if (!has_steps(plans[i]) || !L.lds_comps.empty())
+      assembles[n_assembles++] = assemble_args(plans[i], base[i], S0.batch_res.entry(i).dev);
   }
   if (n_assembles) {
     JF_HIP(hipMemcpyAsync(w + bl.items, tables.data(), tables.size(), hipMemcpyHostToDevice, stream));
@@ -2205,7 +2234,6 @@ extern "C" jf_status jf_fidelity_batch(jf_plan* const* plans, int n, void* ws, s
   JF_HIP(hipEventCreate(&ev.a));
   JF_HIP(hipEventCreate(&ev.b));
   hipEvent_t e0 = ev.a, e1 = ev.b;
-  DevState& S0 = state_of(plans[0]);
   // a lane of its own for the persistent launch where the members have only one
   bool used[BATCH_LANES] = {};
   bool large = false;
@@ -2224,8 +2252,9 @@ extern "C" jf_status jf_fidelity_batch(jf_plan* const* plans, int n, void* ws, s
     for (int i = 0; i < n; ++i) {
       const int l = bl.lane[i];
       if ((which >= 0 && which != l) || !has_steps(plans[i])) continue;
-      const jf_status ms = enqueue_program(plans[i], base[i], lane[l], nullptr, true, nullptr, w + bl.lane_bufs[l],
-                                           nullptr, state_of(plans[i]).lay.lds_comps.empty());
+      const jf_status ms =
+          enqueue_program(plans[i], base[i], lane[l], S0.batch_res.entry(i).dev, nullptr, true, nullptr,
+                          w + bl.lane_bufs[l], nullptr, state_of(plans[i]).lay.lds_comps.empty());
       if (ms != JF_OK) return ms;
     }
     return JF_OK;
@@ -2269,7 +2298,10 @@ extern "C" jf_status jf_fidelity_batch(jf_plan* const* plans, int n, void* ws, s
     S0.graph_lanes = lanes;
   }
   auto run = [&]() -> jf_status {
-    for (int i = 0; i < n; ++i) await_result(state_of(plans[i]));
+    for (int i = 0; i < n; ++i) {
+      await_result(S0.batch_res.entry(i));
+      state_of(plans[i]).reruns = 0;
+    }
     JF_HIP(hipEventRecord(e0, stream));
     bool beside = false;
     for (int l = 1; l < BATCH_LANES; ++l) beside = beside || used[l];
@@ -2300,7 +2332,8 @@ extern "C" jf_status jf_fidelity_batch(jf_plan* const* plans, int n, void* ws, s
     return st;
   }
   for (int i = 0; i < n; ++i) {
-    st = finish_pass(plans[i], base[i], stream, &out[i], nullptr, true, w + bl.lane_bufs[bl.lane[i]], true);
+    st = finish_pass(plans[i], base[i], stream, &out[i], nullptr, S0.batch_res.entry(i), w + bl.lane_bufs[bl.lane[i]],
+                     true);
     if (st != JF_OK) return st;
   }
   float ms = 0;
@@ -2334,7 +2367,8 @@ extern "C" void jf_free_plan(jf_plan* p) {
     for (hipEvent_t e : {s->ev0, s->ev1, s->ev_order, s->ev_fork, s->ev_join, s->ev_terms[0], s->ev_terms[1]})
       if (e) hipEventDestroy(e);
     if (s->pinned_sums) hipHostFree(s->pinned_sums);
-    if (s->pinned_res) hipHostFree(s->pinned_res);
+    if (s->res.host) hipHostFree(s->res.host);
+    if (s->batch_res.host) hipHostFree(s->batch_res.host);
     if (s->pinned_terms) hipHostFree(s->pinned_terms);
     {
       std::lock_guard<std::mutex> g(g_upload_mu);

@@ -87,3 +87,22 @@ def test_void_passes_in_a_batch_and_a_decision():
     print("[gpu-test] void pass of a decision", flush=True)
     d = jf.jf_decide_equivalence(p, 1 - fj + 0.01, _workspace(p.info()["workspace_bytes"]))
     assert p.last_pass()["reruns"] == 1 and d["decision"] == 1 and abs(d["fj_lower"] - fj) <= 1e-12
+
+
+def test_entries_of_one_plan_in_a_batch_have_a_result_each():
+    """A plan that stands in a batch twice: each entry's give-up is seen and its pass run again."""
+    import torch
+    inst, flags, fj, _ = _case("one run")
+    for graph_stream in (torch.cuda.Stream(), None):
+        p = jf.plan(inst, 1, "c128", flags=flags)
+        q = jf.plan(gen.random_circuit(8, 220, 3, 1e-3, 0.2, 20), 1, "c128", flags=QUICK)
+        want = jf.jf_fidelity_alg1(q)["fj"]
+        batch = [p, q, p, p]
+        ws = _workspace(jf.jf_batch_workspace(batch))
+        for wait, reruns in ((0, 3), (DEFAULT_WAIT, 0)):
+            assert jf.lib().jf_set_grid_wait(p.ptr, wait) == 0
+            for rep in range(2):
+                print("[gpu-test] a plan three times in a batch, wait", wait, "rep", rep, flush=True)
+                got = [r["fj"] for r in jf.jf_fidelity_batch(batch, ws, graph_stream)]
+                assert (rep or p.last_pass()["reruns"] == reruns) and q.last_pass()["reruns"] == 0
+                assert max(abs(g - w) for g, w in zip(got, (fj, want, fj, fj))) <= 1e-12
