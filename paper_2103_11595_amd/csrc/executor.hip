@@ -881,8 +881,20 @@ jf_status enqueue_steps(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipS
 // steps' shapes.
 std::map<std::vector<long long>, int> g_run_cache;
 
+// The failure word and the barrier flags of the grid runs as they were uploaded: zero.
+jf_status reset_grid(jf_plan* p, unsigned char* ws, hipStream_t stream) {
+  const DevState& S = state_of(p);
+  const DevLayout& L = S.lay;
+  JF_HIP(hipMemcpyAsync(ws + L.fail_off, &S.host_image[L.fail_off], sizeof(unsigned), hipMemcpyHostToDevice, stream));
+  JF_HIP(hipMemcpyAsync(ws + L.flags_off, &S.host_image[L.flags_off],
+                        size_t(L.slice_lanes) * GRID_WGS * GRID_FLAG_STRIDE * sizeof(unsigned), hipMemcpyHostToDevice,
+                        stream));
+  return JF_OK;
+}
+
 // Time steps [first, last) as one launch (a grid run or a block, switched off by `off`) against their
-// own launches (tuned, chains included) and keep the faster.
+// own launches (tuned, chains included) and keep the faster.  A grid run that gave up its barrier has
+// no time (the launches after that do nothing): its steps get their own launches, for this plan alone.
 jf_status tune_joint(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipStream_t stream, size_t c, int lv, int first,
                      int last, char& off, bool block, const std::vector<int>& vv, const void* in, long long base, int reps) {
   const ComponentProgram& cp = p->prog.comps[c];
@@ -918,6 +930,15 @@ jf_status tune_joint(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipStre
     JF_HIP(hipEventRecord(ev.b, stream));
     JF_HIP(hipEventSynchronize(ev.b));
     JF_HIP(hipEventElapsedTime(&ms[mode], ev.a, ev.b));
+    if (mode == 0 && !block) {
+      unsigned failed = 0;
+      JF_HIP(hipMemcpyAsync(&failed, ws + state_of(p).lay.fail_off, sizeof(failed), hipMemcpyDeviceToHost, stream));
+      JF_HIP(hipStreamSynchronize(stream));
+      if (failed) {
+        off = 1;
+        return reset_grid(p, ws, stream);
+      }
+    }
   }
   off = ms[0] <= ms[1] ? 0 : 1;
   std::lock_guard<std::mutex> g(g_tune_mu);
@@ -1573,15 +1594,10 @@ jf_status finish_pass(jf_plan* p, unsigned char* ws, hipStream_t stream, jf_resu
   bool gave_up = false;
   jf_status st = read_results(p, ws, stream, out, terms, at, &gave_up);
   if (st != JF_OK || !gave_up) return st;
-  DevState& S = state_of(p);
-  const DevLayout& L = S.lay;
-  // the failure word and the barrier flags as they were uploaded: zero
-  JF_HIP(hipMemcpyAsync(ws + L.fail_off, &S.host_image[L.fail_off], sizeof(unsigned), hipMemcpyHostToDevice, stream));
-  JF_HIP(hipMemcpyAsync(ws + L.flags_off, &S.host_image[L.flags_off],
-                        size_t(L.slice_lanes) * GRID_WGS * GRID_FLAG_STRIDE * sizeof(unsigned), hipMemcpyHostToDevice,
-                        stream));
+  st = reset_grid(p, ws, stream);
+  if (st != JF_OK) return st;
   await_result(at);
-  ++S.reruns;
+  ++state_of(p).reruns;
   st = enqueue_program(p, ws, stream, at.dev, nullptr, skip_lds, nullptr, bufs, nullptr, true, false);
   if (st != JF_OK) return st;
   st = read_results(p, ws, stream, out, terms, at, &gave_up);

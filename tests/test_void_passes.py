@@ -106,3 +106,21 @@ def test_entries_of_one_plan_in_a_batch_have_a_result_each():
                 got = [r["fj"] for r in jf.jf_fidelity_batch(batch, ws, graph_stream)]
                 assert (rep or p.last_pass()["reruns"] == reruns) and q.last_pass()["reruns"] == 0
                 assert max(abs(g - w) for g, w in zip(got, (fj, want, fj, fj))) <= 1e-12
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+def test_a_run_that_gives_up_while_it_is_timed_is_not_taken(dtype):
+    """Tuning: the launches after a give-up end at once, which must not read as fast, neither for the plan
+    nor for others of its shape."""
+    inst, flags, fj, _ = _case("one run")
+    p = _never_waits(jf.plan(inst, 1, dtype, flags=flags))
+    ws = _workspace(p.info()["workspace_bytes"])
+    print("[gpu-test] tuning without waits", dtype, flush=True)
+    jf.jf_autotune(p, ws)
+    got = jf.jf_fidelity_alg1(p, ws)
+    assert p.last_pass()["reruns"] == 0 and p.last_pass()["grid_launches"] == 0 and abs(got["fj"] - fj) <= TOL[dtype]
+    q = jf.plan(inst, 1, dtype, flags=flags)
+    print("[gpu-test] tuning with waits", dtype, flush=True)
+    jf.jf_autotune(q, ws)
+    got = jf.jf_fidelity_alg1(q, ws)
+    assert q.last_pass()["reruns"] == 0 and q.last_pass()["grid_launches"] > 0 and abs(got["fj"] - fj) <= TOL[dtype]
