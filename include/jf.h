@@ -384,7 +384,9 @@ jf_status jf_set_kernel_variant(jf_plan* plan, int variant);
 /*
  * jf_set_grid_wait -- test aid: the longest wait, in ticks of the device's 100 MHz wall clock, of the
  * barrier between the steps that one launch runs (default 2 s; 0 gives up at once).  A pass whose
- * barrier gives up is run again with one launch per step before the call returns.  Host only.
+ * barrier gives up is run again with one launch per step before the call returns, and the plan's later
+ * passes run that way from the start, until this call, jf_autotune or jf_set_kernel_variant with
+ * JF_KV_AUTO lets the plan try again.  Host only.
  */
 jf_status jf_set_grid_wait(jf_plan* plan, long long ticks);
 

@@ -108,6 +108,9 @@ struct DevState {
   std::vector<std::vector<char>> run_off;
   std::vector<std::vector<char>> block_off;  // the same for blocks
   long long grid_wait = 200000000;          // longest wait of a grid barrier: 2 s of the 100 MHz wall clock
+  // a barrier gave up (the device is held by others): launch by launch from then on, so that the wait
+  // is lost once, until the caller sets the wait, restores the kernel choice or tunes again
+  bool grid_gave_up = false;
   bool validated = false;                   // the program passed validate_program (plans are immutable)
   hipEvent_t ev_order = nullptr, ev0 = nullptr, ev1 = nullptr;
   int grid_launches = 0, lanes = 1, reruns = 0;  // of the last pass (jf_last_pass)
@@ -881,10 +884,13 @@ jf_status enqueue_steps(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipS
 // steps' shapes.
 std::map<std::vector<long long>, int> g_run_cache;
 
-// The failure word and the barrier flags of the grid runs as they were uploaded: zero.
-jf_status reset_grid(jf_plan* p, unsigned char* ws, hipStream_t stream) {
-  const DevState& S = state_of(p);
+// After a give-up: no grid runs from here on, in captured programs neither, and the failure word and
+// the barrier flags as they were uploaded, zero.
+jf_status leave_grid(jf_plan* p, unsigned char* ws, hipStream_t stream) {
+  DevState& S = state_of(p);
   const DevLayout& L = S.lay;
+  S.grid_gave_up = true;
+  S.variant_gen = g_variant_gen.fetch_add(1);
   JF_HIP(hipMemcpyAsync(ws + L.fail_off, &S.host_image[L.fail_off], sizeof(unsigned), hipMemcpyHostToDevice, stream));
   JF_HIP(hipMemcpyAsync(ws + L.flags_off, &S.host_image[L.flags_off],
                         size_t(L.slice_lanes) * GRID_WGS * GRID_FLAG_STRIDE * sizeof(unsigned), hipMemcpyHostToDevice,
@@ -936,7 +942,7 @@ jf_status tune_joint(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipStre
       JF_HIP(hipStreamSynchronize(stream));
       if (failed) {
         off = 1;
-        return reset_grid(p, ws, stream);
+        return leave_grid(p, ws, stream);
       }
     }
   }
@@ -1183,7 +1189,7 @@ jf_status enqueue_level(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipS
     tune->done[c][first] = 2;
     return tune_joint(p, ws, bufs, stream, c, lv, first, last, off, block, vv, in, base, tune->reps);
   };
-  for (size_t q = 0; q < L.run_desc[c].size() && gu && st == JF_OK; ++q)
+  for (size_t q = 0; q < L.run_desc[c].size() && gu && !S.grid_gave_up && st == JF_OK; ++q)
     st = joint(cp.runs[q].first, cp.runs[q].last, S.run_off[c][q], false);
   for (size_t q = 0; q < L.block_desc[c].size() && st == JF_OK; ++q)
     st = joint(cp.blocks[q].first, cp.blocks[q].last, S.block_off[c][q], true);
@@ -1363,7 +1369,7 @@ jf_status enqueue_program(jf_plan* p, unsigned char* ws, hipStream_t stream, dou
                                                   side, S.ev_fork, S.ev_join);
     if (st != JF_OK) return st;
   }
-  grid = grid && L.grid_bytes > 0 && grid_fits_device();
+  grid = grid && L.grid_bytes > 0 && !S.grid_gave_up && grid_fits_device();
   size_t last = 0;  // the last component on this stream
   for (size_t c = 0; c < P.comps.size(); ++c)
     if (!P.comps[c].lds_resident) last = c;
@@ -1587,14 +1593,15 @@ void await_result(const Landing& at) {
 }
 
 // Wait for a pass and read it back; a pass whose grid runs gave up waiting (their workgroups were not
-// resident together: the device was held by others) is run again with a launch per step.  bufs and
+// resident together: the device was held by others) is run again with a launch per step, and so are
+// the plan's later ones.  bufs and
 // skip_lds as in enqueue_program (a batch member).
 jf_status finish_pass(jf_plan* p, unsigned char* ws, hipStream_t stream, jf_result* out, double* terms,
                       const Landing& at, unsigned char* bufs = nullptr, bool skip_lds = false) {
   bool gave_up = false;
   jf_status st = read_results(p, ws, stream, out, terms, at, &gave_up);
   if (st != JF_OK || !gave_up) return st;
-  st = reset_grid(p, ws, stream);
+  st = leave_grid(p, ws, stream);
   if (st != JF_OK) return st;
   await_result(at);
   ++state_of(p).reruns;
@@ -1876,6 +1883,7 @@ extern "C" jf_status jf_autotune(jf_plan* p, void* ws, size_t ws_bytes, void* st
   if (st != JF_OK) return st;
   st = upload(p, ws, stream);
   if (st != JF_OK) return st;
+  state_of(p).grid_gave_up = false;
   Tune tune;
   tune.reps = reps > 0 ? reps : 3;
   tune.done.resize(p->prog.comps.size());
@@ -1906,6 +1914,7 @@ extern "C" jf_status jf_set_grid_wait(jf_plan* p, long long ticks) {
   }
   DevState& S = state_of(p);
   S.grid_wait = ticks;
+  S.grid_gave_up = false;
   S.variant_gen = g_variant_gen.fetch_add(1);  // captured launches hold the old limit
   return JF_OK;
 }
@@ -1923,6 +1932,7 @@ extern "C" jf_status jf_set_kernel_variant(jf_plan* p, int variant) {
     }
   // a forced kernel runs every step on its own, except the Gauss-form kernels, whose products the
   // chains repeat; AUTO brings the chains back
+  if (variant == KV_AUTO) S.grid_gave_up = false;
   const bool keep = variant == KV_AUTO || variant == KV_GAUSS_256 || variant == KV_GAUSS_512;
   for (auto& v : S.chain_off) std::fill(v.begin(), v.end(), char(!keep));
   for (auto* off : {&S.run_off, &S.block_off})

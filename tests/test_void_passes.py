@@ -124,3 +124,30 @@ def test_a_run_that_gives_up_while_it_is_timed_is_not_taken(dtype):
     jf.jf_autotune(q, ws)
     got = jf.jf_fidelity_alg1(q, ws)
     assert q.last_pass()["reruns"] == 0 and q.last_pass()["grid_launches"] > 0 and abs(got["fj"] - fj) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_a_barrier_that_gave_up_is_not_waited_for_again(name):
+    """After a give-up the plan's passes go out launch by launch, until it is let try again."""
+    import torch
+    inst, flags, fj, _ = _case(name)
+    side = torch.cuda.Stream()
+    for way in ("eager", "graph", "scratch", "batch", "batch, null stream"):
+        p = jf.plan(inst, 1, "c128", flags=flags | (jf.JF_FLAG_GRAPH if way == "graph" else 0))
+        ws = _workspace(jf.jf_batch_workspace([p]))
+        run = {"eager": lambda: jf.jf_fidelity_alg1(p, ws), "graph": lambda: jf.jf_fidelity_alg1(p, ws, side),
+               "scratch": lambda: jf.jf_fidelity_noalloc(p), "batch": lambda: jf.jf_fidelity_batch([p], ws, side)[0],
+               "batch, null stream": lambda: jf.jf_fidelity_batch([p], ws, None)[0]}[way]
+        for again in ("wait", "kernel choice"):
+            _never_waits(p)
+            for reruns in (1, 0, 0):
+                print("[gpu-test] launch by launch after a give-up", name, way, "reruns", reruns, flush=True)
+                assert abs(run()["fj"] - fj) <= 1e-12
+                assert p.last_pass()["reruns"] == reruns and p.last_pass()["grid_launches"] == 0
+            if again == "kernel choice":  # tries, and gives up at the wait of 0
+                jf.jf_set_kernel_variant(p, jf.KV_AUTO)
+                assert abs(run()["fj"] - fj) <= 1e-12 and p.last_pass()["reruns"] == 1
+            assert jf.lib().jf_set_grid_wait(p.ptr, DEFAULT_WAIT) == 0
+            print("[gpu-test] and with its wait again", flush=True)
+            assert abs(run()["fj"] - fj) <= 1e-12
+            assert p.last_pass()["reruns"] == 0 and p.last_pass()["grid_launches"] > 0
