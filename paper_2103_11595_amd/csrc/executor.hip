@@ -2362,6 +2362,8 @@ extern "C" jf_status jf_fidelity_batch(jf_plan* const* plans, int n, void* ws, s
                      true);
     if (st != JF_OK) return st;
   }
+  const int lanes_used = int(std::count(used, used + BATCH_LANES, true));
+  for (int i = 0; i < n; ++i) state_of(plans[i]).lanes = lanes_used;
   float ms = 0;
   JF_HIP(hipEventElapsedTime(&ms, e0, e1));
   for (int i = 0; i < n; ++i) out[i].seconds = ms * 1e-3;

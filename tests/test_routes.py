@@ -1,0 +1,81 @@
+"""GPU tests that passes run as the library says: small steps in launches of their own kind, slices and the
+members of a batch in lanes beside each other, and neither where it is switched off or cannot be.
+Results against the dense oracle or the emulated program within the bars of the forms (complex128 1e-12,
+complex64 1e-6)."""
+import numpy as np
+import pytest
+
+from oracle import dense
+from paper_2103_11595_amd import instances as gen
+from paper_2103_11595_amd import jf
+
+pytestmark = pytest.mark.gpu
+TOL = {"c128": 1e-12, "c64": 1e-6}
+QUICK = jf.JF_FLAG_EFFORT(1)  # little path search
+
+
+def _inst(seed):
+    return gen.random_circuit(8, 220, 3, 1e-3, 0.2, seed)
+
+
+def _same(p, got, fj, dtype, reruns=0):
+    assert abs(got["fj"] - fj) <= TOL[dtype] and p.last_pass()["reruns"] == reruns
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+def test_small_steps_run_several_to_a_launch(dtype):
+    import torch
+    inst = _inst(22)
+    fj = dense.fidelity_alg1(inst)["fj"]
+    side = torch.cuda.Stream()
+    p = jf.plan(inst, 1, dtype, flags=QUICK)
+    print("[gpu-test] routes of small steps", dtype, flush=True)
+    _same(p, jf.jf_fidelity_alg1(p), fj, dtype)
+    runs = p.last_pass()["grid_launches"]
+    assert runs > 0
+    _same(p, jf.jf_fidelity_noalloc(p), fj, dtype)
+    assert p.last_pass()["grid_launches"] == runs
+    ws = jf.workspace(jf.jf_batch_workspace([p]))
+    for stream in (side, None):
+        _same(p, jf.jf_fidelity_batch([p], ws, stream)[0], fj, dtype)
+        assert p.last_pass()["grid_launches"] == runs
+    g = jf.plan(inst, 1, dtype, flags=QUICK | jf.JF_FLAG_GRAPH)
+    ws = jf.workspace(g.info()["workspace_bytes"])
+    for _ in range(2):
+        _same(g, jf.jf_fidelity_alg1(g, ws, side), fj, dtype)
+        assert g.last_pass()["grid_launches"] == runs
+    q = jf.plan(inst, 1, dtype, flags=QUICK | jf.JF_FLAG_NO_CHAIN)
+    _same(q, jf.jf_fidelity_alg1(q), fj, dtype)
+    assert q.last_pass()["grid_launches"] == 0
+    jf.jf_set_kernel_variant(p, jf.KV_FMA)
+    _same(p, jf.jf_fidelity_alg1(p), fj, dtype)
+    assert p.last_pass()["grid_launches"] == 0
+    jf.jf_set_kernel_variant(p, jf.KV_AUTO)
+    _same(p, jf.jf_fidelity_alg1(p), fj, dtype)
+    assert p.last_pass()["grid_launches"] == runs
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+def test_slices_and_members_run_in_lanes(dtype):
+    import torch
+    inst = gen.random_circuit(8, 220, 6, 0.01, 0.3, 21)
+    cap = int(jf.plan(inst, 1, dtype, flags=QUICK).info()["max_log2_intermediate"]) - 2
+    p = jf.plan(inst, 1, dtype, max_log2=cap, flags=QUICK)
+    assert p.stats()["n_sliced_sites"] > 0 and p.stats()["n_sliced_wires"] == 0
+    want = np.sum(np.abs(p.emulate()) ** 2)
+    size = p.info()["workspace_bytes"]
+    ws = jf.workspace(size)
+    print("[gpu-test] routes of slices", dtype, flush=True)
+    for w, lanes in ((ws, 4), (ws[:size - 256], 1)):  # four Kraus operators a site
+        _same(p, jf.jf_fidelity_alg1(p, w), want, dtype)
+        assert p.last_pass()["lanes"] == lanes
+    assert jf.lib().jf_set_grid_wait(p.ptr, 0) == 0  # every lane's barriers give up
+    _same(p, jf.jf_fidelity_alg1(p, ws), want, dtype, reruns=1)
+    plans = [jf.plan(_inst(seed), 1, dtype, flags=QUICK) for seed in (20, 22, 23)]
+    fj = [jf.jf_fidelity_alg1(q)["fj"] for q in plans]
+    ws = jf.workspace(jf.jf_batch_workspace(plans))
+    for stream in (torch.cuda.Stream(), None):
+        print("[gpu-test] routes of a batch", dtype, flush=True)
+        for q, f, r in zip(plans, fj, jf.jf_fidelity_batch(plans, ws, stream)):
+            _same(q, r, f, dtype)
+            assert q.last_pass()["lanes"] > 1 and q.last_pass()["grid_launches"] > 0
