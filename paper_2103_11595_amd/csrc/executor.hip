@@ -51,13 +51,15 @@ struct DevLayout {
   int slice_lanes = 1;
   size_t lane_off = 0, lane_stride = 0, lanes_total = 0;
   size_t grid_bytes = 0; // bytes of the workspace that only the grid runs and the blocks use
+  bool grid = false;     // some run has a table
   std::vector<size_t> leaf_off;                           // per component with sliced wires: its leaf buffer
   std::vector<int> lds_comps;                             // components run by the persistent kernel
   int lds_steps = 0;
   std::vector<std::vector<size_t>> step_desc;             // per component, per step: descriptor offset
   std::vector<std::vector<size_t>> chain_desc;            // per component, per chain: descriptor offset
   std::vector<std::vector<size_t>> block_desc;            // per component, per block
-  std::vector<std::vector<size_t>> run_desc;              // per component, per grid run: its steps' GridSteps
+  std::vector<std::vector<size_t>> run_desc;              // per component, per grid run: its steps' GridSteps,
+                                                          // or kNoTable
   std::vector<std::vector<std::vector<size_t>>> step_b;   // per component, step, variant: B offset
   std::vector<std::vector<size_t>> level_buf;             // per component: 2 buffers per level, offsets in
                                                           // the buffer region [buf_off, total)
@@ -323,9 +325,11 @@ void balanced_round(const std::vector<cd>& M, std::vector<float>& out) {
     }
 }
 
-// The most bytes of a workspace that grid runs may add (the no-allocation scratch holds them beside
-// JF_NOALLOC_BYTES).
-constexpr size_t kGridTableBytes = 1 << 20;
+// The most bytes of a workspace that grid runs and blocks may add (the no-allocation scratch holds them
+// beside JF_NOALLOC_BYTES): the tables of 3600 small steps.  A plan with more keeps its blocks and its
+// longest runs, and the other steps get a launch each.
+constexpr size_t kGridTableBytes = 4 << 20;
+constexpr size_t kNoTable = ~size_t(0);  // the run has no table: a launch per step
 
 // The device descriptors of a grid run: where each step's tensors are (a step whose tensors hold at
 // most 2^GRID_LOCAL elements runs in every workgroup's LDS; the last step of a run that is not the
@@ -472,45 +476,41 @@ void build_layout(const Program& P, DevState& S) {
   L.ctr_off = off;
   L.fail_off = off + 128;
   off += 256;
-  // grid runs: descriptors and barrier flags; blocks: descriptors.  At most kGridTableBytes (else the
-  // plan runs without)
+  // blocks: descriptors; grid runs: barrier flags and descriptors, the longest runs first
   L.run_desc.resize(P.comps.size());
   S.run_off.resize(P.comps.size());
   L.block_desc.resize(P.comps.size());
   S.block_off.resize(P.comps.size());
   L.slice_lanes = slice_lanes_of(P);
   const size_t flag_bytes = size_t(L.slice_lanes) * GRID_WGS * GRID_FLAG_STRIDE * sizeof(unsigned);
-  size_t table = flag_bytes;
-  bool any_run = false;
-  for (auto& cp : P.comps)
-    if (!cp.lds_resident)
-      for (const GridRun& r : cp.runs) {
-        table += align256(size_t(r.last - r.first) * sizeof(GridStep));
-        any_run = true;
-      }
-  for (auto& cp : P.comps)
-    if (!cp.lds_resident) {
-      table += cp.blocks.size() * align256(sizeof(BlockDesc));
-      any_run = any_run || !cp.blocks.empty();
+  const size_t table_end = off + kGridTableBytes;
+  const size_t table_first = off;
+  std::vector<std::pair<int, std::pair<size_t, size_t>>> order;  // -length, component, run
+  for (size_t c = 0; c < P.comps.size(); ++c) {
+    const ComponentProgram& cp = P.comps[c];
+    if (cp.lds_resident) continue;
+    for (size_t q = 0; q < cp.blocks.size() && off + align256(sizeof(BlockDesc)) <= table_end; ++q) {
+      L.block_desc[c].push_back(off);
+      off += align256(sizeof(BlockDesc));
     }
-  if (any_run && table <= kGridTableBytes) {
-    L.grid_bytes = table;
+    S.block_off[c].assign(L.block_desc[c].size(), 0);
+    L.run_desc[c].assign(cp.runs.size(), kNoTable);
+    S.run_off[c].assign(cp.runs.size(), 0);
+    for (size_t q = 0; q < cp.runs.size(); ++q) order.push_back({cp.runs[q].first - cp.runs[q].last, {c, q}});
+  }
+  std::sort(order.begin(), order.end());
+  if (!order.empty() && off + flag_bytes <= table_end) {
     L.flags_off = off;
     off += flag_bytes;
-    for (size_t c = 0; c < P.comps.size(); ++c) {
-      if (P.comps[c].lds_resident) continue;
-      S.run_off[c].assign(P.comps[c].runs.size(), 0);
-      for (const GridRun& r : P.comps[c].runs) {
-        L.run_desc[c].push_back(off);
-        off += align256(size_t(r.last - r.first) * sizeof(GridStep));
-      }
-      S.block_off[c].assign(P.comps[c].blocks.size(), 0);
-      for (size_t q = 0; q < P.comps[c].blocks.size(); ++q) {
-        L.block_desc[c].push_back(off);
-        off += align256(sizeof(BlockDesc));
-      }
+    for (const auto& o : order) {
+      const size_t bytes = align256(size_t(-o.first) * sizeof(GridStep));
+      if (off + bytes > table_end) break;
+      L.run_desc[o.second.first][o.second.second] = off;
+      off += bytes;
+      L.grid = true;
     }
   }
+  L.grid_bytes = off - table_first;
   L.image_end = off;
   L.out_off = off;
   long long outn = 0;
@@ -653,6 +653,7 @@ void build_layout(const Program& P, DevState& S) {
     }
   for (size_t c = 0; c < P.comps.size(); ++c)
     for (size_t q = 0; q < L.run_desc[c].size(); ++q) {
+      if (L.run_desc[c][q] == kNoTable) continue;
       const std::vector<GridStep> d = grid_descriptors(P.comps[c], P.comps[c].runs[q]);
       std::memcpy(&S.host_image[L.run_desc[c][q]], d.data(), d.size() * sizeof(GridStep));
     }
@@ -968,7 +969,7 @@ jf_status enqueue_steps(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipS
     const Step& st = cp.steps[si];
     if (gu) {
       const int q = run_starting_at(cp, si);
-      if (q >= 0 && q < (int)L.run_desc[c].size() && !S.run_off[c][q]) {
+      if (q >= 0 && L.run_desc[c][q] != kNoTable && !S.run_off[c][q]) {
         const GridRun& run = cp.runs[q];
         GridArgs a = {};
         a.steps = reinterpret_cast<const GridStep*>(ws + L.run_desc[c][q]);
@@ -1190,7 +1191,7 @@ jf_status enqueue_level(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipS
     return tune_joint(p, ws, bufs, stream, c, lv, first, last, off, block, vv, in, base, tune->reps);
   };
   for (size_t q = 0; q < L.run_desc[c].size() && gu && !S.grid_gave_up && st == JF_OK; ++q)
-    st = joint(cp.runs[q].first, cp.runs[q].last, S.run_off[c][q], false);
+    if (L.run_desc[c][q] != kNoTable) st = joint(cp.runs[q].first, cp.runs[q].last, S.run_off[c][q], false);
   for (size_t q = 0; q < L.block_desc[c].size() && st == JF_OK; ++q)
     st = joint(cp.blocks[q].first, cp.blocks[q].last, S.block_off[c][q], true);
   return st;
@@ -1369,7 +1370,7 @@ jf_status enqueue_program(jf_plan* p, unsigned char* ws, hipStream_t stream, dou
                                                   side, S.ev_fork, S.ev_join);
     if (st != JF_OK) return st;
   }
-  grid = grid && L.grid_bytes > 0 && !S.grid_gave_up && grid_fits_device();
+  grid = grid && L.grid && !S.grid_gave_up && grid_fits_device();
   size_t last = 0;  // the last component on this stream
   for (size_t c = 0; c < P.comps.size(); ++c)
     if (!P.comps[c].lds_resident) last = c;

@@ -79,3 +79,19 @@ def test_slices_and_members_run_in_lanes(dtype):
         for q, f, r in zip(plans, fj, jf.jf_fidelity_batch(plans, ws, stream)):
             _same(q, r, f, dtype)
             assert q.last_pass()["lanes"] > 1 and q.last_pass()["grid_launches"] > 0
+
+
+@pytest.mark.parametrize("gates, runs", [(600, (20, 40)), (2400, (60, 80))])
+def test_long_programs_keep_their_runs_of_small_steps(gates, runs):
+    """Programs of 1200 and of 4800 small steps: all of them in runs of up to 48, and as many as the tables
+    have room for (3600)."""
+    inst = gen.random_circuit(6, gates, 2, 1e-3, 0.2, 18)
+    ref = dense.fidelity_alg1(inst, want_terms=True)
+    terms = np.array([ref["terms"][k] for k in sorted(ref["terms"])])
+    p = jf.plan(inst, 1, "c128", flags=QUICK | jf.JF_FLAG_NO_FUSE | jf.JF_FLAG_NO_CANCEL)
+    assert p.stats()["n_steps"] >= 2 * gates
+    for run in (jf.jf_fidelity_alg1, jf.jf_fidelity_noalloc):
+        print("[gpu-test] a long program", gates, run.__name__, flush=True)
+        got = run(p, want_terms=True)
+        assert np.max(np.abs(got["terms"] - terms)) <= 1e-12 and p.last_pass()["reruns"] == 0
+        assert runs[0] <= p.last_pass()["grid_launches"] <= runs[1]
