@@ -144,8 +144,10 @@ int first_sliced(const ComponentProgram& cp) {
 }
 
 // The lanes of a plan's slices: 1 where nothing is sliced, where leaves add into one output (sliced
-// wires), and where a lane's level buffers are large enough to fill the device.
+// wires), where a lane's level buffers are large enough to fill the device, and in captured plans (a
+// graph submits its branches one after another).
 int slice_lanes_of(const Program& P) {
+  if (P.opt.flags & JF_FLAG_GRAPH) return 1;
   int lanes = 1;
   for (const ComponentProgram& cp : P.comps) {
     if (cp.lds_resident) continue;
@@ -1625,8 +1627,7 @@ jf_status run_one(jf_plan* p, void* ws, size_t ws_bytes, hipStream_t stream, jf_
   if (st != JF_OK) return st;
   DevState& S = state_of(p);
   const bool graph = (p->prog.opt.flags & JF_FLAG_GRAPH) != 0;
-  // a graph keeps one lane: it submits its branches one after another
-  const int lanes = !graph && ws_bytes >= S.lay.lanes_total ? S.lay.slice_lanes : 1;
+  const int lanes = ws_bytes >= S.lay.lanes_total ? S.lay.slice_lanes : 1;
   st = upload(p, ws, stream, lanes > 1 ? S.lay.lanes_total : 0);
   if (st != JF_OK) return st;
   st = pinned_res_of(p);  // before any enqueue or capture: the assembly writes the result there
