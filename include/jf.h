@@ -398,6 +398,8 @@ typedef struct {
   int lanes;         /* lanes beside each other of its slices, or of the batch that it was last in */
   int reruns;        /* times that the call ran the plan's pass again with one launch per step, after a
                         barrier gave up (a plan stands in a batch more than once: of all its entries) */
+  int joint_timings; /* launches of several steps that the last jf_autotune timed (the decisions on the
+                        others were known) */
 } jf_pass;
 jf_status jf_last_pass(jf_plan* plan, jf_pass* out);
 

@@ -115,7 +115,7 @@ struct DevState {
   bool grid_gave_up = false;
   bool validated = false;                   // the program passed validate_program (plans are immutable)
   hipEvent_t ev_order = nullptr, ev0 = nullptr, ev1 = nullptr;
-  int grid_launches = 0, lanes = 1, reruns = 0;  // of the last pass (jf_last_pass)
+  int grid_launches = 0, lanes = 1, reruns = 0, joint_timings = 0;  // of the last pass (jf_last_pass)
   // pinned host landing area of the component sums (4 doubles each): a pageable destination
   // costs the runtime a staging copy on every call, which small programs feel
   double* pinned_sums = nullptr;
@@ -883,8 +883,9 @@ jf_status enqueue_steps(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipS
                         int from, int to, const std::vector<int>& vv, const void* cur, long long base, const void** end,
                         Prof* prof, Tune* tune, GridUse* gu);
 
-// Process-wide cache of the decisions on grid runs and blocks (1 = launch by launch), keyed by the
-// steps' shapes.
+// Process-wide cache of the decisions on grid runs and blocks (1 = launch by launch), keyed by what
+// either way runs: the steps' shapes, the chains they would run in, and a block's tile (its places in
+// memory decide how much of a line a tile takes).
 std::map<std::vector<long long>, int> g_run_cache;
 
 // After a give-up: no grid runs from here on, in captured programs neither, and the failure word and
@@ -901,18 +902,31 @@ jf_status leave_grid(jf_plan* p, unsigned char* ws, hipStream_t stream) {
   return JF_OK;
 }
 
-// Time steps [first, last) as one launch (a grid run or a block, switched off by `off`) against their
+// Time steps [first, last) as one launch (a grid run, or the block blk, switched off by `off`) against their
 // own launches (tuned, chains included) and keep the faster.  A grid run that gave up its barrier has
 // no time (the launches after that do nothing): its steps get their own launches, for this plan alone.
 jf_status tune_joint(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipStream_t stream, size_t c, int lv, int first,
-                     int last, char& off, bool block, const std::vector<int>& vv, const void* in, long long base, int reps) {
+                     int last, char& off, const Block* blk, const std::vector<int>& vv, const void* in, long long base,
+                     int reps) {
   const ComponentProgram& cp = p->prog.comps[c];
-  std::vector<long long> key = {block ? 1LL : 0LL};
+  DevState& S = state_of(p);
+  std::vector<long long> key = {blk ? 1LL : 0LL};
+  if (blk) {
+    key.insert(key.end(), {(long long)blk->T, blk->nTiles, (long long)blk->Pin.size()});
+    key.insert(key.end(), blk->Pin.begin(), blk->Pin.end());
+    key.insert(key.end(), blk->Pout.begin(), blk->Pout.end());
+  }
   for (int s = first; s < last; ++s) {
     const Step& st = cp.steps[s];
     for (long long v : {(long long)st.kS, (long long)st.kN, (long long)st.rA, (long long)st.rC, (long long)mode_of(st),
-                        (long long)st.chain >= 0 ? 1LL : 0LL, (long long)st.final_step})
+                        (long long)st.final_step})
       key.push_back(v);
+    if (st.chain >= 0 && !S.chain_off[c][st.chain]) {  // relative extents, never 0 apart
+      const Chain& ch = cp.chains[st.chain];
+      key.insert(key.end(), {(long long)(ch.first - s), (long long)(ch.last - s)});
+    } else {
+      key.insert(key.end(), {0LL, 0LL});
+    }
   }
   {
     std::lock_guard<std::mutex> g(g_tune_mu);
@@ -933,15 +947,15 @@ jf_status tune_joint(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipStre
     for (int r = 0; r <= reps; ++r) {  // the first is the warm-up
       if (r == 1) JF_HIP(hipEventRecord(ev.a, stream));
       const jf_status st = enqueue_steps(p, ws, bufs, stream, c, lv, first, last, vv, in, base, &end, nullptr, nullptr,
-                                         block ? nullptr : &gu);
+                                         blk ? nullptr : &gu);
       if (st != JF_OK) return st;
     }
     JF_HIP(hipEventRecord(ev.b, stream));
     JF_HIP(hipEventSynchronize(ev.b));
     JF_HIP(hipEventElapsedTime(&ms[mode], ev.a, ev.b));
-    if (mode == 0 && !block) {
+    if (mode == 0 && !blk) {
       unsigned failed = 0;
-      JF_HIP(hipMemcpyAsync(&failed, ws + state_of(p).lay.fail_off, sizeof(failed), hipMemcpyDeviceToHost, stream));
+      JF_HIP(hipMemcpyAsync(&failed, ws + S.lay.fail_off, sizeof(failed), hipMemcpyDeviceToHost, stream));
       JF_HIP(hipStreamSynchronize(stream));
       if (failed) {
         off = 1;
@@ -950,6 +964,7 @@ jf_status tune_joint(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipStre
     }
   }
   off = ms[0] <= ms[1] ? 0 : 1;
+  ++S.joint_timings;
   std::lock_guard<std::mutex> g(g_tune_mu);
   g_run_cache[key] = off;
   return JF_OK;
@@ -1184,18 +1199,18 @@ jf_status enqueue_level(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipS
   jf_status st = enqueue_steps(p, ws, bufs, stream, c, lv, lev.first, lev.last, vv, cur, base, end, prof, tune,
                                prof || tune ? nullptr : gu);
   if (st != JF_OK || !tune) return st;
-  auto joint = [&](int first, int last, char& off, bool block) {
+  auto joint = [&](int first, int last, char& off, const Block* blk) {
     if (first < lev.first || last > lev.last || tune->done[c][first] == 2) return JF_OK;
     // the input: the level's, or what an earlier step of the level left in a level buffer (the data
     // is garbage by now, which the timing does not see)
     const void* in = first == lev.first ? start : bufs + L.level_buf[c][2 * lv + 1];
     tune->done[c][first] = 2;
-    return tune_joint(p, ws, bufs, stream, c, lv, first, last, off, block, vv, in, base, tune->reps);
+    return tune_joint(p, ws, bufs, stream, c, lv, first, last, off, blk, vv, in, base, tune->reps);
   };
   for (size_t q = 0; q < L.run_desc[c].size() && gu && !S.grid_gave_up && st == JF_OK; ++q)
-    if (L.run_desc[c][q] != kNoTable) st = joint(cp.runs[q].first, cp.runs[q].last, S.run_off[c][q], false);
+    if (L.run_desc[c][q] != kNoTable) st = joint(cp.runs[q].first, cp.runs[q].last, S.run_off[c][q], nullptr);
   for (size_t q = 0; q < L.block_desc[c].size() && st == JF_OK; ++q)
-    st = joint(cp.blocks[q].first, cp.blocks[q].last, S.block_off[c][q], true);
+    st = joint(cp.blocks[q].first, cp.blocks[q].last, S.block_off[c][q], &cp.blocks[q]);
   return st;
 }
 
@@ -1886,6 +1901,7 @@ extern "C" jf_status jf_autotune(jf_plan* p, void* ws, size_t ws_bytes, void* st
   st = upload(p, ws, stream);
   if (st != JF_OK) return st;
   state_of(p).grid_gave_up = false;
+  state_of(p).joint_timings = 0;
   Tune tune;
   tune.reps = reps > 0 ? reps : 3;
   tune.done.resize(p->prog.comps.size());
@@ -1906,6 +1922,7 @@ extern "C" jf_status jf_last_pass(jf_plan* p, jf_pass* out) {
   out->grid_launches = S.grid_launches;
   out->lanes = S.lanes;
   out->reruns = S.reruns;
+  out->joint_timings = S.joint_timings;
   return JF_OK;
 }
 

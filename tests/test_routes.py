@@ -95,3 +95,27 @@ def test_long_programs_keep_their_runs_of_small_steps(gates, runs):
         got = run(p, want_terms=True)
         assert np.max(np.abs(got["terms"] - terms)) <= 1e-12 and p.last_pass()["reruns"] == 0
         assert runs[0] <= p.last_pass()["grid_launches"] <= runs[1]
+
+
+@pytest.mark.parametrize("dtype", ["c128"])  # tensors of 2^16 elements, tiles of 2^12 at most
+def test_blocks_of_other_tiles_are_timed_apart(dtype):
+    """Tuning: blocks of the same step sizes whose legs lie elsewhere are other launches."""
+    inst = gen.random_circuit(8, 500, 2, 1e-3, 0.2, 19)
+    fj = dense.fidelity_alg1(inst)["fj"]
+    flags = QUICK | jf.JF_FLAG_NO_FUSE | jf.JF_FLAG_NO_CANCEL | jf.JF_FLAG_SMALL_BLOCKS
+    p = jf.plan(inst, 1, dtype, flags=flags)
+    ws = jf.workspace(p.info()["workspace_bytes"])
+    steps, sizes, at = p.describe(), set(), 0
+    for launch in jf.jf_profile_steps(p, ws):
+        own = steps[at:at + launch["steps"]]
+        at += launch["steps"]
+        if launch["variant"] == jf.KV_BLOCK:
+            sizes.add(tuple((s["kS"], s["kN"], s["rA"], s["rC"], s["chain"] >= 0) for s in own))
+    assert at == len(steps)
+    print("[gpu-test] tuning blocks", dtype, "sizes", len(sizes), flush=True)
+    jf.jf_autotune(p, ws, reps=1)
+    timed = p.last_pass()["joint_timings"]
+    assert timed > len(sizes) > 0
+    jf.jf_autotune(p, ws, reps=1)
+    assert p.last_pass()["joint_timings"] == 0  # known by now
+    _same(p, jf.jf_fidelity_alg1(p, ws), fj, dtype)
