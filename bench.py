@@ -496,9 +496,10 @@ def main():
         for _ in range(args.warmup if main else 1):
             jf.jf_fidelity_alg1(p, ws, stream)
         r, sec = timed(steps)
+        runs = p.last_pass()
         prof = jf.jf_profile_run(p, ws, stream)
         per_step = jf.jf_profile_steps(p, ws, stream)
-        res[dt] = {"plan": p, "info": info, "r": r, "sec": sec, "steps": steps, "prof": prof, "per_step": per_step,
+        res[dt] = {"plan": p, "info": info, "r": r, "sec": sec, "steps": steps, "prof": prof, "per_step": per_step, "runs": runs,
                    "untuned_sec": untuned, "tune_s": None if args.no_autotune else tune_s}
         del ws
 
@@ -603,6 +604,9 @@ def main():
                        "max_log2_intermediate": v["info"]["max_log2_intermediate"],
                        "path_flops": v["info"]["path_flops"], "path_bytes": v["info"]["path_bytes"],
                        "launches": v["prof"]["launches"], "kernel_ms": v["prof"]["kernel_ms"],
+                       # small steps that a pass runs several to a launch: the launches counted and listed
+                       # here are of a program run that launches each of them by itself
+                       "runs_of_small_steps": {"launches": v["runs"]["grid_launches"], "steps": v["runs"]["grid_steps"]},
                        "untuned_ms_per_step": v["untuned_sec"] * 1e3 if v["untuned_sec"] else None,
                        "autotune_s": v["tune_s"]}
                   for dt, v in res.items()},

@@ -395,6 +395,7 @@ jf_status jf_set_grid_wait(jf_plan* plan, long long ticks);
  */
 typedef struct {
   int grid_launches; /* launches that run several small steps, in the program last enqueued or captured */
+  int grid_steps;    /* and the steps that they run */
   int lanes;         /* lanes beside each other of its slices, or of the batch that it was last in */
   int reruns;        /* times that the call ran the plan's pass again with one launch per step, after a
                         barrier gave up (a plan stands in a batch more than once: of all its entries) */

@@ -115,7 +115,7 @@ struct DevState {
   bool grid_gave_up = false;
   bool validated = false;                   // the program passed validate_program (plans are immutable)
   hipEvent_t ev_order = nullptr, ev0 = nullptr, ev1 = nullptr;
-  int grid_launches = 0, lanes = 1, reruns = 0, joint_timings = 0;  // of the last pass (jf_last_pass)
+  int grid_launches = 0, grid_steps = 0, lanes = 1, reruns = 0, joint_timings = 0;  // (jf_last_pass)
   // pinned host landing area of the component sums (4 doubles each): a pageable destination
   // costs the runtime a staging copy on every call, which small programs feel
   double* pinned_sums = nullptr;
@@ -1016,6 +1016,7 @@ jf_status enqueue_steps(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipS
         }
         JF_HIP(launch_grid(a, stream));
         ++S.grid_launches;
+        S.grid_steps += a.n;
         if (fs.final_step) {
           if (cp.accumulate) JF_HIP(launch_accumulate(out + size_t(base) * 16, a.out, cp.leaf_len, stream));
           cur = a.out;
@@ -1368,7 +1369,7 @@ jf_status enqueue_program(jf_plan* p, unsigned char* ws, hipStream_t stream, dou
   DevState& S = state_of(p);
   const DevLayout& L = S.lay;
   if (!bufs) bufs = ws + L.buf_off;
-  S.grid_launches = 0;
+  S.grid_launches = S.grid_steps = 0;
   S.lanes = lanes;
   const bool lds = !skip_lds && !L.lds_comps.empty();
   if (lds && assemble && L.lds_comps.size() == P.comps.size()) {
@@ -1920,6 +1921,7 @@ extern "C" jf_status jf_last_pass(jf_plan* p, jf_pass* out) {
   }
   const DevState& S = state_of(p);
   out->grid_launches = S.grid_launches;
+  out->grid_steps = S.grid_steps;
   out->lanes = S.lanes;
   out->reruns = S.reruns;
   out->joint_timings = S.joint_timings;

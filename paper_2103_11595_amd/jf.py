@@ -102,7 +102,7 @@ class jf_decision(C.Structure):
 
 
 class jf_pass(C.Structure):
-    _fields_ = [("grid_launches", C.c_int), ("lanes", C.c_int), ("reruns", C.c_int),
+    _fields_ = [("grid_launches", C.c_int), ("grid_steps", C.c_int), ("lanes", C.c_int), ("reruns", C.c_int),
                 ("joint_timings", C.c_int)]
 
 

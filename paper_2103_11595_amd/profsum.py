@@ -7,9 +7,10 @@ files only, runs nothing on the GPU).
         --out profiles/Y.md --json profiles/Z.json --command "..."
 
 ``trace`` reads a ``--kernel-trace`` run of bench.py and reports, per kernel name, the launches of
-the last clean program runs (the passes after the autotuner, identified from the end of the
-trace: every program run has the same number of step launches, taken from bench.py's JSON line),
-and their average duration next to the live HIP-event average bench.py printed.
+the last passes (before the two program runs that bench.py ends with, which launch every small step
+by itself to time it; the passes run small steps several to a launch: the period of the launch
+sequence there, as in ``passes``), and the dominant kernel's average duration next to the live
+HIP-event average bench.py printed.
 
 ``passes`` reads a ``--kernel-trace`` run of any bench.py workload whose passes repeat one fixed
 launch sequence of the library's kernels (graph replays, eager runs of one plan): the period is
@@ -39,7 +40,7 @@ import json
 import os
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-STEP_PREFIXES = ("k_absorb", "k_chain")
+STEP_PREFIXES = ("k_absorb", "k_chain", "k_block")
 
 
 def kernels_sha() -> str:
@@ -56,27 +57,40 @@ def bench_line(log: str) -> dict:
 
 def short(name: str) -> str:
     return (name.replace("void ", "").split("(jf::StepDesc")[0].split("(HIP_vector_type")[0].split("(ChainDesc")[0]
-            .split("(jf::ChainDesc")[0].replace("jf::", ""))
+            .split("(jf::ChainDesc")[0].split("(jf::BlockDesc")[0].split("(jf::GridArgs")[0].replace("jf::", ""))
 
 
 def is_step(name: str) -> bool:
     return any(p in name for p in STEP_PREFIXES)
 
 
-def last_passes(rows, per_pass: int, passes: int):
-    steps = [r for r in rows if is_step(r["Kernel_Name"])]
-    take = per_pass * passes
-    if len(steps) < take:
-        raise SystemExit(f"trace holds {len(steps)} step launches, fewer than {passes} x {per_pass}")
-    return steps[-take:]
+def library_rows(d: str):
+    """The library's kernels of a trace, in order (the runtime's copy kernels come and go)."""
+    rows = [r for r in csv.DictReader(open(os.path.join(d, "bench_kernel_trace.csv"))) if "jf::" in r["Kernel_Name"]]
+    rows.sort(key=lambda r: int(r["Start_Timestamp"]))
+    return rows
+
+
+def last_passes(rows, passes: int):
+    """The launches of the last passes of rows, and how many a pass has."""
+    p = period([r["Kernel_Name"] for r in rows])
+    if len(rows) < p * passes:
+        raise SystemExit(f"trace holds {len(rows)} launches, fewer than {passes} x {p}")
+    return rows[-p * passes:], p
+
+
+def before_profiles(rows, per_run: int, runs: int = 2):
+    """rows without the program runs at the end, which have per_run step launches each."""
+    steps = [i for i, r in enumerate(rows) if is_step(r["Kernel_Name"])]
+    if len(steps) < per_run * runs:
+        raise SystemExit(f"trace holds {len(steps)} step launches, fewer than {runs} x {per_run}")
+    return rows[:steps[-per_run * runs]]
 
 
 def trace(args):
     b = bench_line(args.log)
     n, _ = pass_shape(b)
-    rows = list(csv.DictReader(open(os.path.join(args.dir, "bench_kernel_trace.csv"))))
-    rows.sort(key=lambda r: int(r["Start_Timestamp"]))
-    sel = last_passes(rows, n, args.passes)
+    sel, p = last_passes(before_profiles(library_rows(args.dir), n), args.passes)
     by = {}
     for r in sel:
         d = (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3
@@ -86,8 +100,8 @@ def trace(args):
     total = sum(t for _, t in by.values())
     out = [f"# {args.title}", "", "Command (from the repository root, on one MI355X):", "", "    " + args.command, "",
            f"kernels.hip sha256[:16] = {kernels_sha()}", "",
-           f"Last {args.passes} program runs after autotuning, {n} contraction-step launches each "
-           f"(the launches of the autotuner itself are excluded).", "",
+           f"Last {args.passes} passes of the trace, {p} launches each (the period of the launch sequence before the "
+           "program runs that time every step).", "",
            "| kernel | launches | avg (us) | total (ms) | % |", "|---|---|---|---|---|"]
     for k, (c, t) in sorted(by.items(), key=lambda kv: -kv[1][1]):
         out.append(f"| `{k}` | {c} | {t / c:.1f} | {t / 1e3:.3f} | {100 * t / total:.2f} |")
@@ -96,12 +110,12 @@ def trace(args):
     live = ps["avg_launch_us"]
     kms = ps.get("kernel_ms_per_pass", ps.get("kernel_ms"))
     dom = b["roofline"].get("kernel")
-    dsel = [(c, t) for k, (c, t) in by.items() if dom and k.startswith(dom)]
+    dsel = [(c, t) for k, (c, t) in by.items() if dom and k.startswith(dom.rstrip(">"))]
     dc, dt = sum(c for c, _ in dsel), sum(t for _, t in dsel)
-    out += ["", f"All contraction-step launches: {len(sel)} launches, average **{avg:.1f} us** per launch, "
-            f"{total / 1e3 / args.passes:.3f} ms of step kernels per program run.",
-            f"bench.py in the profiled run (HIP events attached to every step dispatch of one program run, "
-            f"perturbed by the profiler's own instrumentation): {live:.1f} us per launch, "
+    out += ["", f"All launches: {len(sel)}, average **{avg:.1f} us** per launch, "
+            f"**{total / 1e3 / args.passes:.3f} ms** of kernels per pass.",
+            f"bench.py in the profiled run (HIP events attached to every step dispatch of one program run of {n} "
+            f"launches, perturbed by the profiler's own instrumentation): {live:.1f} us per launch, "
             f"{kms:.3f} ms per run; value {b['value']:.0f} {b['unit']} ({b['ms_per_step']:.3f} ms per pass)."]
     if dc:
         out += [f"Dominant kernel of the bench line (`roofline.kernel` = `{dom}`): {dc // args.passes} launches per run, "
@@ -112,7 +126,7 @@ def trace(args):
         cps = c["roofline"].get("pass", c["roofline"])
         lv = cps["avg_launch_us"]
         out += [f"bench.py without the profiler (`{args.live_command}`): **{lv:.1f} us** per launch "
-                f"({cps.get('kernel_ms_per_pass', cps.get('kernel_ms')):.3f} ms per run; trace / live = {avg / lv:.3f}); "
+                f"({cps.get('kernel_ms_per_pass', cps.get('kernel_ms')):.3f} ms per run of {cps['launches']}); "
                 f"value {c['value']:.0f} {c['unit']} ({c['ms_per_step']:.3f} ms per pass)."]
         if dc and c["roofline"].get("kernel") == dom:
             out += [f"Dominant kernel `{dom}` without the profiler: **{c['roofline']['avg_launch_us']:.1f} us** per launch "
@@ -130,14 +144,7 @@ def period(names, max_p=5000):
 
 def passes(args):
     b = bench_line(args.log)
-    # the library's kernels only: the runtime's copy kernels (result read-back) come and go
-    rows = [r for r in csv.DictReader(open(os.path.join(args.dir, "bench_kernel_trace.csv")))
-            if "jf::" in r["Kernel_Name"]]
-    rows.sort(key=lambda r: int(r["Start_Timestamp"]))
-    p = period([r["Kernel_Name"] for r in rows])
-    if len(rows) < p * args.passes:
-        raise SystemExit(f"trace holds {len(rows)} launches, fewer than {args.passes} x {p}")
-    sel = rows[-p * args.passes:]
+    sel, p = last_passes(library_rows(args.dir), args.passes)
     by = {}
     for r in sel:
         d = (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3
@@ -190,7 +197,9 @@ def traffic(args):
         if not copies:
             raise SystemExit(f"no calibration copy in {d}")
         scale = args.copy_mib * 1024.0 / float(copies[0]["Counter_Value"])   # true KiB / counter KiB
-        steps = last_passes(rows, n, 1)
+        steps = [r for r in rows if is_step(r["Kernel_Name"])][-n:]
+        if len(steps) != n:
+            raise SystemExit(f"counter run holds {len(steps)} step launches, fewer than {n}")
         kib = sum(float(r["Counter_Value"]) for r in steps)
         for i, r in enumerate(steps):
             per_launch_bytes[i] += float(r["Counter_Value"]) * 1024.0 * scale
