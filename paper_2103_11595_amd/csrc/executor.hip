@@ -1219,7 +1219,7 @@ jf_status enqueue_level(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipS
 jf_status lanes_of(jf_plan* p, int n, hipStream_t stream, hipStream_t* lane) {
   DevState& S = state_of(p);
   lane[0] = stream;
-  for (int l = 0; l < n; ++l) {
+  for (int l = 0; n > 1 && l < n; ++l) {
     if (!S.ev_lane[l]) JF_HIP(hipEventCreateWithFlags(&S.ev_lane[l], hipEventDisableTiming));
     if (!l) continue;
     if (!S.lane_stream[l - 1]) JF_HIP(hipStreamCreateWithFlags(&S.lane_stream[l - 1], hipStreamNonBlocking));
@@ -2289,7 +2289,10 @@ extern "C" jf_status jf_fidelity_batch(jf_plan* const* plans, int n, void* ws, s
   const int small_lane = !n_items ? -1 : !large ? 0 : lanes > 1 ? lanes - 1 : 1;
   if (small_lane >= 0) used[small_lane] = true;
   hipStream_t lane[BATCH_LANES] = {};
-  st = lanes_of(plans[0], BATCH_LANES, stream, lane);
+  int top = 0;  // lanes up to the last used one: a batch of small circuits makes no streams
+  for (int l = 0; l < BATCH_LANES; ++l)
+    if (used[l]) top = l;
+  st = lanes_of(plans[0], top + 1, stream, lane);
   if (st != JF_OK) return st;
   // the launches of one lane, or of all (which = -1)
   auto enqueue_lane = [&](int which) -> jf_status {
