@@ -41,11 +41,11 @@ struct DevLayout {
   size_t desc_off = 0, pool_off = 0, const_off = 0, buf_off = 0, out_off = 0, sums_off = 0, total = 0;
   size_t image_end = 0;  // end of the host image (descriptors, operators, constants, LDS tables)
   size_t sumsq_off = 0;  // scratch of the two-pass sum of |t|^2 (2 SUMSQ_BLOCKS doubles)
-  size_t res_off = 0;    // F_J, 1 - F_J, |Im|, written by the device
+  size_t res_off = 0;    // F_J, 1 - F_J, |Im|, written by the device; behind the failure word
   size_t lds_items_off = 0, lds_steps_off = 0;
   size_t ctr_off = 0;    // counter of the persistent launch's fused assembly (zero in the image)
   size_t fail_off = 0;   // failure word of the grid runs (zero in the image)
-  size_t flags_off = 0;  // barrier flags of the grid runs (zero in the image)
+  size_t flags_off = 0;  // barrier flags of the grid runs (as in the image before a run that gives up)
   // the variants of a sliced component's first sliced level run in slice_lanes lanes: the level
   // buffers of the lanes after the first, lane_stride apart, lie behind total
   int slice_lanes = 1;
@@ -332,6 +332,10 @@ void balanced_round(const std::vector<cd>& M, std::vector<float>& out) {
 // longest runs, and the other steps get a launch each.
 constexpr size_t kGridTableBytes = 4 << 20;
 constexpr size_t kNoTable = ~size_t(0);  // the run has no table: a launch per step
+constexpr size_t kResBehindFail = 32;
+// A second set of barrier flags lies one word behind the first; a pass whose wait is 0 uses it.  The last
+// workgroup's flag starts so far back there that the others' wait for it cannot end.
+constexpr unsigned kFlagBehind = 0xC0000000u;
 
 // The device descriptors of a grid run: where each step's tensors are (a step whose tensors hold at
 // most 2^GRID_LOCAL elements runs in every workgroup's LDS; the last step of a run that is not the
@@ -477,6 +481,7 @@ void build_layout(const Program& P, DevState& S) {
   off += align256(size_t(L.lds_steps) * sizeof(LdsStep));
   L.ctr_off = off;
   L.fail_off = off + 128;
+  L.res_off = L.fail_off + kResBehindFail;  // one copy reads both
   off += 256;
   // blocks: descriptors; grid runs: barrier flags and descriptors, the longest runs first
   L.run_desc.resize(P.comps.size());
@@ -526,8 +531,6 @@ void build_layout(const Program& P, DevState& S) {
     }
   L.sums_off = off;
   off += align256(P.comps.size() * 4 * sizeof(double));
-  L.res_off = off;
-  off += 256;
   L.sumsq_off = off;
   off += align256(2 * SUMSQ_BLOCKS * sizeof(double));
   // the level buffers last: the members of a batch that run one after another share one buffer
@@ -556,6 +559,9 @@ void build_layout(const Program& P, DevState& S) {
 
   // host image of descriptors, pools and constants
   S.host_image.assign(L.image_end, 0);
+  for (int l = 0; L.grid && l < L.slice_lanes; ++l)
+    std::memcpy(&S.host_image[L.flags_off + (size_t((l + 1) * GRID_WGS - 1) * GRID_FLAG_STRIDE + 1) * sizeof(unsigned)],
+                &kFlagBehind, sizeof(kFlagBehind));
   for (size_t c = 0; c < P.comps.size(); ++c)
     for (size_t s = 0; s < P.comps[c].steps.size(); ++s) {
       const Step& st = P.comps[c].steps[s];
@@ -889,7 +895,7 @@ jf_status enqueue_steps(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipS
 std::map<std::vector<long long>, int> g_run_cache;
 
 // After a give-up: no grid runs from here on, in captured programs neither, and the failure word and
-// the barrier flags as they were uploaded, zero.
+// the barrier flags as they were uploaded.
 jf_status leave_grid(jf_plan* p, unsigned char* ws, hipStream_t stream) {
   DevState& S = state_of(p);
   const DevLayout& L = S.lay;
@@ -994,7 +1000,8 @@ jf_status enqueue_steps(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipS
         a.in = cur;
         a.buf[0] = b0;
         a.buf[1] = b1;
-        a.flags = reinterpret_cast<unsigned*>(ws + L.flags_off) + gu->lane * GRID_WGS * GRID_FLAG_STRIDE;
+        a.flags = reinterpret_cast<unsigned*>(ws + L.flags_off) + gu->lane * GRID_WGS * GRID_FLAG_STRIDE +
+                  (S.grid_wait > 0 ? 0 : 1);
         a.fail = reinterpret_cast<unsigned*>(ws + L.fail_off);
         a.limit = S.grid_wait;
         const GridStep* hs = reinterpret_cast<const GridStep*>(&S.host_image[L.run_desc[c][q]]);
@@ -1556,7 +1563,8 @@ jf_status read_results(jf_plan* p, unsigned char* ws, hipStream_t stream, jf_res
   DevState& S = state_of(p);
   double res[4];
   const bool on_host = res_at.host != nullptr;
-  if (!on_host) JF_HIP(hipMemcpyAsync(res, ws + S.lay.res_off, sizeof(res), hipMemcpyDeviceToHost, stream));
+  unsigned char copied[kResBehindFail + sizeof(res)];  // the failure word and the result
+  if (!on_host) JF_HIP(hipMemcpyAsync(copied, ws + S.lay.fail_off, sizeof(copied), hipMemcpyDeviceToHost, stream));
   // the traces: put in order on the device, chunk by chunk through a pinned landing area (half of it
   // fills while the other is copied out); without host allocations, gathered on the host
   TermArgs ta;
@@ -1583,8 +1591,10 @@ jf_status read_results(jf_plan* p, unsigned char* ws, hipStream_t stream, jf_res
   }
   if (total > kTermChunk && on_device) JF_HIP(hipEventSynchronize(S.ev_terms[0]));
   else JF_HIP(hipStreamSynchronize(stream));
-  if (on_host) std::memcpy(res, res_at.host, sizeof(res));
-  *gave_up = res[3] != 0.0;
+  unsigned failed = 0;
+  if (!on_host) std::memcpy(&failed, copied, sizeof(failed));
+  std::memcpy(res, on_host ? reinterpret_cast<unsigned char*>(res_at.host) : copied + kResBehindFail, sizeof(res));
+  *gave_up = failed != 0 || res[3] != 0.0;
   if (*gave_up) return JF_OK;
   jf_result r;
   static_result(P, &r);

@@ -1691,7 +1691,8 @@ __global__ __launch_bounds__(PERSIST_NT) void k_persistent(const LdsItem* __rest
 // 1 MB, 1.58 up to 2 MB, 1.56 without runs).
 //
 // The wait is bounded: past a.limit a workgroup sets *fail and leaves, launches that find *fail set
-// do nothing, and the assembly, or the launch that was to do it, reports it, so that the host runs
+// do nothing, and the assembly reports it, or the host finds no result where this launch was to
+// assemble (a report from the early ways out costs scalar registers, 1-3% of every run): it runs
 // the pass again launch by launch.
 //
 // Arithmetic: FP64 matrix cores on the real embedding (as k_absorb_mfma_rd) whatever the form; the
@@ -1897,25 +1898,20 @@ __device__ __forceinline__ void grid_products(GridShared& sh, const GridStep& sd
 // Wait, in wave 0, until every workgroup's flag has reached `want`; past the limit *fail is set.
 __device__ __forceinline__ void grid_wait(GridShared& sh, const GridArgs& a, unsigned want) {
   const long long t0 = wall_clock64();
-  bool done = false, late = a.limit <= 0;  // a limit of 0: given up before the first look
-  for (int polls = 1; !late; ++polls) {
+  bool done = false;
+  for (int polls = 1;; ++polls) {
     if (!done)
       done = int(__hip_atomic_load(a.flags + threadIdx.x * GRID_FLAG_STRIDE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) -
                  want) >= 0;
     if (__all(done)) return;
-    late = (polls & 31) == 0 && wall_clock64() - t0 >= a.limit;
+    if ((polls & 31) == 0 && wall_clock64() - t0 >= a.limit) {
+      if (threadIdx.x == 0) {
+        sh.ok = 0;
+        __hip_atomic_store(a.fail, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      return;
+    }
   }
-  if (threadIdx.x == 0) {
-    sh.ok = 0;
-    __hip_atomic_store(a.fail, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-}
-
-// A run that was to assemble F_J and leaves before that reports the pass as void itself.
-__device__ __forceinline__ void grid_void(const GridArgs& a) {
-  if (blockIdx.x != 0 || threadIdx.x != 0 || !a.as.res) return;
-  a.as.res[3] = 1.0;
-  if (a.as.host) a.as.host[3] = 1.0;
 }
 
 __global__ __launch_bounds__(GRID_NT) void k_grid(GridArgs a) {
@@ -1937,7 +1933,7 @@ __global__ __launch_bounds__(GRID_NT) void k_grid(GridArgs a) {
     if (a.n > 1) reinterpret_cast<int*>(&sh.sd[1])[tid] = reinterpret_cast<const int*>(a.steps + 1)[tid];
   }
   __syncthreads();
-  if (!sh.ok) return grid_void(a);
+  if (!sh.ok) return;
   const unsigned base = sh.base;
   {
     const GridShape g0 = GridShape::unpack(grid_uniform(sh.shape[0]));
@@ -2032,7 +2028,7 @@ __global__ __launch_bounds__(GRID_NT) void k_grid(GridArgs a) {
     }
     if (exchange && tid < GRID_WGS) grid_wait(sh, a, base + epoch);  // wave 0: one flag per lane
     __syncthreads();  // operator, descriptor and (exchange) every workgroup's output visible
-    if (!sh.ok) return grid_void(a);
+    if (!sh.ok) return;
   }
   // the end of the run
   if (blockIdx.x != 0) return;
