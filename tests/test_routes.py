@@ -119,3 +119,24 @@ def test_blocks_of_other_tiles_are_timed_apart(dtype):
     jf.jf_autotune(p, ws, reps=1)
     assert p.last_pass()["joint_timings"] == 0  # known by now
     _same(p, jf.jf_fidelity_alg1(p, ws), fj, dtype)
+
+
+@pytest.mark.parametrize("dtype", ["c64", "bf16x6"])
+@pytest.mark.parametrize("case", [(7, 300, 5, 22, 1), (7, 300, 5, 22, 2), (8, 220, 3, 22, 1)])
+def test_runs_beside_chains_against_oracle(case, dtype):
+    """Small steps that a chain runs faster stay in it, between the runs of the others."""
+    n, gates, sites, seed, alg = case
+    inst = gen.random_circuit(n, gates, sites, 1e-3, 1e-2, seed)
+    p = jf.plan(inst, alg, dtype, flags=QUICK)
+    steps = p.describe()
+    ref = dense.fidelity_alg1(inst, want_terms=True)
+    ws = jf.workspace(p.info()["workspace_bytes"])
+    ws.fill_(255)  # NaN wherever a launch leaves something unwritten
+    jf.jf_workspace_release(ws)
+    print("[gpu-test] runs beside chains", case, dtype, flush=True)
+    got = jf.jf_fidelity_alg1(p, ws, want_terms=True) if alg == 1 else jf.jf_fidelity_alg2(p, ws)
+    assert p.last_pass()["grid_steps"] == sum(s["run"] >= 0 for s in steps) < len(steps)
+    assert p.last_pass()["grid_launches"] == len({s["run"] for s in steps if s["run"] >= 0}) > 1
+    assert abs(got["fj"] - ref["fj"]) <= 1e-6
+    if alg == 1:
+        assert np.max(np.abs(got["terms"] - np.array([ref["terms"][k] for k in sorted(ref["terms"])]))) <= 1e-6
