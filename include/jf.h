@@ -134,10 +134,12 @@ typedef struct jf_plan jf_plan;
                                   and replay it (see there) */
 #define JF_FLAG_NO_CHAIN 16u   /* run every step as its own launch: no chains of in-place complex64
                                   steps applied to one LDS tile per HBM pass (same results bit for
-                                  bit; chains are the default), no runs of small steps in one
-                                  launch (FP64 arithmetic: results of the form's accuracy) */
-#define JF_FLAG_SMALL_BLOCKS 32u /* test aid: blocks of steps on one LDS tile at any size (the default
-                                    keeps them to large tensors), and no runs of small steps */
+                                  bit; chains are the default), no blocks of steps that change the
+                                  tensor's size on one LDS tile (Gauss-form products), no runs of
+                                  small steps in one launch (FP64 arithmetic); results of the form's
+                                  accuracy */
+#define JF_FLAG_SMALL_BLOCKS 32u /* test aid: blocks at any size (the default keeps them to tensors of
+                                    2^21 elements and more), and no runs of small steps */
 /* Search effort of the planner: JF_FLAG_EFFORT(e), e = 1..15, runs 2^(e+5) randomised greedy
  * restarts per component.  The default (e = 0 in the flags) sizes the search to the network:
  * min(2^17, max(2^12, 8e7 / tensors)) restarts, i.e. 2^17 up to ~600 tensors and 2^16 at ~1200,
@@ -361,10 +363,13 @@ typedef enum {
  * can run the step (a warm-up launch, then reps launches between HIP events, on the step's own
  * input and output buffers) and keeps the fastest for all later runs of this plan; a chain of
  * steps is timed as one launch against its steps run one launch each (with their tuned kernels)
- * and the faster is kept, and so is a run of small steps in one launch against theirs.  The
+ * and the faster is kept, and so are a block of steps and a run of small steps in one launch against
+ * theirs.  The
  * workspace contents are undefined afterwards (no result is produced).  Choices are cached for
- * the process by step shape (arithmetic, kS, kN, rows per tile, tile count, in place or not) and
- * by chain shape, so plans sharing shapes are tuned once.  A chain computes exactly what its steps
+ * the process by step shape (arithmetic, kS, kN, rows per tile, tile count, in place or not), by
+ * chain shape, and for blocks and runs by their steps' shapes, a block's tile and the chains beside
+ * it, so plans sharing shapes are tuned once; a run that gives up its barrier while it is timed is
+ * not used and not remembered.  A chain computes exactly what its steps
  * compute with the Gauss kernels (same products in the same order).  Kernels sum in different orders, so a tuned plan may
  * differ from an untuned one in the last bits; replays of a tuned plan are bitwise identical.
  * reps <= 0 means 3.  Synchronises the stream.  Errors: JF_E_ARG, JF_E_OOM (workspace too
@@ -375,10 +380,10 @@ jf_status jf_autotune(jf_plan* plan, void* dev_ws, size_t ws_bytes, void* stream
 /*
  * jf_set_kernel_variant -- force one kernel (jf_kernel_variant) on every step it can run; the
  * other steps keep the AUTO rule.  Chains stay chains under JF_KV_GAUSS_256 / 512 (they compute
- * the Gauss form) and are split into their steps under the other kernels; small steps then get a
- * launch each.  JF_KV_AUTO restores the
- * rule, the chains and the runs of small steps everywhere (and so undoes jf_autotune).  For testing each kernel against
- * the oracle.  Host only.  Errors: JF_E_ARG (JF_KV_CHAIN is not a per-step kernel).
+ * the Gauss form) and are split into their steps under the other kernels; under every forced kernel
+ * the steps of blocks and of runs get a launch each.  JF_KV_AUTO restores the rule, the chains, the
+ * blocks and the runs everywhere (and so undoes jf_autotune).  For testing each kernel against the
+ * oracle.  Host only.  Errors: JF_E_ARG (JF_KV_CHAIN is not a per-step kernel).
  */
 jf_status jf_set_kernel_variant(jf_plan* plan, int variant);
 

@@ -7,16 +7,16 @@ files only, runs nothing on the GPU).
         --out profiles/Y.md --json profiles/Z.json --command "..."
 
 ``trace`` reads a ``--kernel-trace`` run of bench.py and reports, per kernel name, the launches of
-the last passes (before the two program runs that bench.py ends with, which launch every small step
+the last passes (before the program runs that bench.py ends with, which launch every small step
 by itself to time it; the passes run small steps several to a launch: the period of the launch
 sequence there, as in ``passes``), and the dominant kernel's average duration next to the live
 HIP-event average bench.py printed.
 
 ``passes`` reads a ``--kernel-trace`` run of any bench.py workload whose passes repeat one fixed
 launch sequence of the library's kernels (graph replays, eager runs of one plan): the period is
-found from the end of the trace (the shortest sequence of kernel names that the last three
-repetitions share), and the last ``--passes`` periods are summarised per kernel, with the device
-time and the span of a pass.
+found from the end of the trace (the shortest sequence of kernel names that repeats ``--passes``
+times there), and those periods are summarised per kernel, with the device time and the span of a
+pass.
 
 ``mfma`` reads one ``--pmc`` run of bench.py with the matrix-core counters (``MfmaUtil``: busy cycles
 of the MFMA units over the dispatch's active cycles and SIMDs; ``SQ_INSTS_VALU_MFMA_MOPS_*``:
@@ -71,26 +71,32 @@ def library_rows(d: str):
     return rows
 
 
-def last_passes(rows, passes: int):
-    """The launches of the last passes of rows, and how many a pass has."""
-    p = period([r["Kernel_Name"] for r in rows])
-    if len(rows) < p * passes:
-        raise SystemExit(f"trace holds {len(rows)} launches, fewer than {passes} x {p}")
-    return rows[-p * passes:], p
+def period(names, max_p=5000):
+    for p in range(1, min(max_p, len(names) // 3) + 1):
+        if names[-p:] == names[-2 * p:-p] == names[-3 * p:-2 * p]:
+            return p
+    raise SystemExit("no repeating launch sequence at the end of the trace")
 
 
-def before_profiles(rows, per_run: int, runs: int = 2):
-    """rows without the program runs at the end, which have per_run step launches each."""
-    steps = [i for i, r in enumerate(rows) if is_step(r["Kernel_Name"])]
-    if len(steps) < per_run * runs:
-        raise SystemExit(f"trace holds {len(steps)} step launches, fewer than {runs} x {per_run}")
-    return rows[:steps[-per_run * runs]]
+def last_passes(rows, passes: int, tail: int = 1000):
+    """The launches of the last passes of rows, and how many a pass has: the shortest sequence of kernel names
+    that repeats that often up to the end, or up to at most tail launches before it (program runs that
+    launch every small step by itself end a bench run, and are no passes)."""
+    names = [r["Kernel_Name"] for r in rows]
+    for end in range(len(names), max(0, len(names) - tail), -1):
+        try:
+            p = period(names[:end], end // passes)
+        except SystemExit:
+            continue
+        if names[end - p * passes:end] == names[end - p:end] * passes:
+            return rows[end - p * passes:end], p
+    raise SystemExit(f"no launch sequence that repeats {passes} times at the end of the trace")
 
 
 def trace(args):
     b = bench_line(args.log)
     n, _ = pass_shape(b)
-    sel, p = last_passes(before_profiles(library_rows(args.dir), n), args.passes)
+    sel, p = last_passes(library_rows(args.dir), args.passes)
     by = {}
     for r in sel:
         d = (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3
@@ -101,7 +107,7 @@ def trace(args):
     out = [f"# {args.title}", "", "Command (from the repository root, on one MI355X):", "", "    " + args.command, "",
            f"kernels.hip sha256[:16] = {kernels_sha()}", "",
            f"Last {args.passes} passes of the trace, {p} launches each (the period of the launch sequence before the "
-           "program runs that time every step).", "",
+           "program runs that time every step by itself).", "",
            "| kernel | launches | avg (us) | total (ms) | % |", "|---|---|---|---|---|"]
     for k, (c, t) in sorted(by.items(), key=lambda kv: -kv[1][1]):
         out.append(f"| `{k}` | {c} | {t / c:.1f} | {t / 1e3:.3f} | {100 * t / total:.2f} |")
@@ -133,13 +139,6 @@ def trace(args):
                     f"(`roofline.avg_launch_us`; trace / live = {dt / dc / c['roofline']['avg_launch_us']:.3f})."]
     open(args.out, "w").write("\n".join(out) + "\n")
     print("\n".join(out))
-
-
-def period(names, max_p=5000):
-    for p in range(1, min(max_p, len(names) // 3) + 1):
-        if names[-p:] == names[-2 * p:-p] == names[-3 * p:-2 * p]:
-            return p
-    raise SystemExit("no repeating launch sequence at the end of the trace")
 
 
 def passes(args):

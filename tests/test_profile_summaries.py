@@ -24,7 +24,7 @@ def _log(tmp_path, kernel="k_block<float>"):
 
 
 def test_a_trace_summary_counts_the_launches_of_a_pass(tmp_path):
-    # passes: one launch for the two small steps, the block, the chain, the sum; then two program runs with a
+    # passes: one launch for the two small steps, the block, the chain, the sum; then the program runs with a
     # launch for every step, which are no passes
     one_pass = [("jf::k_grid(jf::GridArgs)", 5), (STEPS[2], 20), (STEPS[3], 30), ("jf::k_sumsq_one(double2)", 2)]
     one_run = list(zip(STEPS, (4, 4, 20, 30))) + [("jf::k_sumsq_one(double2)", 2), ("jf::k_assemble(jf::AssembleArgs)", 1)]
@@ -32,15 +32,15 @@ def test_a_trace_summary_counts_the_launches_of_a_pass(tmp_path):
         w = csv.writer(f)
         w.writerow(["Kernel_Name", "Start_Timestamp", "End_Timestamp"])
         t = 0
-        for name, us in [("void jf::k_absorb_mfma<tune>(jf::StepDesc const*)", 9)] * 3 + one_pass * 4 + one_run * 2:
+        for name, us in [("void jf::k_absorb_mfma<tune>(jf::StepDesc const*)", 9)] * 3 + one_pass * 5 + one_run * 3:
             w.writerow([name, t, t + 1000 * us])
             t += 1000 * us + 500
     out = tmp_path / "t.md"
-    profsum.trace(Namespace(dir=str(tmp_path), log=_log(tmp_path), passes=3, out=str(out), title="t", command="c",
+    profsum.trace(Namespace(dir=str(tmp_path), log=_log(tmp_path), passes=4, out=str(out), title="t", command="c",
                             live_log=None, live_command="x"))
     text = out.read_text()
-    assert "Last 3 passes of the trace, 4 launches each" in text
-    for row in ("| `k_grid` | 3 | 5.0 |", "| `k_block<float, 16>` | 3 | 20.0 |", "| `k_chain<256>` | 3 | 30.0 |"):
+    assert "Last 4 passes of the trace, 4 launches each" in text
+    for row in ("| `k_grid` | 4 | 5.0 |", "| `k_block<float, 16>` | 4 | 20.0 |", "| `k_chain<256>` | 4 | 30.0 |"):
         assert row in text
     assert "k_absorb" not in text and "0.057 ms" in text
     assert "(`roofline.kernel` = `k_block<float>`): 1 launches per run, average **20.0 us**" in text
