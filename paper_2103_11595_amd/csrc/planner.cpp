@@ -354,9 +354,9 @@ void chain_tables(const ComponentProgram& cp, const Chain& ch, ChainTables& out)
 }
 
 // Sizes up to which a step joins a grid run: 1 MB of storage on either side (2^16 complex128 or
-// 2^17 complex64 elements).  Measured on MI355X, complex64: a sliced 10-qubit plan 1.39 / 1.37 / 1.58
-// ms a pass with 0.5 / 1 / 2 MB, a batch of 40 circuits 2.70 / 2.71 / 3.04 ms; complex128, an 11-step
-// program of 2^16 elements, 91 / 68 / 68 us.
+// 2^17 complex64 elements).  Measured on MI355X with every such step in a run and one lane, complex64: a
+// sliced 10-qubit plan 1.39 / 1.37 / 1.58 ms a pass with 0.5 / 1 / 2 MB, a batch of 40 circuits 2.70 /
+// 2.71 / 3.04 ms; complex128, an 11-step program of 2^16 elements, 91 / 68 / 68 us.
 static constexpr int kGridMaxBytesLog2 = 20;
 
 bool grid_step_ok(const Step& st) {
