@@ -201,11 +201,10 @@ jf_status jf_plan_stats_get(const jf_plan* plan, jf_plan_stats* stats);
 
 /* Text description of the lowered program, one line per device step:
  * "comp step level kS kN L rA rC tiles in_prec out_prec compute nvar flops bytes rowsA rowsC sA nC
- *  chain run", rowsA .. nC being comma-separated bit positions (A for tile rows and summed legs, C for
+ *  chain", rowsA .. nC being comma-separated bit positions (A for tile rows and summed legs, C for
  * tile rows and new legs; "-" when empty).  compute is f64, f32, f32x2 (FP32 with the operator kept
  * as an FP32 pair), split or split4 (the split form; split4 with the fourth operator piece).  chain is the index (within the component) of the chain the step
- * belongs to, -1 if it runs as its own launch (see JF_FLAG_NO_CHAIN); run is the index of the run of
- * small steps that it belongs to, -1 if none (a chain whose steps are in one is not launched).
+ * belongs to, -1 if it runs as its own launch (see JF_FLAG_NO_CHAIN).
  * Writes at most len bytes (NUL-terminated) and returns the full length needed. Host only. */
 long long jf_plan_describe(const jf_plan* plan, char* buf, long long len);
 

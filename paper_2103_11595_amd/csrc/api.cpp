@@ -150,9 +150,6 @@ extern "C" long long jf_plan_describe(const jf_plan* p, char* buf, long long len
     for (size_t lv = 0; lv < cp.levels.size(); ++lv)
       for (int s = cp.levels[lv].first; s < cp.levels[lv].last; ++s) {
         const Step& st = cp.steps[s];
-        int run = -1;
-        for (size_t q = 0; q < cp.runs.size(); ++q)
-          if (s >= cp.runs[q].first && s < cp.runs[q].last) run = int(q);
         char line[256];
         snprintf(line, sizeof(line), "%zu %d %zu %d %d %d %d %d %lld %s %s %s %d %.6g %.6g", c, s, lv, st.kS, st.kN, st.L,
                  st.rA, st.rC, st.nTiles, pn[st.in_prec], pn[st.out_prec],
@@ -172,7 +169,7 @@ extern "C" long long jf_plan_describe(const jf_plan* p, char* buf, long long len
           return b.empty() ? std::string("-") : b;
         };
         out += " " + bits(st.offR_A, st.L) + " " + bits(st.offR_C, st.L) + " " + bits(st.offS_A, st.kS) + " " +
-               bits(st.offN_C, st.kN) + " " + std::to_string(st.chain) + " " + std::to_string(run) + "\n";
+               bits(st.offN_C, st.kN) + " " + std::to_string(st.chain) + "\n";
       }
   }
   if (buf && len > 0) {

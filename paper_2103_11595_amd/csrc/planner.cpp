@@ -387,60 +387,14 @@ void grid_tables(const Step& st, GridTables& out) {
         }
 }
 
-// Microseconds of small launches in a pass: one step's, a chain's, a step's in a grid run.  Fitted to 2725
-// programs of 5 to 25 qubits in the three forms, each timed with its runs and launch by launch (MI355X,
-// graph replay; 2-7% rms).  A step costs 3.9 us in a run and its own launch 5.1-7.3, but a chain of
-// FP32 steps 5.7 and only 1.1 a step more: a run over four chained in-place steps of 2^16 elements
-// takes 24 us, their chain 11.
-static double small_launch_us(const Step& st) {
-  const double gf = st.flops * 1e-9;
-  if (st.compute == C_F64) return 6.4 + 28.7 * gf;
-  if (st.compute == C_F32) return st.two_term ? 7.3 + 28.0 * gf : 6.0 + 9.4 * gf;
-  return st.two_term ? 5.1 + 18.0 * gf : 5.8 + 12.5 * gf;
-}
-static double small_chain_us(const ComponentProgram& cp, const Chain& ch) {
-  const double gf = ch.flops * 1e-9;
-  bool pairs = false;
-  for (int q = ch.first; q < ch.last; ++q) pairs = pairs || cp.steps[q].two_term;
-  if (cp.steps[ch.first].compute == C_SPLIT) return 1.7 + 2.7 * (ch.last - ch.first) + 7.6 * gf;
-  return pairs ? 6.3 + 1.2 * (ch.last - ch.first) + 12.5 * gf : 5.7 + 1.1 * (ch.last - ch.first) + 6.7 * gf;
-}
-static double run_step_us(const Step& st) {
-  return (st.rA <= GRID_LOCAL && st.rC <= GRID_LOCAL ? 2.3 : 3.9) + 60.0 * st.flops * 1e-9;
-}
-constexpr double kRunUs = 2.7;
-
-// Grid runs of one level: the cheapest partition of its steps into launches -- single steps, the chains
-// as they stand, runs of two steps and more that may join one.  A chain is launched whole or not at
-// all: its steps may join runs from its first one on.
+// Grid runs of one level: every maximal run of two or more steps that may join one.
 static void build_level_runs(ComponentProgram& cp, int first, int last) {
-  const int n = last - first;
-  std::vector<double> best(n + 1, 1e300);
-  std::vector<int> from(n + 1, 0);
-  std::vector<char> run(n + 1, 0);
-  best[0] = 0;
-  auto relax = [&](int i, int j, double t, bool r) {
-    if (best[i] + t < best[j]) {
-      best[j] = best[i] + t;
-      from[j] = i;
-      run[j] = r;
-    }
-  };
-  for (int i = 0; i < n; ++i) {
-    const Step& st = cp.steps[first + i];
-    const bool head = st.chain >= 0 && cp.chains[st.chain].first == first + i;
-    if (head) relax(i, cp.chains[st.chain].last - first, small_chain_us(cp, cp.chains[st.chain]), false);
-    else relax(i, i + 1, small_launch_us(st), false);
-    double t = kRunUs;
-    for (int j = i; j < n && j - i < GRID_MAX_STEPS && grid_step_ok(cp.steps[first + j]); ++j) {
-      t += run_step_us(cp.steps[first + j]);
-      if (j > i) relax(i, j + 1, t, true);
-    }
+  for (int i = first; i < last;) {
+    int j = i;
+    while (j < last && j - i < GRID_MAX_STEPS && grid_step_ok(cp.steps[j])) ++j;
+    if (j - i >= 2) cp.runs.push_back({i, j});
+    i = std::max(j, i + 1);
   }
-  std::vector<GridRun> got;
-  for (int j = n; j > 0; j = from[j])
-    if (run[j]) got.push_back({first + from[j], first + j});
-  cp.runs.insert(cp.runs.end(), got.rbegin(), got.rend());
 }
 
 // ------------------------------------------------------------------------------ blocks ---

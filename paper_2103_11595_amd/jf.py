@@ -230,7 +230,7 @@ class Plan:
         buf = C.create_string_buffer(int(n))
         L.jf_plan_describe(self.ptr, buf, n)
         keys = ["comp", "step", "level", "kS", "kN", "L", "rA", "rC", "tiles", "in_prec", "out_prec", "compute",
-                "nvar", "flops", "bytes", "rowsA", "rowsC", "sA", "nC", "chain", "run"]
+                "nvar", "flops", "bytes", "rowsA", "rowsC", "sA", "nC", "chain"]
 
         def conv(k, v):
             if k in ("in_prec", "out_prec", "compute"):

@@ -2,8 +2,6 @@
 members of a batch in lanes beside each other, and neither where it is switched off or cannot be.
 Results against the dense oracle or the emulated program within the bars of the forms (complex128 1e-12,
 complex64 1e-6)."""
-import functools
-
 import numpy as np
 import pytest
 
@@ -121,29 +119,3 @@ def test_blocks_of_other_tiles_are_timed_apart(dtype):
     jf.jf_autotune(p, ws, reps=1)
     assert p.last_pass()["joint_timings"] == 0  # known by now
     _same(p, jf.jf_fidelity_alg1(p, ws), fj, dtype)
-
-
-@functools.lru_cache(None)
-def _reference(n, gates, sites, seed):
-    ref = dense.fidelity_alg1(gen.random_circuit(n, gates, sites, 1e-3, 1e-2, seed), want_terms=True)
-    return ref["fj"], np.array([ref["terms"][k] for k in sorted(ref["terms"])])
-
-
-@pytest.mark.parametrize("dtype", ["c64", "bf16x6"])
-@pytest.mark.parametrize("case", [(7, 300, 5, 22, 1), (7, 300, 5, 22, 2), (8, 220, 3, 22, 1)])
-def test_runs_beside_chains_against_oracle(case, dtype):
-    """Small steps that a chain runs faster stay in it, between the runs of the others."""
-    n, gates, sites, seed, alg = case
-    p = jf.plan(gen.random_circuit(n, gates, sites, 1e-3, 1e-2, seed), alg, dtype, flags=QUICK)
-    steps = p.describe()
-    fj, terms = _reference(n, gates, sites, seed)
-    ws = jf.workspace(p.info()["workspace_bytes"])
-    ws.fill_(255)  # NaN wherever a launch leaves something unwritten
-    jf.jf_workspace_release(ws)
-    print("[gpu-test] runs beside chains", case, dtype, flush=True)
-    got = jf.jf_fidelity_alg1(p, ws, want_terms=True) if alg == 1 else jf.jf_fidelity_alg2(p, ws)
-    assert p.last_pass()["grid_steps"] == sum(s["run"] >= 0 for s in steps) < len(steps)
-    assert p.last_pass()["grid_launches"] == len({s["run"] for s in steps if s["run"] >= 0}) > 1
-    assert abs(got["fj"] - fj) <= 1e-6
-    if alg == 1:
-        assert np.max(np.abs(got["terms"] - terms)) <= 1e-6
