@@ -1240,8 +1240,8 @@ jf_status lanes_of(jf_plan* p, int n, hipStream_t stream, hipStream_t* lane) {
 // lanes > 1: the variants of the first sliced level, with all below them, are dealt to that many
 // lanes beside each other (a step of one of them is bound by its launch or by the 64 workgroups of
 // its grid run), each with level buffers and barrier flags of its own; the launches go out to the
-// lanes in turn.  A plan of 16 leaves of 2^16 elements takes 1164 us one leaf after another and 435 in
-// four lanes; 474-645 with other plans' streams alive, where lanes share a hardware queue.
+// lanes in turn.  A plan of 16 leaves of 2^16 elements takes 1265 us one leaf after another and 531 in
+// four lanes; up to 720 with other plans' streams alive, where lanes can share a hardware queue.
 jf_status enqueue_component(jf_plan* p, unsigned char* ws, unsigned char* bufs, hipStream_t stream, size_t c, Prof* prof,
                             Tune* tune, GridUse* gu, int lanes = 1) {
   const ComponentProgram& cp = p->prog.comps[c];
@@ -2146,8 +2146,8 @@ extern "C" jf_status jf_fidelity_alg2(jf_plan* p, void* ws, size_t ws_bytes, voi
 // few workgroups they have, so lanes overlap; a member with buffers beyond kLaneBytes fills the
 // device by itself, and all of those share the first lane, so that the workspace grows by at most
 // BATCH_LANES - 1 times kLaneBytes.  Longest members first, each to the lane with the least work.
-// 40 uneven circuits of up to 11 qubits take 2383 us in one lane and 1479 in four, captured or launched
-// call by call; 1515-1920 with other plans' streams alive, where lanes share a hardware queue.  As
+// 40 uneven circuits of up to 11 qubits take 2474 us in one lane and 1457 in four (1549 launched call by
+// call); up to 1930 with other plans' streams alive, where lanes can share a hardware queue.  As
 // branches of one graph (its nodes are submitted branch after branch) they took 1822 us where a graph per
 // lane took 1490.  96 circuits of four qubits took 320 us with an assembly launch each and 135 with one
 // for all.
